@@ -1,0 +1,235 @@
+"""The work that the speed of this framework is judged by: prefill attention of one layer, called as a program
+that uses the library calls it.
+
+  path   quantize_qk -> select -> sparse_attn, the three calls of the sparse prefill
+  dense  dense_attn, which short prompts use and which the sparse path is compared with
+
+`listed` holds one case for each way the library is used, from one head of 2048 tokens to the 128K layer; `draw` gives
+more of the same ranges.  A case:
+
+  call             "path" or "dense"
+  tokens           length of the token axis (of all sequences together where lengths is given)
+  lengths          "": every batch entry is one sequence; otherwise the comma-separated lengths of a packed batch
+  batch, q_heads, kv_heads
+  block_k          64, or 32 (the paper's block shape); segments: the paper's rule for the local area
+  attn             "bf16", "int8" (8-bit first product) or "fp8" (also the second product)
+  layout           "bhnd": contiguous heads; "bnhd": views of [batch, token, head, channel] projection outputs
+  keep             the program keeps outputs and workspaces from call to call; otherwise every call allocates its own
+  lse              the program also asks for the log-sum-exp of every row
+"""
+import math
+
+import torch
+
+from paper_2505_24179_amd import sale
+from paper_2505_24179_amd.inputs import LLAMA_32K, TOY
+
+HEAD_DIM = 128
+
+# The largest batch * query heads * length^2 that `draw` gives: the largest listed case's.
+_MOST_PATH = 32 * 131072 ** 2
+_MOST_DENSE = _MOST_PATH // 6      # (a dense pass costs several times a sparse one of the same length)
+
+
+def _case(name, call, tokens, q_heads, kv_heads, batch=1, lengths="", block_k=64, segments=False, attn="bf16",
+          layout="bhnd", keep=True, lse=False):
+    return dict(name=name, call=call, tokens=tokens, lengths=lengths, batch=batch, q_heads=q_heads, kv_heads=kv_heads,
+                block_k=block_k, segments=segments, attn=attn, layout=layout, keep=keep, lse=lse)
+
+
+def listed():
+    return [
+        # one head, every buffer allocated by the call: the smallest use, where launches and latency are what counts
+        _case("one-head-2k", "path", 2048, 1, 1, keep=False),
+        # a short prompt of a Llama-3.1-8B-shaped layer: too short for sparsity, the dense kernel serves it
+        _case("dense-1k", "dense", 1024, 32, 8),
+        # an ordinary prompt whose length is one block more than a whole mask word
+        _case("layer-4k", "path", 4160, 32, 8),
+        # a batch of two prompts with three query heads per KV head, read in place from projection outputs, with lse
+        _case("batch2-gqa3-7k", "path", 6976, 6, 2, batch=2, layout="bnhd", keep=False, lse=True),
+        # one sweep per row: the longest prompt below the windowed sweep
+        _case("layer-16k", "path", 16384, 32, 8),
+        # several prompts of very different lengths packed into one call, read in place from projection outputs
+        _case("packed-24k", "path", 24576, 32, 8, lengths="12672,64,4160,1024,320,6336", layout="bnhd"),
+        # the quantized Computation-Pass, 8-bit first product, at a length that no tile divides evenly
+        _case("int8-25k", "path", 25024, 32, 8, attn="int8"),
+        # the benchmark's three lengths: one each with 64-key blocks, the paper's 64x32 shape, and FP8
+        _case("layer-32k", "path", 32768, 32, 8),
+        _case("dense-32k", "dense", 32768, 32, 8),
+        _case("paper-shape-64k", "path", 65536, 32, 8, block_k=32, segments=True),
+        _case("fp8-64k", "path", 65536, 32, 8, attn="fp8"),
+        _case("layer-128k", "path", 131072, 32, 8),
+    ]
+
+
+def _log_blocks(rng, lo, hi):
+    """A length in tokens, a multiple of 64, spread over the logarithm of lo .. hi tokens."""
+    return 64 * max(1, round(math.exp(rng.uniform(math.log(lo / 64), math.log(hi / 64)))))
+
+
+def draw(rng):
+    call = "dense" if rng.random() < 0.25 else "path"
+    q_heads, kv_heads = rng.choice([(32, 8), (32, 8), (32, 8), (32, 8), (8, 2), (6, 2), (4, 4), (16, 2), (1, 1)])
+    batch = rng.choice([1, 1, 1, 2])
+    attn = rng.choice(["bf16", "bf16", "bf16", "int8", "fp8"])
+    most = _MOST_DENSE if call == "dense" else _MOST_PATH
+    longest = min(131072, 64 * int(math.sqrt(most / (batch * q_heads)) / 64))
+    lengths = ""
+    if batch == 1 and attn == "bf16" and rng.random() < 0.25:
+        parts = [_log_blocks(rng, 64, 16384) for _ in range(rng.randint(2, 9))]
+        lengths, tokens = ",".join(map(str, parts)), sum(parts)
+    else:
+        tokens = _log_blocks(rng, 1024, longest)
+    block_k = 32 if call == "path" and attn != "fp8" and rng.random() < 0.3 else 64
+    return dict(call=call, tokens=tokens, lengths=lengths, batch=batch, q_heads=q_heads, kv_heads=kv_heads, block_k=block_k,
+                segments=block_k == 32 and rng.random() < 0.7, attn=attn, layout=rng.choice(["bhnd", "bnhd"]),
+                keep=rng.random() < 0.75, lse=rng.random() < 0.3)
+
+
+def _params(case):
+    flags = sale.FLAG_SEGMENT_LOCAL if case["segments"] else 0
+    if case["attn"] != "bf16":
+        flags |= sale.FLAG_ATTN_INT8_QK
+    if case["attn"] == "fp8":
+        flags |= sale.FLAG_ATTN_FP8_PV
+    cu = ()
+    if case["lengths"]:
+        cu = (0,)
+        for n in case["lengths"].split(","):
+            cu += (cu[-1] + int(n),)
+    return sale.Params(case["batch"], case["q_heads"], case["kv_heads"], case["tokens"], block_k=case["block_k"], flags=flags,
+                       cu_seqlens=cu)
+
+
+def _rope(x):
+    """Rotary position embedding, base 500000, pairs (c, c + 64)."""
+    half = HEAD_DIM // 2
+    inv = torch.pow(500000.0, -torch.arange(half, dtype=torch.float64, device=x.device) / half)
+    angle = torch.arange(x.shape[-2], dtype=torch.float64, device=x.device)[:, None] * inv
+    cos, sin = angle.cos().float(), angle.sin().float()
+    a, b = x[..., :half], x[..., half:]
+    return torch.cat([a * cos - b * sin, b * cos + a * sin], dim=-1)
+
+
+def _sequence(n, group, recipe, gen):
+    """Q [group, n, d], K, V [n, d] of one KV head, made by the recipe of paper_2505_24179_amd.inputs on the GPU: a
+    sink at the first key, a local band (not in the toy recipe), a common query component and a few heavy keys."""
+    q = torch.randn(group, n, HEAD_DIM, generator=gen, device="cuda")
+    k = torch.randn(n, HEAD_DIM, generator=gen, device="cuda")
+    v = torch.randn(n, HEAD_DIM, generator=gen, device="cuda")
+    u = torch.randn(HEAD_DIM, generator=gen, device="cuda")
+    heavy = min(recipe.n_heavy, max(0, n - 256))
+    at = 256 + torch.randperm(max(1, n - 256), generator=gen, device="cuda")[:heavy]
+    if recipe.rope:
+        q, k = _rope(q), _rope(k)
+    q += recipe.rho * math.sqrt(HEAD_DIM) * (u / u.norm())
+    if recipe.local_bias:
+        q += 0.5 * k
+    mean = q.mean(dim=(0, 1))
+    k[0] += 4.0 * mean
+    k[at] += 3.0 * mean
+    return q.bfloat16(), k.bfloat16(), v.bfloat16()
+
+
+def _inputs(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    batch, heads, kv_heads, tokens = case["batch"], case["q_heads"], case["kv_heads"], case["tokens"]
+    group = heads // kv_heads
+    recipe = TOY if heads == 1 else LLAMA_32K
+    lengths = [int(n) for n in case["lengths"].split(",")] if case["lengths"] else [tokens]
+
+    def empty(h):
+        if case["layout"] == "bnhd":
+            return torch.empty(batch, tokens, h, HEAD_DIM, dtype=torch.bfloat16, device="cuda").transpose(1, 2)
+        return torch.empty(batch, h, tokens, HEAD_DIM, dtype=torch.bfloat16, device="cuda")
+
+    q, k, v = empty(heads), empty(kv_heads), empty(kv_heads)
+    for b in range(batch):
+        for g in range(kv_heads):
+            t0 = 0
+            for n in lengths:
+                t1 = t0 + n
+                q[b, g * group:(g + 1) * group, t0:t1], k[b, g, t0:t1], v[b, g, t0:t1] = _sequence(n, group, recipe, gen)
+                t0 = t1
+    return q, k, v
+
+
+def prepare(case, seed):
+    p = _params(case)
+    q, k, v = _inputs(case, seed)
+    state = dict(case=case, p=p, q=q, k=k, v=v, tau=torch.tensor([LLAMA_32K.tau], dtype=torch.float32, device="cuda"),
+                 codes=None, choice=None, o=None, ws_select=None, ws_attn=None)
+    if case["keep"]:
+        def new(*shape, dtype):
+            return torch.empty(*shape, dtype=dtype, device="cuda")
+
+        b, hq, hk, n = p.batch, p.n_q_heads, p.n_kv_heads, p.seq_len
+        path = case["call"] == "path"
+        if path:
+            state["codes"] = (new(b, hq, n, 64, dtype=torch.uint8), new(b, hk, n, 64, dtype=torch.uint8),
+                              new(b, hq, p.n_q, dtype=torch.float32), new(b, hk, p.n_k, dtype=torch.float32))
+            state["choice"] = (new(b, hq, p.n_q, p.words, dtype=torch.int64), new(b, hq, p.n_q, dtype=torch.int32))
+            state["ws_select"] = new(sale.workspace_bytes(p, sale.WS_SELECT), dtype=torch.uint8)
+        state["ws_attn"] = new(sale.workspace_bytes(p, sale.WS_SPARSE_ATTN if path else sale.WS_DENSE_ATTN), dtype=torch.uint8)
+        state["o"] = torch.empty_like(q)
+    return state
+
+
+def run(state):
+    case, p, q, k, v = state["case"], state["p"], state["q"], state["k"], state["v"]
+    if case["call"] == "dense":
+        o, lse = sale.dense_attn(p, q, k, v, want_lse=case["lse"], out=state["o"], ws=state["ws_attn"])
+        return {"o": o, "lse": lse}
+    q4, k4, q_scale, k_scale = sale.quantize_qk(p, q, k, out=state["codes"])
+    mask, counts, _, _ = sale.select(p, q, k, q4, k4, q_scale, k_scale, state["tau"], out=state["choice"], ws=state["ws_select"])
+    o, lse = sale.sparse_attn(p, q, k, v, mask, counts, want_lse=case["lse"], out=state["o"], ws=state["ws_attn"])
+    return {"q4": q4, "k4": k4, "q_scale": q_scale, "k_scale": k_scale, "mask": mask, "counts": counts, "o": o, "lse": lse}
+
+
+# Share of the causal blocks that the path keeps at the threshold used here, measured at (tokens, share) for 64-key and
+# 32-key blocks; between the lengths the share is interpolated over the logarithm.
+_KEPT = {
+    64: ((320, 1.0), (512, 0.83), (1024, 0.78), (4096, 0.68), (8192, 0.50), (16384, 0.37), (32768, 0.268), (65536, 0.225), (131072, 0.20)),
+    32: ((320, 0.87), (512, 0.69), (2048, 0.64), (4096, 0.47), (8192, 0.32), (16384, 0.25), (32768, 0.18), (65536, 0.157), (131072, 0.14)),
+}
+
+
+def _kept(n, block_k):
+    table = _KEPT[block_k]
+    if n <= table[0][0]:
+        return table[0][1]
+    for (n0, s0), (n1, s1) in zip(table, table[1:]):
+        if n <= n1:
+            return s0 + (s1 - s0) * math.log(n / n0) / math.log(n1 / n0)
+    return table[-1][1]
+
+
+def work(case):
+    """Bytes: Q, K, V in, O (and the codes, masks and counts of the path) out.  Flops: the attention products over the
+    causal (dense) or the usually kept (path) pairs of a query and a key; of the path also the 4-bit products over every
+    causal pair, counted as a quarter, for they run at four times the rate of bf16 products."""
+    b, hq, hk, n = case["batch"], case["q_heads"], case["kv_heads"], case["tokens"]
+    lengths = [int(x) for x in case["lengths"].split(",")] if case["lengths"] else [n]
+    words = -(-max(lengths) // (64 * case["block_k"]))
+    size = 2.0 * HEAD_DIM * b * n * (2 * hq + 2 * hk)
+    if case["lse"]:
+        size += 4.0 * b * hq * n
+    pairs = sum(m * (m + 1) / 2.0 for m in lengths) * b * hq
+    # (8-bit products count as half of bf16 ones)
+    rate = {"bf16": 1.0, "int8": 0.75, "fp8": 0.5}[case["attn"]]
+    if case["call"] == "dense":
+        return {"bytes": size, "flops": 4.0 * HEAD_DIM * pairs * rate}
+    size += b * n * (hq + hk) * (64 + 4.0 / 64) + b * hq * (n // 64) * (8.0 * words + 4)
+    kept = sum(m * (m + 1) / 2.0 * _kept(m, case["block_k"]) for m in lengths) * b * hq
+    return {"bytes": size, "flops": 4.0 * HEAD_DIM * kept * rate + 2.0 * HEAD_DIM * pairs / 4.0}
+
+
+def tolerance(case):
+    """The outputs are bf16 averages of bf16 values under probabilities rounded to bf16 (to FP8 E4M3 with attn = "fp8")
+    relative to a running maximum, which depends on the order of the sums; a block whose score lies within rounding of
+    the threshold may change sides.  Measured at 4096 tokens against 64-bit attention over the same blocks: rel 1.6e-3,
+    max 6.5e-3 (bf16, int8); against FP8 probabilities relative to the final maximum: rel 3.1e-3, max 6.2e-2."""
+    if case["attn"] == "fp8":
+        return {"rel": 1.2e-2, "max": 0.25, "differ": 1e-4}
+    return {"rel": 6e-3, "max": 0.05, "differ": 1e-4}
