@@ -187,6 +187,128 @@ def run(state):
     return {"q4": q4, "k4": k4, "q_scale": q_scale, "k_scale": k_scale, "mask": mask, "counts": counts, "o": o, "lse": lse}
 
 
+# The longest pass that `exact` computes (the sum over sequences of batch * query heads * length^2).
+_MOST_EXACT = 32 * 65536 ** 2
+
+
+def _blocks(x, rows, top, out):
+    """Symmetric codes of the blocks of `rows` rows of x [n, d] (fp32, as the definition of the codes says): integers in
+    [-top, top] as `out`, and the scales in 64 bits."""
+    b = x.float().reshape(-1, rows * x.shape[-1])
+    amax = b.abs().amax(dim=1, keepdim=True)
+    inv = torch.where(amax > 0, top / amax, torch.zeros_like(amax))
+    codes = torch.round(b * inv).clamp_(-top, top).view(x.shape).to(out)
+    scale = torch.where(amax > 0, amax.double() / top, torch.ones_like(amax, dtype=torch.float64))
+    return codes, scale.view(-1)
+
+
+def _nibbles(codes):
+    c = codes.to(torch.int32) & 15
+    return (c[:, 0::2] | (c[:, 1::2] << 4)).to(torch.uint8)
+
+
+def _choice(case, q, k, qc, kc, qs, ks):
+    """Kept blocks of one head of one sequence: bool [n / 64, n / block_k] (sink and local blocks always; a middle block
+    if its 4-bit estimate reaches the threshold in one of the 64 rows)."""
+    n, bk = q.shape[0], case["block_k"]
+    n_q, n_k, f = n // 64, n // bk, 64 // bk
+    keep = torch.zeros(n_q, n_k, dtype=torch.bool, device=q.device)
+    qd, kd = q.double(), k.double()
+    for i in range(n_q):
+        j_last = (i + 1) * f - 1
+        middle = j_last + 1 - 1 - 4
+        local = 4 + (middle % 4 if case["segments"] and middle > 0 else 0)
+        lo = max(j_last - local + 1, 0)
+        keep[i, :1] = True
+        keep[i, lo:j_last + 1] = True
+        if lo <= 1:
+            continue
+        near = torch.cat([kd[:bk], kd[lo * bk:(j_last + 1) * bk]])
+        s = qd[i * 64:(i + 1) * 64] @ near.T / math.sqrt(HEAD_DIM)
+        threshold = math.log(LLAMA_32K.tau) + torch.logsumexp(s, dim=1)
+        # (integer products and their sums below 2^24: exact in fp32)
+        est = (qc[i * 64:(i + 1) * 64] @ kc[bk:lo * bk].T).view(64, lo - 1, bk).amax(dim=2).double()
+        keep[i, 1:lo] = (est * (qs[i] * ks[1:lo] / math.sqrt(HEAD_DIM)) >= threshold[:, None]).any(dim=0)
+    return keep
+
+
+def _attend(q, k, v, keep, block_k, o, lse):
+    """Causal attention of one head of one sequence over the kept blocks (all, if keep is None), into o and lse."""
+    n, step = q.shape[0], 1024
+    at = torch.arange(n, device=q.device)
+    for t0 in range(0, n, step):
+        t1 = min(n, t0 + step)
+        s = q[t0:t1] @ k[:t1].T
+        hide = at[None, :t1] > at[t0:t1, None]
+        if keep is not None:
+            hide |= ~keep[t0 // 64:t1 // 64, :t1 // block_k].repeat_interleave(64, 0).repeat_interleave(block_k, 1)
+        s.masked_fill_(hide, -math.inf)
+        total = torch.logsumexp(s, dim=1)
+        o[t0:t1] = torch.exp_(s.sub_(total[:, None])) @ v[:t1]
+        lse[t0:t1] = total
+
+
+def exact(case, seed):
+    """What `run` returns, by plain torch: the codes in fp32 (their definition), everything else in 64 bits.  The 8-bit
+    operands of attn = "int8" and the FP8 values of V are part of what is asked for; the rounding of probabilities and
+    of the output is not.  None for the longest cases."""
+    batch, heads, kv_heads, tokens = case["batch"], case["q_heads"], case["kv_heads"], case["tokens"]
+    bk, path, group = case["block_k"], case["call"] == "path", case["q_heads"] // case["kv_heads"]
+    lengths = [int(n) for n in case["lengths"].split(",")] if case["lengths"] else [tokens]
+    if batch * heads * sum(n * n for n in lengths) > _MOST_EXACT:
+        return None
+    q, k, v = _inputs(case, seed)
+
+    def new(*shape, dtype=torch.float64):
+        return torch.zeros(*shape, dtype=dtype, device="cuda")
+
+    words = -(-max(lengths) // (64 * bk))
+    o, lse = new(batch, heads, tokens, HEAD_DIM), new(batch, heads, tokens)
+    q4, k4 = new(batch, heads, tokens, 64, dtype=torch.uint8), new(batch, kv_heads, tokens, 64, dtype=torch.uint8)
+    q_scale, k_scale = new(batch, heads, tokens // 64), new(batch, kv_heads, tokens // bk)
+    mask, counts = new(batch, heads, tokens // 64, words, dtype=torch.int64), new(batch, heads, tokens // 64, dtype=torch.int32)
+    shift = torch.arange(64, device="cuda")
+    for b in range(batch):
+        for g in range(kv_heads):
+            kg, vg = k[b, g], v[b, g].double()
+            kc, k_scale[b, g] = _blocks(kg, bk, 7.0, torch.float32)
+            k4[b, g] = _nibbles(kc)
+            ka, mean = kg.double(), None
+            if case["attn"] != "bf16":
+                mean = ka.mean(dim=0).float()
+                c8, s8 = _blocks(kg.float() - mean, 64, 127.0, torch.float64)
+                ka = c8 * s8.repeat_interleave(64)[:, None]
+            if case["attn"] == "fp8":
+                amax = v[b, g].float().abs().amax(dim=0)
+                vg = (v[b, g].float() * (448.0 / amax)).to(torch.float8_e4m3fn).double() * (amax.double() / 448.0)
+            for h in range(g * group, (g + 1) * group):
+                qh = q[b, h]
+                qc, q_scale[b, h] = _blocks(qh, 64, 7.0, torch.float32)
+                q4[b, h] = _nibbles(qc)
+                qa = qh.double()
+                if case["attn"] != "bf16":
+                    c8, s8 = _blocks(qh, 64, 127.0, torch.float64)
+                    qa = c8 * s8.repeat_interleave(64)[:, None]
+                qa = qa / math.sqrt(HEAD_DIM)
+                t0 = 0
+                for n in lengths:
+                    t, keep = slice(t0, t0 + n), None
+                    if path:
+                        rows, blocks = slice(t0 // 64, (t0 + n) // 64), slice(t0 // bk, (t0 + n) // bk)
+                        keep = _choice(case, qh[t], kg[t], qc[t], kc[t], q_scale[b, h, rows], k_scale[b, g, blocks])
+                        bits = torch.nn.functional.pad(keep, (0, words * 64 - n // bk)).view(n // 64, words, 64)
+                        mask[b, h, rows] = (bits.long() << shift).sum(dim=2)
+                        counts[b, h, rows] = keep.sum(dim=1, dtype=torch.int32)
+                    _attend(qa[t], ka[t], vg[t], keep, bk, o[b, h, t], lse[b, h, t])
+                    t0 += n
+                if mean is not None:
+                    lse[b, h] += qh.double() @ mean.double() / math.sqrt(HEAD_DIM)
+    out = {"o": o, "lse": lse if case["lse"] else None}
+    if path:
+        out.update(q4=q4, k4=k4, q_scale=q_scale, k_scale=k_scale, mask=mask, counts=counts)
+    return out
+
+
 # Share of the causal blocks that the path keeps at the threshold used here, measured at (tokens, share) for 64-key and
 # 32-key blocks; between the lengths the share is interpolated over the logarithm.
 _KEPT = {
