@@ -222,16 +222,19 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   float cl[2] = {cs, cs};
   float ks_pend[2] = {1.0f, 1.0f};      // QK8: K scale of the half-tile whose operands were requested last
   float sq_cs = cs;
-  const i32x4* k8t = nullptr;
+  const int first_tile = __builtin_amdgcn_readfirstlane((int)((size_t)u.kvh * g.seq / 64) + (u.i - il));
+  const int tiles = __builtin_amdgcn_readfirstlane(il) + 1;      // (64-key tiles up to the diagonal)
+  const int lane16 = lane * 16;
+  __amdgpu_buffer_rsrc_t k8t;      // (the FP8 pass reads through plain pointers: with descriptors its loop took 8.5 ms at 64K instead of 7.5)
   const float* ks8 = nullptr;
   if constexpr (QK8) {
     sq_cs = q8o.q_scale[unit_flat] * cs;
-    k8t = (const i32x4*)q8o.k8p + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 8 + lane;     // 512 16-byte chunks per 64 keys
-    ks8 = q8o.k_scale + (size_t)u.kvh * (g.seq / 64) + (u.i - il);
+    k8t = operand_buffer(q8o.k8p + (size_t)first_tile * 512, tiles * 8192);      // 512 16-byte chunks per 64 keys
+    ks8 = PV8 ? q8o.k_scale + (size_t)u.kvh * (g.seq / 64) + (u.i - il) : q8o.k_scale + first_tile;
   }
   // (the sequence's first key tile: u.i - il 64-row blocks into the KV head)
-  const bf16x8* kt = kp + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 16 + lane;     // 1024 16-byte chunks per 64 keys
-  const bf16x8* vt = vp + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 16 + lane;
+  const __amdgpu_buffer_rsrc_t kt = operand_buffer(kp + (size_t)first_tile * 1024, tiles * 16384);     // 1024 16-byte chunks per 64 keys
+  const __amdgpu_buffer_rsrc_t vt = operand_buffer(vp + (size_t)first_tile * 1024, tiles * 16384);
   // Work proceeds in pairs of 32-key half-tiles held in slots 0 and 1; half-tile hb covers keys
   // 32hb .. 32hb+31 (half hb % 2 of the 64-key tile hb / 2 of K', V').  K operands of slot mt: kf[mt][s];
   // V operands of slot mt: vf[mt][dt][s2].
@@ -239,22 +242,23 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   i32x4 kf8[QK8 ? 2 : 1][QK8 ? 4 : 1];
   auto load_k = [&](int hb, int mt) __attribute__((always_inline)) {
     if constexpr (QK8) {
-      const i32x4* t = k8t + (size_t)hb * 256;
+      const int hu = __builtin_amdgcn_readfirstlane(hb);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) kf8[mt][s] = t[s * 64];
+      for (int s = 0; s < 4; ++s) kf8[mt][s] = load_chunk<i32x4>(k8t, lane16, hu * 4096, s);
       ks_pend[mt] = ks8[hb >> 1];
     } else {
-      const bf16x8* t = kt + (size_t)hb * 512;
+      const int t = __builtin_amdgcn_readfirstlane(hb) * 8192;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) kf[mt][s] = t[s * 64];
+      for (int s = 0; s < 8; ++s) kf[mt][s] = load_chunk<bf16x8>(kt, lane16, t, s);
     }
   };
   auto load_v = [&](int hb, int mt) __attribute__((always_inline)) {
-    const bf16x8* t = vt + (size_t)(hb >> 1) * 1024 + (hb & 1) * 128;
+    const int hu = __builtin_amdgcn_readfirstlane(hb);
+    const int t = (hu >> 1) * 16384 + (hu & 1) * 2048;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) vf[mt][dt][s2] = t[(dt * 4 + s2) * 64];
+      for (int s2 = 0; s2 < 2; ++s2) vf[mt][dt][s2] = load_chunk<bf16x8>(vt, lane16, t, dt * 4 + s2);
   };
 
   f32x16 oacc[4][2];
@@ -304,12 +308,13 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     // block's, the next V8 once the second product has.
     static_assert(QK8 && !BK32, "the FP8 second product comes with the 8-bit first product on 64-key blocks");
     const u32x4* const v8t = q8o.v8p + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 8 + lane;   // 512 chunks per 64 keys
+    const i32x4* const k8g = (const i32x4*)q8o.k8p + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 8 + lane;
     const float kLog2Top = 8.807354922057604f;      // log2(448)
     i32x4 k8[2][4];
     u32x4 v8[4][2];
     float k_sc = 1.0f;
     auto fetch_k = [&](int j) __attribute__((always_inline)) {
-      const i32x4* t = k8t + (size_t)j * 512;
+      const i32x4* t = k8g + (size_t)j * 512;
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll

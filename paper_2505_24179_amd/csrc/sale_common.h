@@ -102,6 +102,20 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(lo, hi);
 }
 
+// Operand copies in fragment order are read through buffer descriptors: an address is descriptor base + scalar tile
+// offset + lane * 16 + immediate, so a load costs no vector instruction for its address (with plain pointers the step
+// of the attention kernel spent 26 of its 290 vector instructions besides the MFMAs on 64-bit addresses; bf16 sparse
+// attention at 64K with 32-key blocks 7.94 -> 7.80 ms, dense at 32K 7.69 -> 7.61 ms; Selection-Pass at 128K 13.65 -> 13.32 ms).
+// Base and size must be wave-uniform.  A descriptor covers one KV head of one sequence: at most 64 MB.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+}
+// Chunk n (lane-contiguous 1 KB) from the scalar byte offset t on.
+template <class T>
+__device__ __forceinline__ T load_chunk(__amdgpu_buffer_rsrc_t r, int lane16, int t, int n) {
+  return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, lane16 + (n & 3) * 1024, t + (n & ~3) * 1024, 0));
+}
+
 // Unit = (flattened query head, 64-row query block): the work of one wave.
 // Units of one KV head are numbered block-major, head-in-group minor, so the
 // four waves of a workgroup share their K (and V) rows.  Workgroups are dealt

@@ -306,12 +306,12 @@ __global__ __launch_bounds__(256) void pack_fp6_kernel(const uint8_t* __restrict
 }
 
 // The 2 operand fragments (ks = 0, 1) of 32-row group `grp` of an X6 array.
-__device__ __forceinline__ void load_x6(const uint8_t* __restrict__ base, size_t grp, int lane, i32x8 f[2]) {
-  const uint8_t* b = base + grp * kX6GroupBytes;
+__device__ __forceinline__ void load_x6(__amdgpu_buffer_rsrc_t base, int grp, int lane, i32x8 f[2]) {
+  const int b = grp * kX6GroupBytes;
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const u32x4 lo = *(const u32x4*)(b + (ks * 64 + lane) * 16);
-    const u32x2 hi = *(const u32x2*)(b + 2048 + (ks * 64 + lane) * 8);
+    const u32x4 lo = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(base, lane * 16 + ks * 1024, b, 0));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(base, lane * 8 + 2048 + ks * 512, b, 0));
     f[ks][0] = lo[0]; f[ks][1] = lo[1]; f[ks][2] = lo[2]; f[ks][3] = lo[3];
     f[ks][4] = hi[0]; f[ks][5] = hi[1]; f[ks][6] = 0; f[ks][7] = 0;
   }
@@ -391,11 +391,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     cq[a] = q_scale[(size_t)(qh0 + a) * g.n_qb + i] * 0.08838834764831845f;   // s_q / sqrt(d)
   }
   const float* ks = k_scale + (size_t)kvh * g.n_kb;
-  const size_t kgrp0 = (size_t)kvh * g.n_kb * MT;
-
   const SeqPos sp = seq_pos(g, i);
   const int j_last = j_last_of(g, sp.il), local = local_of(g, j_last);
   const int mid_lo = g.sink_blocks, mid_hi = j_last - local;      // the middle blocks (inclusive), scored below
+  const __amdgpu_buffer_rsrc_t kbuf = operand_buffer(k6 + ((size_t)kvh * g.n_kb + sp.kb0) * MT * kX6GroupBytes,
+                                                     (j_last + 1) * MT * kX6GroupBytes);
   int count[HPW];
   uint64_t word[HPW];
   int wc = 0;                                                       // mask word being assembled
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   float ska = 0.0f, skb = 0.0f;
   auto fetch = [&](int j, i32x8 (&kf)[MT][2], float& sk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) load_x6(k6, kgrp0 + (size_t)(sp.kb0 + j) * MT + mt, lane, kf[mt]);
+    for (int mt = 0; mt < MT; ++mt) load_x6(kbuf, j * MT + mt, lane, kf[mt]);
     sk = ks[sp.kb0 + j];
   };
   auto score = [&](int j, const i32x8 (&kf)[MT][2], float sk, i32x8 (&kn)[MT][2], float& skn) __attribute__((always_inline)) {
