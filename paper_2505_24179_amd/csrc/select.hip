@@ -32,16 +32,29 @@ __device__ __forceinline__ bool in_sink_local(const Geo& g, int j, int j_last, i
   return j < g.sink_blocks || j > j_last - local;
 }
 
+// Rows that several waves of select_kernel share: the statistics kernel, which runs before it, clears their counts and
+// (where several waves share a mask word) their mask words.
+struct ClearRows {
+  int32_t* row_counts;      // nullptr: nothing to clear
+  uint64_t* mask;           // nullptr: words are stored whole
+  __device__ __forceinline__ void row(const Geo& g, const Unit& u, int lane) const {
+    const size_t r = (size_t)u.qh * g.n_qb + u.i;
+    if (row_counts && lane == 0) row_counts[r] = 0;
+    if (mask && lane < g.words) mask[r * g.words + lane] = 0;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Sink-local statistics (display equation of Sec. 3.2; first loop of Alg. 1)
 // ---------------------------------------------------------------------------
 template <int MT>
 __global__ __launch_bounds__(256) void stats_kernel(Geo g, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                     const float* __restrict__ tau, int tau_len, float* __restrict__ thr,
-                                                    float* __restrict__ m_out, float* __restrict__ l_out) {
+                                                    float* __restrict__ m_out, float* __restrict__ l_out, ClearRows clear) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform by construction
   const Unit u = unit_of(g, blockIdx.x, wave);
   if (!u.valid) return;
+  clear.row(g, u, lane);
   const int c = lane & 31, h = lane >> 5;
   const float rsd = 0.08838834764831845f;   // 1 / sqrt(128)
 
@@ -142,11 +155,12 @@ template <int MT>
 __global__ __launch_bounds__(256) void stats_shared_kernel(Geo g, const uint16_t* __restrict__ q,
                                                            const uint16_t* __restrict__ k, const float* __restrict__ tau,
                                                            int tau_len, float* __restrict__ thr, float* __restrict__ m_out,
-                                                           float* __restrict__ l_out) {
+                                                           float* __restrict__ l_out, ClearRows clear) {
   __shared__ bf16x8 k_lds[2][8 * 64];                // [buffer][s][lane] 16 bytes: the A operands of one half-block
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const Unit u = unit_of(g, blockIdx.x, wave);       // (group % 4 == 0: every wave is valid, all four share u.i and u.kvh)
+  clear.row(g, u, lane);
   const int c = lane & 31, h = lane >> 5;
   const float rsd = 0.08838834764831845f;   // 1 / sqrt(128)
 
@@ -259,27 +273,34 @@ __global__ __launch_bounds__(256) void stats_shared_kernel(Geo g, const uint16_t
 //   [group][ks][lane] 16 bytes (dwords 0..3)  followed by  [group][ks][lane] 8 bytes (dwords 4..5).
 constexpr int kX6GroupBytes = 2 * 64 * 24;   // 3072 bytes per 32 rows
 
-// E2M3 code of a 4-bit two's-complement nibble n (-7..7).
-__device__ __forceinline__ uint32_t e2m3_of_nibble(uint32_t n) {
-  const uint32_t sign = (n >> 3) & 1u;
-  const uint32_t mag = ((n ^ (0u - sign)) + sign) & 7u;          // |value|
-  return (sign << 5) | (((0xFEDCA840u >> (4u * mag)) & 0xFu) << 1);
+// (about 30 vector instructions per 8 codes; code by code it took 64 and was 7 us of a wave of select_kernel)
+// E2M3 codes of the four 4-bit two's-complement nibbles (-7..7) in the low halves of the bytes of n (the high halves
+// are zero): two byte look-ups by the low three bits, for n >= 0 and n < 0, chosen by the sign bit.
+__device__ __forceinline__ uint32_t e2m3_of_nibbles(uint32_t n) {
+  const uint32_t at = n & 0x07070707u, sign = n & 0x08080808u;
+  const uint32_t pos = __builtin_amdgcn_perm(0x1E1C1A18u, 0x14100800u, at);       // 0, 1, 2, 3 | 4, 5, 6, 7
+  const uint32_t neg = __builtin_amdgcn_perm(0x28303438u, 0x3A3C3E20u, at);       // (-8: -0), -7, -6, -5 | -4, -3, -2, -1
+  const uint32_t is_neg = (sign << 5) - (sign >> 3);                              // 0xFF in the bytes of negative codes
+  return (neg & is_neg) | (pos & ~is_neg);
 }
 
 // 16 packed bytes (32 nibble codes, channel order) -> 32 six-bit codes in 6 dwords.
 __device__ __forceinline__ void pack_fp6(const u32x4 w, uint32_t out[6]) {
-  uint64_t acc = 0;
-  int bits = 0, o = 0;
+  uint32_t f[8];      // 24 bits each: the codes of two bytes
 #pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    const uint32_t nib = (w[e >> 3] >> (4 * (e & 7))) & 0xFu;
-    acc |= (uint64_t)e2m3_of_nibble(nib) << bits;
-    bits += 6;
-    if (bits >= 32) {
-      out[o++] = (uint32_t)acc;
-      acc >>= 32;
-      bits -= 32;
-    }
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t lo = e2m3_of_nibbles(w[d] & 0x0F0F0F0Fu), hi = e2m3_of_nibbles((w[d] >> 4) & 0x0F0F0F0Fu);
+    const uint32_t x0 = (lo & 0x00FF00FFu) | ((hi & 0x00FF00FFu) << 6);                  // 12 bits: bytes 0 and 2
+    const uint32_t x1 = ((lo >> 8) & 0x00FF00FFu) | (((hi >> 8) & 0x00FF00FFu) << 6);    //          bytes 1 and 3
+    f[2 * d] = (x0 & 0xFFFu) | ((x1 & 0xFFFu) << 12);
+    f[2 * d + 1] = (x0 >> 16) | ((x1 >> 16) << 12);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {      // four 24-bit pieces make three dwords
+    const uint32_t* p = f + 4 * t;
+    out[3 * t] = p[0] | (p[1] << 24);
+    out[3 * t + 1] = (p[1] >> 8) | (p[2] << 16);
+    out[3 * t + 2] = (p[2] >> 16) | (p[3] << 8);
   }
 }
 
@@ -348,14 +369,16 @@ __device__ __forceinline__ float lane_max(const f32x16 acc[MT][2], int nt) {
 
 // One wave scores HPW query heads of one GQA group at the same query block, so every K~ fragment it
 // loads feeds HPW x 2 MFMAs (HPW = 4 when the group allows).  A workgroup is 4 such waves (consecutive head sets / query blocks of one
-// KV head); workgroups go round-robin over KV heads, longest rows first.
+// KV head); workgroups go round-robin over KV heads, longest rows first.  chunk > 0 (select_chunk): a wave scores
+// blockIdx.y's `chunk` blocks of its rows only.  A mask word belongs to one wave if chunk is a multiple of 64,
+// otherwise (a divisor of 64) its bits are joined by atomics, as are the counts (whole numbers: any order gives the same).
 // (At least 2 waves per SIMD caps the register file at 256 VGPRs, which lets the MFMA results land in
 // ordinary VGPRs instead of AGPRs that the max chain would have to copy out one by one.)
 template <int HPW, int MT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void select_kernel(
     Geo g, const uint8_t* __restrict__ q4, const uint8_t* __restrict__ k6, const float* __restrict__ q_scale,
     const float* __restrict__ k_scale, const float* __restrict__ thr, uint64_t* __restrict__ mask,
-    int32_t* __restrict__ row_counts) {
+    int32_t* __restrict__ row_counts, int chunk) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform by construction
   const int c = lane & 31;
   const int sets = g.group / HPW;                 // head sets per (KV head, query block)
@@ -366,6 +389,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   if (id >= units) return;
   const int i = id / sets;
   const int qh0 = kvh * g.group + (id % sets) * HPW;
+  const SeqPos sp = seq_pos(g, i);
+  const int j_last = j_last_of(g, sp.il), local = local_of(g, j_last);
+  // This wave's blocks of the row: r_lo .. r_hi - 1.
+  const int r_lo = chunk ? (int)blockIdx.y * chunk : 0, r_hi = chunk ? min(r_lo + chunk, g.words * 64) : g.words * 64;
+  const bool shared_word = chunk != 0 && chunk < 64;
+  if (chunk && r_lo > j_last) {       // nothing of the row: its words stay empty (shared words were cleared)
+    const int n_w = (r_hi - r_lo) >> 6;
+    if (!shared_word)
+      for (int e = lane; e < HPW * n_w; e += 64)
+        mask[((size_t)(qh0 + e / n_w) * g.n_qb + i) * g.words + (r_lo >> 6) + e % n_w] = 0;
+    return;
+  }
 
   i32x8 qf[HPW][2][2];
   float th[HPW][2], cq[HPW];
@@ -391,27 +426,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     cq[a] = q_scale[(size_t)(qh0 + a) * g.n_qb + i] * 0.08838834764831845f;   // s_q / sqrt(d)
   }
   const float* ks = k_scale + (size_t)kvh * g.n_kb;
-  const SeqPos sp = seq_pos(g, i);
-  const int j_last = j_last_of(g, sp.il), local = local_of(g, j_last);
-  const int mid_lo = g.sink_blocks, mid_hi = j_last - local;      // the middle blocks (inclusive), scored below
+  const int row_mid_hi = j_last - local;                          // the row's middle blocks: sink_blocks .. row_mid_hi
+  const int mid_lo = max(g.sink_blocks, r_lo), mid_hi = min(row_mid_hi, r_hi - 1);      // those scored here
   const __amdgpu_buffer_rsrc_t kbuf = operand_buffer(k6 + ((size_t)kvh * g.n_kb + sp.kb0) * MT * kX6GroupBytes,
                                                      (j_last + 1) * MT * kX6GroupBytes);
   int count[HPW];
   uint64_t word[HPW];
-  int wc = 0;                                                       // mask word being assembled
+  int wc = r_lo >> 6;                                               // mask word being assembled
   // Bits of word wc that are set without scoring: the sink and local blocks the row can see.
   auto fixed_bits = [&]() -> uint64_t {
     auto span = [&](int lo, int hi) -> uint64_t {                   // bits of blocks lo..hi that fall into word wc
-      lo = max(lo - wc * 64, 0); hi = min(hi - wc * 64, 63);
+      lo = max(max(lo, r_lo) - wc * 64, 0); hi = min(min(hi, r_hi - 1) - wc * 64, 63);
       return lo > hi ? 0ull : ((~0ull >> (63 - hi)) & (~0ull << lo));
     };
-    return span(0, min(g.sink_blocks - 1, j_last)) | span(max(mid_hi + 1, 0), j_last);
+    return span(0, min(g.sink_blocks - 1, j_last)) | span(max(row_mid_hi + 1, 0), j_last);
   };
   // Completes word wc (store, count) and starts the next one.
   auto flush = [&]() {
 #pragma unroll
     for (int a = 0; a < HPW; ++a) {
-      if (lane == 0) mask[((size_t)(qh0 + a) * g.n_qb + i) * g.words + wc] = word[a];
+      uint64_t* at = mask + ((size_t)(qh0 + a) * g.n_qb + i) * g.words + wc;
+      if (lane == 0) {
+        if (shared_word) atomicOr((unsigned long long*)at, (unsigned long long)word[a]); else *at = word[a];
+      }
       count[a] += __popcll(word[a]);
     }
     ++wc;
@@ -456,10 +493,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       if (j + 1 <= mid_hi) score(j + 1, kfb, skb, kfa, ska);
     }
   }
-  while (wc < g.words) flush();
+  while (wc * 64 < r_hi) flush();
 #pragma unroll
   for (int a = 0; a < HPW; ++a)
-    if (lane == 0) row_counts[(size_t)(qh0 + a) * g.n_qb + i] = count[a];
+    if (lane == 0) {
+      int32_t* at = row_counts + (size_t)(qh0 + a) * g.n_qb + i;
+      if (chunk) atomicAdd(at, count[a]); else *at = count[a];
+    }
 }
 
 // Appendix E ablation ("w/o QK Quant"): the same rule with the estimate taken from the 16-bit Q, K
@@ -561,33 +601,50 @@ using namespace sale;
 
 namespace {
 
+// Key blocks of a row that one wave of select_kernel scores (0: the whole row).  With one wave per row a call of few
+// rows is as long as its longest row (4K tokens, 32 / 8 heads: 520 waves for 2048 places, 65 blocks one after the
+// other), and up to 32K the last rows leave places empty.  The rows are cut so that about 2.5 * 16384 / blocks-per-row
+// waves come to work, in powers of two from 8 blocks on (below, the re-encoding of Q~ costs more than the blocks:
+// 4K took 62 us with 4).  Select call, before -> after (the faster re-encoding of Q~ is part of it; without the cut it
+// gave 79.7, 321 and 13100): 4K tokens 85.7 -> 54.8 us, 16K 338 -> 301, 32K 1020 -> 990, 128K (not cut) 13400 -> 13090.
+// With twice as many waves 16K took 314 us, with four times 360; with half as many 304.
+int select_chunk(const Geo& g, int hpw) {
+  const long waves = (long)g.n_qb * (g.group / hpw) * g.n_kvh, blocks = (long)g.words * 64;
+  long chunk = 8;
+  while (chunk * 16384 < blocks * waves) chunk *= 2;
+  return chunk < blocks ? (int)chunk : 0;
+}
+
 template <int MT>
 int launch_select(const Geo& g, bool est16, const void* q, const void* k, const uint8_t* q4, const uint8_t* k6,
                   const float* q_scale, const float* k_scale, const float* tau, int tau_len, const float* thr_c,
                   float* thr, uint64_t* block_mask, int32_t* row_counts, float* m_out, float* l_out, hipStream_t st) {
   const int tiles = (g.n_qb * g.group + 3) / 4;
+  // Heads per wave of select_kernel (with 32-key blocks two are faster than four: 15.8 against 17.1 ms at 128K).
+  const int hpw = MT == 2 && g.group % 4 == 0 ? 4 : g.group % 2 == 0 ? 2 : 1;
+  const int chunk = est16 ? 0 : select_chunk(g, hpw);
+  const ClearRows clear = {chunk ? row_counts : nullptr, chunk && chunk < 64 ? block_mask : nullptr};
   if (g.group % 4 == 0)      // (then every workgroup holds 4 heads of one KV head at one query block: they share K)
     stats_shared_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k,
-                                                                                    tau, tau_len, thr, m_out, l_out);
+                                                                                    tau, tau_len, thr, m_out, l_out, clear);
   else
     stats_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k, tau,
-                                                                             tau_len, thr, m_out, l_out);
+                                                                             tau_len, thr, m_out, l_out, clear);
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   if (est16) {
     select16_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k,
                                                                                 thr_c, block_mask, row_counts);
-  } else if (MT == 2 && g.group % 4 == 0) {     // (with 32-key blocks two heads per wave are faster: 15.8 against 17.1 ms at 128K)
-    const int t4 = (g.n_qb * (g.group / 4) + 3) / 4;
-    select_kernel<4, MT><<<dim3((unsigned)(t4 * g.n_kvh)), dim3(256), 0, st>>>(g, q4, k6, q_scale, k_scale, thr_c,
-                                                                              block_mask, row_counts);
-  } else if (g.group % 2 == 0) {
-    const int t2 = (g.n_qb * (g.group / 2) + 3) / 4;
-    select_kernel<2, MT><<<dim3((unsigned)(t2 * g.n_kvh)), dim3(256), 0, st>>>(g, q4, k6, q_scale, k_scale, thr_c,
-                                                                              block_mask, row_counts);
-  } else {
-    select_kernel<1, MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, q4, k6, q_scale, k_scale, thr_c,
-                                                                                 block_mask, row_counts);
+    return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
+  const int wgs = (g.n_qb * (g.group / hpw) + 3) / 4;
+  const dim3 grid((unsigned)(wgs * g.n_kvh), chunk ? (unsigned)((g.words * 64 + chunk - 1) / chunk) : 1u);
+#define SALE_SELECT_ARGS g, q4, k6, q_scale, k_scale, thr_c, block_mask, row_counts, chunk
+  if constexpr (MT == 2) {
+    if (hpw == 4) select_kernel<4, MT><<<grid, dim3(256), 0, st>>>(SALE_SELECT_ARGS);
+  }
+  if (hpw == 2) select_kernel<2, MT><<<grid, dim3(256), 0, st>>>(SALE_SELECT_ARGS);
+  if (hpw == 1) select_kernel<1, MT><<<grid, dim3(256), 0, st>>>(SALE_SELECT_ARGS);
+#undef SALE_SELECT_ARGS
   return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
 }
 

@@ -1,0 +1,45 @@
+"""Calls of few rows split them over more waves than calls of many rows do.  The rule goes by the whole call, so the same
+sequence alone and repeated along the batch takes different splits, and its results must not differ by a bit (the
+element-by-element comparison of the single calls with the oracle is in the parity tests)."""
+import pytest
+import torch
+
+from paper_2505_24179_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sale():
+    from paper_2505_24179_amd import sale as mod
+    return mod
+
+
+def _qkv(tokens, q_heads, kv_heads):
+    w = inputs.scaled(inputs.LLAMA_32K, tokens, q_heads, kv_heads, f"small-{tokens}-{q_heads}")
+    return w, [t.unsqueeze(0).cuda() for t in inputs.make_inputs(w)]
+
+
+# Key blocks per wave at these batches (64-key blocks, 32 / 8 heads): 65 blocks: 8, 16, 32, 64, whole rows; 198 blocks:
+# 32, 64, 128, whole rows.  6 / 2 heads: one head per wave; 4 / 2: two.
+@pytest.mark.parametrize("tokens,q_heads,kv_heads,batches", [(4160, 32, 8, (2, 4, 8, 16)), (12672, 32, 8, (2, 4, 8)),
+                                                             (4160, 6, 2, (2, 11, 22)), (4160, 4, 2, (33, 64)), (64, 4, 1, (3,))])
+@pytest.mark.parametrize("block_k,segments", [(64, False), (32, True)])
+def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv_heads, batches, block_k, segments):
+    w, (q, k, _) = _qkv(tokens, q_heads, kv_heads)
+    tau = torch.tensor([w.tau], dtype=torch.float32, device="cuda")
+    flags = sale.FLAG_SEGMENT_LOCAL if segments else 0
+
+    def choose(n):
+        p = sale.Params(n, q_heads, kv_heads, tokens, block_k=block_k, flags=flags)
+        qn, kn = q.expand(n, -1, -1, -1).contiguous(), k.expand(n, -1, -1, -1).contiguous()
+        codes = sale.quantize_qk(p, qn, kn)
+        out = (torch.full((n, q_heads, p.n_q, p.words), -1, dtype=torch.int64, device="cuda"),
+               torch.full((n, q_heads, p.n_q), -1, dtype=torch.int32, device="cuda"))
+        mask, counts, _, _ = sale.select(p, qn, kn, *codes, tau, out=out)
+        return mask, counts
+
+    mask, counts = choose(1)
+    for n in batches:
+        mask_n, counts_n = choose(n)
+        assert torch.equal(mask_n, mask.expand_as(mask_n)) and torch.equal(counts_n, counts.expand_as(counts_n)), n
