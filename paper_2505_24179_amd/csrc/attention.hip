@@ -139,8 +139,13 @@ struct Qk8 {
 // bytes and half the MFMA time of that product; see the PV8 section of the kernel.
 constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_half)
 
-template <int WAVES, bool BK32, bool QK8, bool PV8 = false>
-__global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint16_t* __restrict__ q,
+//
+// NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
+// launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
+// and key block, the same operand loads (the second wave of a row hits in L1), about 250 registers, so two waves share
+// a SIMD.  A query's arithmetic is the same in both, bit for bit.
+template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
+__global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g, const uint16_t* __restrict__ q,
                                                                const bf16x8* __restrict__ kp,
                                                                const bf16x8* __restrict__ vp, Qk8 q8o,
                                                                const uint64_t* __restrict__ mask,
@@ -150,7 +155,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
                                                                float* __restrict__ lse,
                                                                RowFilter flt, f32x4* __restrict__ st_o,
                                                                float* __restrict__ st_ml) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  static_assert(NT == 2 || WAVES == 1, "the two halves of a row share a workgroup of their own");
+  const int tid = threadIdx.x, wave = NT == 1 ? 0 : tid >> 6, lane = tid & 63;
+  const int q0 = NT == 1 ? (tid >> 6) * 32 : 0;      // first query of this wave inside the row block
   const int c = lane & 31, h = lane >> 5;
   const int units = g.n_qb * g.group;
   Unit u;
@@ -202,16 +209,16 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
 
   // ---- operands -----------------------------------------------------------------------
   // Q fragments (B operand of S^T = K Q^T), resident for the whole row.
-  bf16x8 qf[QK8 ? 1 : 2][QK8 ? 1 : 8];
-  i32x4 qf8[QK8 ? 2 : 1][QK8 ? 4 : 1];
+  bf16x8 qf[QK8 ? 1 : NT][QK8 ? 1 : 8];
+  i32x4 qf8[QK8 ? NT : 1][QK8 ? 4 : 1];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     if constexpr (QK8) {
-      const int8_t* row = q8o.q8 + ((size_t)u.qh * g.seq + u.i * 64 + 32 * nt + c) * kHeadDim + 16 * h;
+      const int8_t* row = q8o.q8 + ((size_t)u.qh * g.seq + u.i * 64 + q0 + 32 * nt + c) * kHeadDim + 16 * h;
 #pragma unroll
       for (int s = 0; s < 4; ++s) qf8[nt][s] = *(const i32x4*)(row + 32 * s);
     } else {
-      const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + 32 * nt + c) + 8 * h;
+      const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 32 * nt + c) + 8 * h;
 #pragma unroll
       for (int s = 0; s < 8; ++s) qf[nt][s] = *(const bf16x8*)(row + 16 * s);
     }
@@ -261,21 +268,23 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
       for (int s2 = 0; s2 < 2; ++s2) vf[mt][dt][s2] = load_chunk<bf16x8>(vt, lane16, t, dt * 4 + s2);
   };
 
-  f32x16 oacc[4][2];
+  f32x16 oacc[4][NT];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[dt][nt][r] = 0.0f;
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.0f, 0.0f};      // m_run in log2 units
+  float m_run[NT], l_run[NT];      // m_run in log2 units
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) { m_run[nt] = -INFINITY; l_run[nt] = 0.0f; }
 
-  if (resume) {
+  if constexpr (NT == 2) if (resume) {
     const f32x4* so = st_o + (size_t)slot * 2048 + lane;       // [dt][nt][quarter][lane] 16-byte chunks
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
           const f32x4 w = so[((dt * 2 + nt) * 4 + qd) * 64];
@@ -328,9 +337,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) v8[dt][jj] = t[(dt * 2 + jj) * 64];
     };
-    f32x16 lacc[2];      // every register: sum over the row's keys of P8 (all 32 rows of the ones product are equal)
+    f32x16 lacc[NT];      // every register: sum over the row's keys of P8 (all 32 rows of the ones product are equal)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) lacc[nt][r] = 2.0f * l_run[nt];      // (parked as half the sum: see below)
     i32x8 ones8;
@@ -343,40 +352,40 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     // blocks pay nothing for it
     auto step8 = [&](int jn_or_j, auto diag) __attribute__((always_inline)) {
       // (the accumulators start at the bit pattern of kIntOffset and are read as floats, as in qk_half)
-      i32x16 a[2][2];
+      i32x16 a[2][NT];
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
+          for (int nt = 0; nt < NT; ++nt)
             a[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(k8[mt][s], qf8[nt][s], s == 0 ? magic : a[mt][nt], 0, 0, 0);
       const float cj = k_sc * sq_cs;                 // raw integer product -> logit in log2 units
       const float off = kIntOffset * cj;                 // what the offset amounts to in logit units
       fetch_k(jn_or_j);                              // (unconditional: the last block re-reads its own)
-      float S[2][2][16];
+      float S[2][NT][16];
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             S[mt][nt][r] = int_bits_as_float(a[mt][nt][r]);
             if constexpr (decltype(diag)::value) {
-              if (32 * mt + mfma32_row(r, lane) > 32 * nt + c) S[mt][nt][r] = -INFINITY;
+              if (32 * mt + mfma32_row(r, lane) > q0 + 32 * nt + c) S[mt][nt][r] = -INFINITY;
             }
           }
-      float mx[2];
+      float mx[NT];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         float v = fmaxf(S[0][nt][0], S[1][nt][0]);
 #pragma unroll
         for (int r = 1; r < 16; ++r) v = fmaxf(fmaxf(v, S[0][nt][r]), S[1][nt][r]);
         mx[nt] = __builtin_fmaf(max_with_other_half(v), cj, -off);
       }
-      if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[1] > m_run[1]) != 0ull) {
+      if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1]) != 0ull) {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
           const float m_new = fmaxf(m_run[nt], mx[nt]);
           const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m_new);
           m_run[nt] = m_new;
@@ -388,9 +397,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
             for (int r = 0; r < 16; ++r) oacc[dt][nt][r] *= alpha;
         }
       }
-      i32x8 p8[2];
+      i32x8 p8[NT];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         const float mb = m_run[nt] - kLog2Top + off;       // exp2(x - m) * 448, x = (S - offset) * cj
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
@@ -411,11 +420,11 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
 #pragma unroll
         for (int w = 0; w < 4; ++w) { va[w] = (int)v8[dt][0][w]; va[4 + w] = (int)v8[dt][1][w]; }
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
           oacc[dt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, p8[nt], oacc[dt][nt], 0, 0, 0, 0, 0, 0);
       }
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
         lacc[nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones8, p8[nt], lacc[nt], 0, 0, 0, 0, 0, 0);
       fetch_v(jn_or_j);                              // (unconditional as well: every path leaves the same loads in flight,
                                                      // so the next step waits for exactly the K8 it needs, not for everything)
@@ -433,7 +442,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     }
     // the common tail adds the two lane halves' partial sums; here every lane already holds the whole sum
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) l_run[nt] = 0.5f * lacc[nt][0];
+    for (int nt = 0; nt < NT; ++nt) l_run[nt] = 0.5f * lacc[nt][0];
   } else {
   // ---- pipeline stages ----------------------------------------------------------------
   // Half-tile score accumulators S[mt][nt] (keys 32mt.. x queries 32nt..) and the bf16 P^T operands
@@ -443,61 +452,62 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   //   stage B: S[1] = K Q^T of this block's half 1            ||  P[0] = exp2(S[0] - max), row sums
   //   stage C: O += V^T P^T of this block's half 0            ||  row max of S[1], rescale test
   //   stage D: S[0] = K Q^T of the NEXT block's half 0        ||  P[1] = exp2(S[1] - max), row sums
-  f32x16 S[2][2];
-  bf16x8 P[2][2][2];
+  f32x16 S[2][NT];
+  bf16x8 P[2][NT][2];
 
   auto qk_half = [&](int mt) __attribute__((always_inline)) {                       // S[mt][*] = K(half mt) Q^T
     if constexpr (QK8) {
       // The integer accumulators start at the bit pattern of kIntOffset = 1.5 * 2^23: an integer x with |x| < 2^22
       // added to it (the sums are below 127 * 127 * 128 < 2^21) gives the bit pattern of the FLOAT kIntOffset + x,
       // so the sums are read as floats without a conversion each; the offset leaves with the scaling FMAs.
-      i32x16 a0, a1;
+      i32x16 a[NT];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) a0[r] = a1[r] = 0x4B400000;
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        a0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf8[mt][s], qf8[0][s], a0, 0, 0, 0);
-        a1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf8[mt][s], qf8[1][s], a1, 0, 0, 0);
-      }
+        for (int r = 0; r < 16; ++r) a[nt][r] = 0x4B400000;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        S[mt][0][r] = int_bits_as_float(a0[r]);
-        S[mt][1][r] = int_bits_as_float(a1[r]);
-      }
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          a[nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf8[mt][s], qf8[nt][s], a[nt], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) S[mt][nt][r] = int_bits_as_float(a[nt][r]);
     } else {
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) S[mt][nt][r] = 0.0f;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        S[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mt][s], qf[0][s], S[mt][0], 0, 0, 0);
-        S[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mt][s], qf[1][s], S[mt][1], 0, 0, 0);
-      }
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          S[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mt][s], qf[nt][s], S[mt][nt], 0, 0, 0);
     }
   };
   auto pv_half = [&](int mt) __attribute__((always_inline)) {                       // O^T += V^T(half mt) P^T(half mt)
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        oacc[dt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mt][dt][s2], P[mt][0][s2], oacc[dt][0], 0, 0, 0);
-        oacc[dt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mt][dt][s2], P[mt][1][s2], oacc[dt][1], 0, 0, 0);
-      }
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          oacc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mt][dt][s2], P[mt][nt][s2], oacc[dt][nt], 0, 0, 0);
   };
   // Row maxima of the half-tile in slot mt (after causal masking where `diag` asks for it): mx[nt].
   // koff[mt]: first key of the slot's half-tile minus the first query row of the block (b_k = 32 only;
   // with b_k = 64 the masked pair is the diagonal block: 0 and 32).  A huge koff empties the slot.
-  float mx[2];
+  float mx[NT];
   int koff[2] = {0, 32};
   auto max_half = [&](int mt, auto diag) __attribute__((always_inline)) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       if constexpr (decltype(diag)::value) {
         const int ko = BK32 ? koff[mt] : 32 * mt;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (ko + mfma32_row(r, lane) > 32 * nt + c) S[mt][nt][r] = -INFINITY;
+          if (ko + mfma32_row(r, lane) > q0 + 32 * nt + c) S[mt][nt][r] = -INFINITY;
       }
       float v = fmaxf(S[mt][nt][0], S[mt][nt][1]);
 #pragma unroll
@@ -509,9 +519,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   // Lazy rescale: O and l are rescaled only when some row's maximum grew (exact: otherwise the factor
   // is 1).  Rows of the diagonal block that see no key of a half keep their (finite) maximum.
   auto rescale = [&]() __attribute__((always_inline)) {
-    if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[1] > m_run[1]) != 0ull) {
+    if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1]) != 0ull) {
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         const float m_new = fmaxf(m_run[nt], mx[nt]);
         float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m_new);
         // b_k = 32: a query row may have seen no key yet (its first half-tile lies above the diagonal)
@@ -536,7 +546,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     bf16x2 ones;
     ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       const float ch = cl[mt];
       float mb = (BK32 && m_run[nt] == -INFINITY) ? 0.0f : m_run[nt];
       if constexpr (QK8) mb += kIntOffset * ch;        // S carries the accumulators' offset
@@ -571,7 +581,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     if constexpr (!decltype(first)::value) pv_half(1);
     max_half(0, diag);
     load_v(cur.b, 1);
-    if constexpr (!decltype(first)::value) { SALE_PIPE(16, 2, 1) }
+    if constexpr (!decltype(first)::value) { SALE_PIPE(8 * NT, 2, 1) }
     rescale();
     // stage B
     qk_half(1);
@@ -581,14 +591,14 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
     pv_half(0);
     max_half(1, diag);
     if constexpr (!kLast) { load_k(nxt.b, 1); load_v(nxt.a, 0); }
-    SALE_PIPE(16, 6, 0)
-    SALE_PIPE(16, 2, 1)
+    SALE_PIPE(8 * NT, 6, 0)
+    SALE_PIPE(8 * NT, 2, 2 / NT)
     rescale();
     // stage D (kf[0] of the next pair was requested before stage A)
     if constexpr (!kLast) qk_half(0);
     exp_half(1);
     if constexpr (!kLast) {
-      if constexpr (QK8) { SALE_PIPE(8, 14, 0) } else { SALE_PIPE(16, 6, 0) }      // 8 MFMAs in the 8-bit first product
+      if constexpr (QK8) { SALE_PIPE(4 * NT, 14, 0) } else { SALE_PIPE(8 * NT, 6, 0) }      // (the 8-bit first product has half the MFMAs)
     }
     if constexpr (QK8 && !kLast) cl[0] = ks_pend[0] * sq_cs;      // slot 0 now holds the next pair's first half-tile
   };
@@ -665,12 +675,12 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
 
   }
 
-  if (park) {
+  if constexpr (NT == 2) if (park) {
     f32x4* so = st_o + (size_t)slot * 2048 + lane;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
           f32x4 w;
@@ -687,9 +697,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   // four banks) and leaves as whole 256-byte rows, 4 rows per instruction.
   constexpr int kRowPad = kHeadDim + 8;      // bf16 elements per LDS row
   __shared__ __attribute__((aligned(16))) uint16_t o_lds[WAVES * 64 * kRowPad];
-  uint16_t* const tile = o_lds + wave * 64 * kRowPad;
+  uint16_t* const tile = o_lds + (wave * 64 + q0) * kRowPad;
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     const float l_tot = l_run[nt] + swap_half(l_run[nt]);
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
     if constexpr (PV8) {      // O = v_scale[channel] * (sum P8 V8) / (sum P8)
@@ -703,7 +713,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
           for (int e = 0; e < 4; ++e) oacc[dt][nt][4 * q4 + e] *= sc[e];
         }
     }
-    const size_t row = (size_t)u.qh * g.seq + u.i * 64 + 32 * nt + c;
+    const size_t row = (size_t)u.qh * g.seq + u.i * 64 + q0 + 32 * nt + c;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -722,11 +732,12 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
       }
     if (lse && h == 0) {
       // (PV8: the sum is that of 448 p)
-      float v = l_tot > 0.0f ? m_run[nt] * 0.6931471805599453f + __logf(PV8 ? l_tot * (1.0f / 448.0f) : l_tot) : -INFINITY;
+      // (the FMA is spelled out so that every instance of the kernel rounds alike)
+      float v = l_tot > 0.0f ? __builtin_fmaf(m_run[nt], 0.6931471805599453f, __logf(PV8 ? l_tot * (1.0f / 448.0f) : l_tot)) : -INFINITY;
       if constexpr (QK8) {
         // The 8-bit logits are those of K minus its mean key, i.e. Eq. 1's logits of this row minus q_r . mean /
         // sqrt(d) (which the softmax cancels in O); lse is reported for Eq. 1's S, so the shift goes back in.
-        const uint16_t* qr = q + row_off(g.sq, u.qh, u.i * 64 + 32 * nt + c);
+        const uint16_t* qr = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 32 * nt + c);
         const float* mean = q8o.k_mean + (size_t)u.kvh * kHeadDim;
         float dot = 0.0f;
         for (int ch = 0; ch < kHeadDim; ++ch) dot = __builtin_fmaf(bf16_bits_to_float(qr[ch]), mean[ch], dot);
@@ -737,9 +748,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_rows_kernel(Geo g, const uint
   }
   if (!o32) {
     // (each wave reads back only its own tile: no barrier, LDS operations of a wave complete in order)
-    uint16_t* const out = o + row_off(g.so, u.qh, u.i * 64);
+    uint16_t* const out = o + row_off(g.so, u.qh, u.i * 64 + q0);
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
+    for (int it = 0; it < 8 * NT; ++it) {
       const int r = 4 * it + (lane >> 4), ch = 8 * (lane & 15);
       *(u32x4*)(out + (size_t)r * g.so.st + ch) = *(const u32x4*)(tile + r * kRowPad + ch);
     }
@@ -965,6 +976,33 @@ constexpr int kWindowMinWords = 4;   // sequences of up to 16K tokens use one sw
 
 namespace {
 
+// Whether a call of `rows` 64-row blocks without window launches runs with two waves per row (NT = 1).  Up to about one
+// row per SIMD (1024) the longest row is the call, and half a row per wave shortens it; with many rows the operand loads,
+// twice as many per FLOP, cost more than that gives.  One wave -> two waves per row, us:
+//   sparse bf16:  256 rows 22.2 -> 20.8, 1024 (2K x 32 heads) 64.5 -> 54.0, 1024 (16K x 4) 342 -> 223, 1308 (7K x 12)
+//                 175.7 -> 122.3, 1536 (3K x 32) 93.9 -> 90.5, 2080 (4K x 32) 136.0 -> 139.5, 8192 (16K x 32) 808 -> 973
+//   32-key blocks (fewer registers: two waves share a SIMD): 1536 96.8 -> 72.4, 2080 134.4 -> 112.0
+//   sparse FP8:   1024 84.3 -> 75.1, 1280 97.9 -> 97.7, 1536 111.9 -> 118.3
+//   dense bf16:   512 39.8 -> 27.4, 1024 66.4 -> 53.1, 1280 84.5 -> 80.4, 1536 97.6 -> 104.5
+//   dense FP8:    1024 87.5 -> 76.7, 1280 104.3 -> 107.1
+bool halves_of(long rows, bool dense, bool bk32, bool pv8) {
+  return rows <= (dense ? (pv8 ? 1024 : 1280) : bk32 ? 2080 : pv8 ? 1280 : 1536);
+}
+
+template <bool QK8, bool PV8>
+int launch_dense_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, uint16_t* o, float* o32,
+                      float* lse, hipStream_t st) {
+  const int units = g.n_qb * g.group;
+  const RowFilter all = {nullptr, -1, 0, -1, 0, 0};
+#define SALE_DENSE_ARGS g, q, kp, vp, q8o, nullptr, nullptr, nullptr, o, o32, lse, all, nullptr, nullptr
+  if (halves_of((long)units * g.n_kvh, true, false, PV8))
+    attn_rows_kernel<1, false, QK8, PV8, 1><<<dim3((unsigned)(units * g.n_kvh)), dim3(128), 0, st>>>(SALE_DENSE_ARGS);
+  else
+    attn_rows_kernel<4, false, QK8, PV8><<<dim3((unsigned)(((units + 3) / 4) * g.n_kvh)), dim3(256), 0, st>>>(SALE_DENSE_ARGS);
+#undef SALE_DENSE_ARGS
+  return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
+}
+
 template <bool BK32, bool QK8, bool PV8 = false>
 int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, const uint64_t* mask,
                        const int32_t* row_counts, int32_t* order, int32_t* assign, LaneLoad* load, int32_t* slot_of,
@@ -980,6 +1018,11 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
     order_units_kernel<<<dim3((unsigned)g.n_kvh), dim3(1024), 0, st>>>(g, row_counts, order, windows ? slot_of : nullptr,
                                                                        kLongRow * f, n_slots, slot_counter);
     if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
+  }
+  if (!windows && halves_of((long)units * g.n_kvh, false, BK32, PV8)) {
+    attn_rows_kernel<1, BK32, QK8, PV8, 1><<<grid, dim3(128), 0, st>>>(g, q, kp, vp, q8o, mask, row_counts ? order : nullptr, nullptr,
+                                                                       o, o32, lse, all, nullptr, nullptr);
+    return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
   if (!windows) {
     // (one sweep per row: every row reads K', V' of the whole sequence, and moving rows to another XCD costs
@@ -1108,19 +1151,9 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
     return qk8 ? launch_sparse_rows<false, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<false, false>(SALE_SPARSE_ARGS);
 #undef SALE_SPARSE_ARGS
   }
-  const int units = g.n_qb * g.group;
-  const RowFilter all = {nullptr, -1, 0, -1, 0, 0};
-  const dim3 grid((unsigned)(((units + 3) / 4) * g.n_kvh));
-  if (pv8)
-    attn_rows_kernel<4, false, true, true><<<grid, dim3(256), 0, st>>>(g, qq, kpp, vpp, q8o, nullptr, nullptr, nullptr, (uint16_t*)o,
-                                                                      o32, lse, all, nullptr, nullptr);
-  else if (qk8)
-    attn_rows_kernel<4, false, true><<<grid, dim3(256), 0, st>>>(g, qq, kpp, vpp, q8o, nullptr, nullptr, nullptr, (uint16_t*)o, o32,
-                                                                lse, all, nullptr, nullptr);
-  else
-    attn_rows_kernel<4, false, false><<<grid, dim3(256), 0, st>>>(g, qq, kpp, vpp, q8o, nullptr, nullptr, nullptr, (uint16_t*)o, o32,
-                                                                 lse, all, nullptr, nullptr);
-  return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
+  if (pv8) return launch_dense_rows<true, true>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st);
+  return qk8 ? launch_dense_rows<true, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st)
+             : launch_dense_rows<false, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st);
 }
 
 }  // namespace sale

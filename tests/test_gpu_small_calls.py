@@ -43,3 +43,30 @@ def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv
     for n in batches:
         mask_n, counts_n = choose(n)
         assert torch.equal(mask_n, mask.expand_as(mask_n)) and torch.equal(counts_n, counts.expand_as(counts_n)), n
+
+
+# 1024 tokens, 8 / 2 heads: 128 rows alone (two waves per row), 2176 rows seventeen times (one).  704 tokens: an odd
+# number of blocks, one head per KV head; 64: nothing but the diagonal block.
+@pytest.mark.parametrize("attn", ["bf16", "int8", "fp8"])
+@pytest.mark.parametrize("block_k", [64, 32])
+@pytest.mark.parametrize("tokens,q_heads,kv_heads,n", [(1024, 8, 2, 17), (704, 3, 3, 64), (64, 4, 1, 600)])
+def test_attention_does_not_depend_on_waves_per_row(sale, attn, block_k, tokens, q_heads, kv_heads, n):
+    if attn == "fp8" and block_k == 32:
+        pytest.skip("the FP8 second product takes 64-key blocks only")
+    _, (q, k, v) = _qkv(tokens, q_heads, kv_heads)
+    flags = {"bf16": 0, "int8": sale.FLAG_ATTN_INT8_QK, "fp8": sale.FLAG_ATTN_INT8_QK | sale.FLAG_ATTN_FP8_PV}[attn]
+    gen = torch.Generator(device="cuda").manual_seed(tokens + block_k)
+    p1 = sale.Params(1, q_heads, kv_heads, tokens, block_k=block_k, flags=flags)
+    # random masks: odd counts, rows that keep only early blocks
+    mask = torch.randint(-2 ** 62, 2 ** 62, (1, q_heads, p1.n_q, p1.words), generator=gen, dtype=torch.int64, device="cuda") | 1
+
+    def attend(m):
+        p = sale.Params(m, q_heads, kv_heads, tokens, block_k=block_k, flags=flags)
+        qm, km, vm = (t.expand(m, -1, -1, -1).contiguous() for t in (q, k, v))
+        out = [torch.full_like(qm, float("nan")) for _ in range(2)]
+        o, lse = sale.sparse_attn(p, qm, km, vm, mask.expand(m, -1, -1, -1).contiguous(), want_lse=True, out=out[0])
+        od, lsed = sale.dense_attn(p, qm, km, vm, want_lse=True, out=out[1])
+        return o, lse, od, lsed
+
+    for alone, many in zip(attend(1), attend(n)):
+        assert torch.isfinite(alone.float()).all() and torch.equal(many, alone.expand_as(many))
