@@ -32,6 +32,79 @@ __device__ __forceinline__ bool in_sink_local(const Geo& g, int j, int j_last, i
   return j < g.sink_blocks || j > j_last - local;
 }
 
+// ---------------------------------------------------------------------------
+// 4-bit estimate on the FP6 (E2M3) MFMA
+// ---------------------------------------------------------------------------
+// CDNA4 has no int4 MFMA.  Every integer in [-7, 7] is exactly representable in
+// FP6 E2M3 (1 sign, 2 exponent, 3 mantissa bits, bias 1: 1 = 0b001000, 2 =
+// 0b010000, 3 = 0b010100, 4 = 0b011000, 5 = 0b011010, 6 = 0b011100, 7 =
+// 0b011110), products are at most 49 and a 128-term sum at most 6272 < 2^24, so
+// v_mfma_f32_32x32x64_f8f6f4 with both operands in E2M3 and unit scales returns
+// the integer product EXACTLY in its fp32 accumulator (checked on hardware
+// against integer arithmetic, including all-(+-7) operands) at twice the int8
+// MFMA rate.  A pre-pass re-encodes the nibble codes of K~ once into MFMA operand
+// order ("X6"; Q~ is re-encoded by the wave that uses it): per group of 32 rows 2 fragments ks (channels 64ks..); lane l of a
+// fragment owns row l%32 of the group, channels 64ks + 32(l/32) + e, e = 0..31, as
+// 32 six-bit codes = 6 dwords, stored as
+//   [group][ks][lane] 16 bytes (dwords 0..3)  followed by  [group][ks][lane] 8 bytes (dwords 4..5).
+constexpr int kX6GroupBytes = 2 * 64 * 24;   // 3072 bytes per 32 rows
+
+// (about 30 vector instructions per 8 codes; code by code it took 64 and was 7 us of a wave of select_kernel)
+// E2M3 codes of the four 4-bit two's-complement nibbles (-7..7) in the low halves of the bytes of n (the high halves
+// are zero): two byte look-ups by the low three bits, for n >= 0 and n < 0, chosen by the sign bit.
+__device__ __forceinline__ uint32_t e2m3_of_nibbles(uint32_t n) {
+  const uint32_t at = n & 0x07070707u, sign = n & 0x08080808u;
+  const uint32_t pos = __builtin_amdgcn_perm(0x1E1C1A18u, 0x14100800u, at);       // 0, 1, 2, 3 | 4, 5, 6, 7
+  const uint32_t neg = __builtin_amdgcn_perm(0x28303438u, 0x3A3C3E20u, at);       // (-8: -0), -7, -6, -5 | -4, -3, -2, -1
+  const uint32_t is_neg = (sign << 5) - (sign >> 3);                              // 0xFF in the bytes of negative codes
+  return (neg & is_neg) | (pos & ~is_neg);
+}
+
+// 16 packed bytes (32 nibble codes, channel order) -> 32 six-bit codes in 6 dwords.
+__device__ __forceinline__ void pack_fp6(const u32x4 w, uint32_t out[6]) {
+  uint32_t f[8];      // 24 bits each: the codes of two bytes
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t lo = e2m3_of_nibbles(w[d] & 0x0F0F0F0Fu), hi = e2m3_of_nibbles((w[d] >> 4) & 0x0F0F0F0Fu);
+    const uint32_t x0 = (lo & 0x00FF00FFu) | ((hi & 0x00FF00FFu) << 6);                  // 12 bits: bytes 0 and 2
+    const uint32_t x1 = ((lo >> 8) & 0x00FF00FFu) | (((hi >> 8) & 0x00FF00FFu) << 6);    //          bytes 1 and 3
+    f[2 * d] = (x0 & 0xFFFu) | ((x1 & 0xFFFu) << 12);
+    f[2 * d + 1] = (x0 >> 16) | ((x1 >> 16) << 12);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {      // four 24-bit pieces make three dwords
+    const uint32_t* p = f + 4 * t;
+    out[3 * t] = p[0] | (p[1] << 24);
+    out[3 * t + 1] = (p[1] >> 8) | (p[2] << 16);
+    out[3 * t + 2] = (p[2] >> 16) | (p[3] << 8);
+  }
+}
+
+// Re-encoding of a nibble-packed [32 * groups][64-byte] matrix: one thread per (32-row group, fragment, lane).  It is
+// the last workgroups of the statistics launch (from number `first` on), which it does not depend on: a launch of its
+// own cost 3 us in the smallest calls and its streaming (49 us at 128K) now runs beside the statistics.
+struct PackFp6 {
+  const uint8_t* x;
+  uint8_t* y;
+  long groups;
+  int first;
+  __device__ __forceinline__ void run(int block) const {
+    const long grp = (long)(block - first) * (blockDim.x >> 7) + (threadIdx.x >> 7);
+    if (grp >= groups) return;
+    const int ks = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63;
+    const u32x4 w = *(const u32x4*)(x + ((size_t)grp * 32 + (lane & 31)) * 64 + 32 * ks + 16 * (lane >> 5));
+    uint32_t d[6];
+    pack_fp6(w, d);
+    uint8_t* yg = y + (size_t)grp * kX6GroupBytes;
+    u32x4 lo;
+    lo[0] = d[0]; lo[1] = d[1]; lo[2] = d[2]; lo[3] = d[3];
+    u32x2 hi;
+    hi[0] = d[4]; hi[1] = d[5];
+    *(u32x4*)(yg + (ks * 64 + lane) * 16) = lo;
+    *(u32x2*)(yg + 2048 + (ks * 64 + lane) * 8) = hi;
+  }
+};
+
 // Rows that several waves of select_kernel share: the statistics kernel, which runs before it, clears their counts and
 // (where several waves share a mask word) their mask words.
 struct ClearRows {
@@ -47,25 +120,41 @@ struct ClearRows {
 // ---------------------------------------------------------------------------
 // Sink-local statistics (display equation of Sec. 3.2; first loop of Alg. 1)
 // ---------------------------------------------------------------------------
-template <int MT>
-__global__ __launch_bounds__(256) void stats_kernel(Geo g, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+//
+// NT: 32-query tiles per wave.  NT = 2: one wave per row, four rows per workgroup.  NT = 1: the two waves of a workgroup
+// take 32 queries each of one row; the same arithmetic per query, half of it per wave and step.
+template <int MT, int NT>
+__global__ __launch_bounds__(NT == 1 ? 128 : 256) void stats_kernel(Geo g, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                     const float* __restrict__ tau, int tau_len, float* __restrict__ thr,
-                                                    float* __restrict__ m_out, float* __restrict__ l_out, ClearRows clear) {
+                                                    float* __restrict__ m_out, float* __restrict__ l_out, ClearRows clear, PackFp6 pack) {
+  if ((int)blockIdx.x >= pack.first) { pack.run(blockIdx.x); return; }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform by construction
-  const Unit u = unit_of(g, blockIdx.x, wave);
-  if (!u.valid) return;
-  clear.row(g, u, lane);
+  Unit u;
+  int q0 = 0;                          // first query of this wave inside the row block
+  if constexpr (NT == 1) {
+    const int id = g.n_qb * g.group - 1 - (int)blockIdx.x / g.n_kvh;
+    u.kvh = blockIdx.x % g.n_kvh;
+    u.i = id / g.group;
+    u.qh = u.kvh * g.group + id % g.group;
+    q0 = 32 * wave;
+  } else {
+    u = unit_of(g, blockIdx.x, wave);
+    if (!u.valid) return;
+  }
+  if (q0 == 0) clear.row(g, u, lane);
   const int c = lane & 31, h = lane >> 5;
   const float rsd = 0.08838834764831845f;   // 1 / sqrt(128)
 
-  bf16x8 qf[2][8];
+  bf16x8 qf[NT][8];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + 32 * nt + c) + 8 * h;
+  for (int nt = 0; nt < NT; ++nt) {
+    const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 32 * nt + c) + 8 * h;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[nt][s] = *(const bf16x8*)(row + 16 * s);
   }
-  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0f, 0.0f};
+  float m[NT], l[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) { m[nt] = -INFINITY; l[nt] = 0.0f; }
   const SeqPos sp = seq_pos(g, u.i);               // (variable-length batches: block indices inside the row's sequence)
   const int j_last = j_last_of(g, sp.il), local = local_of(g, j_last);
   // The sink-local blocks of the row, numbered t = 0 ..: the sink blocks that are not local ones, then the local
@@ -84,30 +173,30 @@ __global__ __launch_bounds__(256) void stats_kernel(Geo g, const uint16_t* __res
   const float kLog2e = 1.4426950408889634f;
   auto half = [&](int hs, const bf16x8 (&kk)[8], bf16x8 (&kn)[8]) __attribute__((always_inline)) {
     fetch(min(hs + 1, n_hs - 1), kn);
-    f32x16 acc[2];
+    f32x16 acc[NT];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[nt][r] = 0.0f;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[s], qf[0][s], acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[s], qf[1][s], acc[1], 0, 0, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[s], qf[nt][s], acc[nt], 0, 0, 0);
     }
     const int j = block_of(hs), mt = hs % MT;
     // keys of this half that lie after a query row (only with SALE_FLAG_STATS_CAUSAL)
     const int ahead = j * g.bk + 32 * mt - sp.il * 64;      // first key of the half minus first query row
     if (g.stats_causal && ahead + 31 > 0) {
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (ahead + mfma32_row(r, lane) > 32 * nt + c) acc[nt][r] = -INFINITY;
+          if (ahead + mfma32_row(r, lane) > q0 + 32 * nt + c) acc[nt][r] = -INFINITY;
     }
     // (VALU-bound: per score one half of a v_max3, one FMA that folds 1 / sqrt(d), log2(e) and the maximum,
     // one v_exp_f32 and one add)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       float mx = fmaxf(acc[nt][0], acc[nt][1]);
 #pragma unroll
       for (int r = 2; r < 16; r += 2) mx = fmaxf(fmaxf(mx, acc[nt][r]), acc[nt][r + 1]);
@@ -130,13 +219,13 @@ __global__ __launch_bounds__(256) void stats_kernel(Geo g, const uint16_t* __res
     }
   }
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     const float m_o = swap_half(m[nt]), l_o = swap_half(l[nt]);
     const float m_t = fmaxf(m[nt], m_o);
     const float m_safe = m_t == -INFINITY ? 0.0f : m_t;
     const float l_t = l[nt] * __expf(m[nt] - m_safe) + l_o * __expf(m_o - m_safe);
     if (h == 0) {
-      const size_t idx = (size_t)u.qh * g.seq + u.i * 64 + 32 * nt + c;
+      const size_t idx = (size_t)u.qh * g.seq + u.i * 64 + q0 + 32 * nt + c;
       const float t = tau[tau_len == 1 ? 0 : u.qh % g.hq_per_b];
       thr[idx] = __logf(t * l_t) + m_t;
       if (m_out) m_out[idx] = m_t;
@@ -155,7 +244,8 @@ template <int MT>
 __global__ __launch_bounds__(256) void stats_shared_kernel(Geo g, const uint16_t* __restrict__ q,
                                                            const uint16_t* __restrict__ k, const float* __restrict__ tau,
                                                            int tau_len, float* __restrict__ thr, float* __restrict__ m_out,
-                                                           float* __restrict__ l_out, ClearRows clear) {
+                                                           float* __restrict__ l_out, ClearRows clear, PackFp6 pack) {
+  if ((int)blockIdx.x >= pack.first) { pack.run(blockIdx.x); return; }
   __shared__ bf16x8 k_lds[2][8 * 64];                // [buffer][s][lane] 16 bytes: the A operands of one half-block
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -254,76 +344,6 @@ __global__ __launch_bounds__(256) void stats_shared_kernel(Geo g, const uint16_t
       if (l_out) l_out[idx] = l_t;
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// 4-bit estimate on the FP6 (E2M3) MFMA
-// ---------------------------------------------------------------------------
-// CDNA4 has no int4 MFMA.  Every integer in [-7, 7] is exactly representable in
-// FP6 E2M3 (1 sign, 2 exponent, 3 mantissa bits, bias 1: 1 = 0b001000, 2 =
-// 0b010000, 3 = 0b010100, 4 = 0b011000, 5 = 0b011010, 6 = 0b011100, 7 =
-// 0b011110), products are at most 49 and a 128-term sum at most 6272 < 2^24, so
-// v_mfma_f32_32x32x64_f8f6f4 with both operands in E2M3 and unit scales returns
-// the integer product EXACTLY in its fp32 accumulator (checked on hardware
-// against integer arithmetic, including all-(+-7) operands) at twice the int8
-// MFMA rate.  A pre-pass re-encodes the nibble codes of K~ once into MFMA operand
-// order ("X6"; Q~ is re-encoded by the wave that uses it): per group of 32 rows 2 fragments ks (channels 64ks..); lane l of a
-// fragment owns row l%32 of the group, channels 64ks + 32(l/32) + e, e = 0..31, as
-// 32 six-bit codes = 6 dwords, stored as
-//   [group][ks][lane] 16 bytes (dwords 0..3)  followed by  [group][ks][lane] 8 bytes (dwords 4..5).
-constexpr int kX6GroupBytes = 2 * 64 * 24;   // 3072 bytes per 32 rows
-
-// (about 30 vector instructions per 8 codes; code by code it took 64 and was 7 us of a wave of select_kernel)
-// E2M3 codes of the four 4-bit two's-complement nibbles (-7..7) in the low halves of the bytes of n (the high halves
-// are zero): two byte look-ups by the low three bits, for n >= 0 and n < 0, chosen by the sign bit.
-__device__ __forceinline__ uint32_t e2m3_of_nibbles(uint32_t n) {
-  const uint32_t at = n & 0x07070707u, sign = n & 0x08080808u;
-  const uint32_t pos = __builtin_amdgcn_perm(0x1E1C1A18u, 0x14100800u, at);       // 0, 1, 2, 3 | 4, 5, 6, 7
-  const uint32_t neg = __builtin_amdgcn_perm(0x28303438u, 0x3A3C3E20u, at);       // (-8: -0), -7, -6, -5 | -4, -3, -2, -1
-  const uint32_t is_neg = (sign << 5) - (sign >> 3);                              // 0xFF in the bytes of negative codes
-  return (neg & is_neg) | (pos & ~is_neg);
-}
-
-// 16 packed bytes (32 nibble codes, channel order) -> 32 six-bit codes in 6 dwords.
-__device__ __forceinline__ void pack_fp6(const u32x4 w, uint32_t out[6]) {
-  uint32_t f[8];      // 24 bits each: the codes of two bytes
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const uint32_t lo = e2m3_of_nibbles(w[d] & 0x0F0F0F0Fu), hi = e2m3_of_nibbles((w[d] >> 4) & 0x0F0F0F0Fu);
-    const uint32_t x0 = (lo & 0x00FF00FFu) | ((hi & 0x00FF00FFu) << 6);                  // 12 bits: bytes 0 and 2
-    const uint32_t x1 = ((lo >> 8) & 0x00FF00FFu) | (((hi >> 8) & 0x00FF00FFu) << 6);    //          bytes 1 and 3
-    f[2 * d] = (x0 & 0xFFFu) | ((x1 & 0xFFFu) << 12);
-    f[2 * d + 1] = (x0 >> 16) | ((x1 >> 16) << 12);
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {      // four 24-bit pieces make three dwords
-    const uint32_t* p = f + 4 * t;
-    out[3 * t] = p[0] | (p[1] << 24);
-    out[3 * t + 1] = (p[1] >> 8) | (p[2] << 16);
-    out[3 * t + 2] = (p[2] >> 16) | (p[3] << 8);
-  }
-}
-
-// One thread per (32-row group, fragment, lane) of a nibble-packed [rows][64-byte] matrix; a workgroup
-// handles two groups.  (Two matrices in one launch; the second may be empty.)
-__global__ __launch_bounds__(256) void pack_fp6_kernel(const uint8_t* __restrict__ xa, uint8_t* __restrict__ ya,
-                                                       long groups_a, const uint8_t* __restrict__ xb,
-                                                       uint8_t* __restrict__ yb, long groups_b) {
-  long grp = (long)blockIdx.x * 2 + (threadIdx.x >> 7);
-  const uint8_t* x = xa;
-  uint8_t* y = ya;
-  if (grp >= groups_a) { grp -= groups_a; x = xb; y = yb; if (grp >= groups_b) return; }
-  const int ks = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63;
-  const u32x4 w = *(const u32x4*)(x + ((size_t)grp * 32 + (lane & 31)) * 64 + 32 * ks + 16 * (lane >> 5));
-  uint32_t d[6];
-  pack_fp6(w, d);
-  uint8_t* yg = y + (size_t)grp * kX6GroupBytes;
-  u32x4 lo;
-  lo[0] = d[0]; lo[1] = d[1]; lo[2] = d[2]; lo[3] = d[3];
-  u32x2 hi;
-  hi[0] = d[4]; hi[1] = d[5];
-  *(u32x4*)(yg + (ks * 64 + lane) * 16) = lo;
-  *(u32x2*)(yg + 2048 + (ks * 64 + lane) * 8) = hi;
 }
 
 // The 2 operand fragments (ks = 0, 1) of 32-row group `grp` of an X6 array.
@@ -616,7 +636,7 @@ int select_chunk(const Geo& g, int hpw) {
 }
 
 template <int MT>
-int launch_select(const Geo& g, bool est16, const void* q, const void* k, const uint8_t* q4, const uint8_t* k6,
+int launch_select(const Geo& g, bool est16, const void* q, const void* k, const uint8_t* q4, const uint8_t* k4, uint8_t* k6,
                   const float* q_scale, const float* k_scale, const float* tau, int tau_len, const float* thr_c,
                   float* thr, uint64_t* block_mask, int32_t* row_counts, float* m_out, float* l_out, hipStream_t st) {
   const int tiles = (g.n_qb * g.group + 3) / 4;
@@ -624,12 +644,19 @@ int launch_select(const Geo& g, bool est16, const void* q, const void* k, const 
   const int hpw = MT == 2 && g.group % 4 == 0 ? 4 : g.group % 2 == 0 ? 2 : 1;
   const int chunk = est16 ? 0 : select_chunk(g, hpw);
   const ClearRows clear = {chunk ? row_counts : nullptr, chunk && chunk < 64 ? block_mask : nullptr};
-  if (g.group % 4 == 0)      // (then every workgroup holds 4 heads of one KV head at one query block: they share K)
-    stats_shared_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k,
-                                                                                    tau, tau_len, thr, m_out, l_out, clear);
-  else
-    stats_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k, tau,
-                                                                             tau_len, thr, m_out, l_out, clear);
+  const long kgroups = est16 ? 0 : (long)g.n_kvh * (g.seq / 32);
+  const bool shared = g.group % 4 == 0;      // (then 4 heads of one KV head at one query block share K)
+  // Two waves per row while every row still finds a CU of its own: one head of 2K tokens (32 rows) 20.2 -> 18.2 us a
+  // select call; at 1308 rows it loses (52.7 -> 58.5).  (Where K is shared it changes nothing: 50.8, 50.9 us at 4K.)
+  const bool halves = !shared && (long)g.n_qb * g.n_qh <= 256;
+  const int threads = halves ? 128 : 256;
+  const PackFp6 pack = {k4, k6, kgroups, halves ? g.n_qb * g.n_qh : tiles * g.n_kvh};
+  const dim3 stats_grid((unsigned)(pack.first + (kgroups + threads / 128 - 1) / (threads / 128)));
+#define SALE_STATS_ARGS g, (const uint16_t*)q, (const uint16_t*)k, tau, tau_len, thr, m_out, l_out, clear, pack
+  if (shared) stats_shared_kernel<MT><<<stats_grid, dim3(256), 0, st>>>(SALE_STATS_ARGS);
+  else if (halves) stats_kernel<MT, 1><<<stats_grid, dim3(128), 0, st>>>(SALE_STATS_ARGS);
+  else stats_kernel<MT, 2><<<stats_grid, dim3(256), 0, st>>>(SALE_STATS_ARGS);
+#undef SALE_STATS_ARGS
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   if (est16) {
     select16_kernel<MT><<<dim3((unsigned)(tiles * g.n_kvh)), dim3(256), 0, st>>>(g, (const uint16_t*)q, (const uint16_t*)k,
@@ -666,7 +693,7 @@ int check_select_args(const sale_params_t* p, const void* q, const void* k, cons
 }
 
 // The Selection-Pass on a workspace that has been checked.  Every byte of the workspace that a kernel reads is
-// written earlier in the same call (thresholds by the statistics kernel, operand copies by the packing kernel),
+// written earlier in the same call (thresholds and operand copies by the statistics launch),
 // so nothing in it has to be cleared.
 int run_select(const sale_params_t* p, const void* q, const void* k, const uint8_t* q4, const uint8_t* k4,
                const float* q_scale, const float* k_scale, const float* tau, int32_t tau_len, uint64_t* block_mask,
@@ -681,14 +708,9 @@ int run_select(const sale_params_t* p, const void* q, const void* k, const uint8
     if (rc != SALE_OK) return rc;
     g.seq_start = table;
   }
-  const long kgroups = (long)g.n_kvh * (g.seq / 32);
-  if (!est16) {
-    pack_fp6_kernel<<<dim3((unsigned)((kgroups + 1) / 2)), dim3(256), 0, st>>>(k4, k6, kgroups, nullptr, nullptr, 0);
-    if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  }
-  return g.bk == 64 ? launch_select<2>(g, est16, q, k, q4, k6, q_scale, k_scale, tau, tau_len, thr, thr, block_mask,
+  return g.bk == 64 ? launch_select<2>(g, est16, q, k, q4, k4, k6, q_scale, k_scale, tau, tau_len, thr, thr, block_mask,
                                        row_counts, m_out, l_out, st)
-                    : launch_select<1>(g, est16, q, k, q4, k6, q_scale, k_scale, tau, tau_len, thr, thr, block_mask,
+                    : launch_select<1>(g, est16, q, k, q4, k4, k6, q_scale, k_scale, tau, tau_len, thr, thr, block_mask,
                                        row_counts, m_out, l_out, st);
 }
 
