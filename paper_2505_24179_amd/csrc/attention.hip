@@ -59,6 +59,11 @@ namespace sale {
 // (the key order inside V' is the order in which the S^T accumulator registers
 // hand P^T to the second product).
 // ---------------------------------------------------------------------------
+// K, V: which copies are made.  The 8-bit first product does not read K' and the FP8 second product not V': without the
+// copies nobody reads the attention call with int8 takes 1496 instead of 1512 us at 25K, with FP8 7446 instead of 7544
+// us at 64K.  (As template parameters: a run-time test kept the loads of V from being in flight with those of K, 28.0
+// instead of 27.5 us in the dense call of 1K tokens.)
+template <bool K, bool V>
 __global__ __launch_bounds__(256) void rearrange_kv_kernel(int seq, const uint16_t* __restrict__ k, Strided lk,
                                                            const uint16_t* __restrict__ v, Strided lv,
                                                            u32x4* __restrict__ kp, u32x4* __restrict__ vp,
@@ -71,7 +76,7 @@ __global__ __launch_bounds__(256) void rearrange_kv_kernel(int seq, const uint16
   const uint16_t* kt = k + row_off(lk, (int)(tile / tiles_per_head), (int)(tile % tiles_per_head) * 64);
   const uint16_t* vt = v + row_off(lv, (int)(tile / tiles_per_head), (int)(tile % tiles_per_head) * 64);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < (V ? 4 : 0); ++r) {
     const int chunk = tid + 256 * r;                   // V tile -> LDS, rows padded by one bank
     const int row = chunk >> 4, col = (chunk & 15) * 8;
     const u32x4 w = *(const u32x4*)(vt + (size_t)row * lv.st + col);
@@ -79,11 +84,12 @@ __global__ __launch_bounds__(256) void rearrange_kv_kernel(int seq, const uint16
     d[0] = w[0]; d[1] = w[1]; d[2] = w[2]; d[3] = w[3];
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < (K ? 4 : 0); ++r) {
     const int oc = tid + 256 * r;
     const int lane = oc & 63, s = (oc >> 6) & 7, mt = oc >> 9;
     kp[tile * 1024 + oc] = *(const u32x4*)(kt + (size_t)(32 * mt + (lane & 31)) * lk.st + 16 * s + 8 * (lane >> 5));
   }
+  if constexpr (!V) return;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -1121,12 +1127,15 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   f32x4* st_o = (f32x4*)w.parked;                               // [slot] 32 KB
   float* st_ml = (float*)(w.parked + (size_t)n_slots * 2048 * 16);      // [slot] 1 KB
   int32_t *order = w.order, *assign = w.assign;
-  rearrange_kv_kernel<<<dim3((unsigned)(g.n_kvh * (g.seq / 64))), dim3(256), 0, st>>>(g.seq, (const uint16_t*)k, g.sk,
-                                                                                    (const uint16_t*)v, g.sv, kp, vp,
-                                                                                    w.slot_counter);
-  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   const bool qk8 = (p->flags & SALE_FLAG_ATTN_INT8_QK) != 0;
   const bool pv8 = (p->flags & SALE_FLAG_ATTN_FP8_PV) != 0;      // (validated: only with qk8 and 64-key blocks)
+  const dim3 kv_tiles((unsigned)(g.n_kvh * (g.seq / 64)));
+#define SALE_REARRANGE_ARGS g.seq, (const uint16_t*)k, g.sk, (const uint16_t*)v, g.sv, kp, vp, w.slot_counter
+  if (!qk8) rearrange_kv_kernel<true, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
+  else if (!pv8) rearrange_kv_kernel<false, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
+  else if (w.slot_counter) rearrange_kv_kernel<false, false><<<dim3(1), dim3(64), 0, st>>>(SALE_REARRANGE_ARGS);      // (clears the counter)
+#undef SALE_REARRANGE_ARGS
+  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   Qk8 q8o = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (qk8) {
     const Int8Operands w8i = carve_int8_operands(p, (void*)w.ops8);
