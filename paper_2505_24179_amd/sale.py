@@ -126,7 +126,7 @@ def _check(status: int) -> None:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # (the argument types make it a void pointer)
 
 
 def _expect(name: str, t, dtype, numel: int, optional: bool = False):
@@ -166,7 +166,7 @@ def _expect_bhnd(name: str, t, p: "Params", heads: int):
     _expect(name, t, torch.bfloat16, p.batch * heads * p.seq_len * p.head_dim)
 
 
-def _expect_ws(ws, need: int):
+def _expect_ws(ws):
     """-> the workspace's size in BYTES (whatever its dtype).  Size and alignment are the library's to judge
     (SALE_ERR_WORKSPACE)."""
     if ws is None or not ws.is_cuda or not ws.is_contiguous():
@@ -179,7 +179,8 @@ def _qkv_numel(p: "Params"):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # (the handle alone: torch.cuda.current_stream() builds a Stream object around it on every call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def raw():
@@ -226,9 +227,8 @@ def select(p: Params, q, k, q4, k4, q_scale, k_scale, tau: torch.Tensor, want_st
     if want_stats:
         m = torch.empty(p.batch, p.n_q_heads, p.seq_len, dtype=torch.float32, device=dev)
         l = torch.empty_like(m)
-    need = workspace_bytes(p, WS_SELECT)
     if ws is None:
-        ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+        ws = torch.empty(max(1, workspace_bytes(p, WS_SELECT)), dtype=torch.uint8, device=dev)
     nq, nk = _qkv_numel(p)
     est16 = bool(p.flags & FLAG_SELECT_16BIT)          # the 16-bit estimate does not read the codes
     _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads)
@@ -242,7 +242,7 @@ def select(p: Params, q, k, q4, k4, q_scale, k_scale, tau: torch.Tensor, want_st
     _expect("row_counts", counts, torch.int32, p.batch * p.n_q_heads * p.n_q)
     _check(_lib.sale_select(ctypes.byref(p.c(q, k)), _ptr(q), _ptr(k), _ptr(q4), _ptr(k4), _ptr(q_scale), _ptr(k_scale),
                             _ptr(tau), tau.numel(), _ptr(mask), _ptr(counts), _ptr(m), _ptr(l),
-                            _ptr(ws), _expect_ws(ws, need), _stream()))
+                            _ptr(ws), _expect_ws(ws), _stream()))
     return mask, counts, m, l
 
 
@@ -279,7 +279,7 @@ def sparse_attn(p: Params, q, k, v, block_mask, row_counts=None, want_lse: bool 
     _expect("block_mask", block_mask, (torch.int64, torch.uint64), p.batch * p.n_q_heads * p.n_q * p.words)
     _expect("row_counts", row_counts, torch.int32, p.batch * p.n_q_heads * p.n_q, optional=True)
     _check(_lib.sale_sparse_attn(ctypes.byref(p.c(q, k, v, o)), _ptr(q), _ptr(k), _ptr(v), _ptr(block_mask), _ptr(row_counts),
-                                 _ptr(o), _ptr(lse), _ptr(ws), _expect_ws(ws, workspace_bytes(p, WS_SPARSE_ATTN)), _stream()))
+                                 _ptr(o), _ptr(lse), _ptr(ws), _expect_ws(ws), _stream()))
     return o, lse
 
 
@@ -293,7 +293,7 @@ def dense_attn(p: Params, q, k, v, want_lse: bool = False, out=None, ws=None):
     _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads); _expect_bhnd("v", v, p, p.n_kv_heads)
     _expect_bhnd("o", o, p, p.n_q_heads)
     _check(_lib.sale_dense_attn(ctypes.byref(p.c(q, k, v, o)), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                _ptr(ws), _expect_ws(ws, workspace_bytes(p, WS_DENSE_ATTN)), _stream()))
+                                _ptr(ws), _expect_ws(ws), _stream()))
     return o, lse
 
 
@@ -332,7 +332,7 @@ def attn_fp8_operands(p: Params, v):
     v8 = torch.empty(p.batch, p.n_kv_heads, p.seq_len, p.head_dim, dtype=torch.uint8, device=dev)
     vs = torch.empty(p.batch, p.n_kv_heads, p.head_dim, dtype=torch.float32, device=dev)
     ws = torch.empty(max(1, workspace_bytes(p, WS_FP8_OPERANDS)), dtype=torch.uint8, device=dev)
-    _check(_lib.sale_attn_fp8_operands(ctypes.byref(p.c(v=v)), _ptr(v), _ptr(v8), _ptr(vs), _ptr(ws), _expect_ws(ws, 0),
+    _check(_lib.sale_attn_fp8_operands(ctypes.byref(p.c(v=v)), _ptr(v), _ptr(v8), _ptr(vs), _ptr(ws), _expect_ws(ws),
                                        _stream()))
     return v8, vs
 
@@ -348,6 +348,6 @@ def calibrate_tau(p: Params, q, k, v, tau0: float = 0.008, theta: float = 0.4, m
     if ws is None:
         ws = torch.empty(max(1, workspace_bytes(p, WS_CALIBRATE)), dtype=torch.uint8, device=dev)
     _check(_lib.sale_calibrate_tau(ctypes.byref(p.c(q, k, v)), _ptr(q), _ptr(k), _ptr(v), tau0, theta, max_halvings,
-                                   _ptr(tau), _ptr(err), _ptr(halv), _ptr(ws), _expect_ws(ws, workspace_bytes(p, WS_CALIBRATE)),
+                                   _ptr(tau), _ptr(err), _ptr(halv), _ptr(ws), _expect_ws(ws),
                                    _stream()))
     return tau, err, halv
