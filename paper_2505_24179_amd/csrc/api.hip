@@ -47,6 +47,13 @@ int validate_common(const sale_params_t* p, GeomClass cls) {
   return SALE_OK;
 }
 
+int longest_sequence(const sale_params_t* p) {
+  if (p->n_seqs <= 0) return p->seq_len;
+  int longest = 0;
+  for (int s = 0; s < p->n_seqs; ++s) longest = max(longest, p->cu_seqlens[s + 1] - p->cu_seqlens[s]);
+  return longest;
+}
+
 Geo make_geo(const sale_params_t* p) {
   Geo g;
   g.n_qh = p->batch * p->n_q_heads;
@@ -57,12 +64,7 @@ Geo make_geo(const sale_params_t* p) {
   g.n_qb = p->seq_len / kBlockQ;
   g.bk = p->block_k;
   g.n_kb = p->seq_len / p->block_k;
-  int longest = p->seq_len;
-  if (p->n_seqs > 0) {
-    longest = 0;
-    for (int s = 0; s < p->n_seqs; ++s) longest = max(longest, p->cu_seqlens[s + 1] - p->cu_seqlens[s]);
-  }
-  g.words = (longest / p->block_k + 63) / 64;
+  g.words = (longest_sequence(p) / p->block_k + 63) / 64;
   g.seq_start = nullptr;
   g.sink_blocks = p->sink_blocks;
   g.local_blocks = p->local_blocks;

@@ -39,6 +39,7 @@
 //   window launches (details at launch_sparse_rows and balance_kernel).
 #include <type_traits>
 
+#include "row_split.h"
 #include "sale_common.h"
 
 namespace sale {
@@ -1010,26 +1011,13 @@ bool use_windows(const Geo& g, const int32_t* row_counts, int n_slots) {
   return row_counts && g.words > kWindowMinWords * (g.bk == 32 ? 2 : 1) && n_slots > 0;
 }
 
-// Whether a call of `rows` 64-row blocks without window launches runs with two waves per row (NT = 1).  Up to about one
-// row per SIMD (1024) the longest row is the call, and half a row per wave shortens it; with many rows the operand loads,
-// twice as many per FLOP, cost more than that gives.  One wave -> two waves per row, us:
-//   sparse bf16:  256 rows 22.2 -> 20.8, 1024 (2K x 32 heads) 64.5 -> 54.0, 1024 (16K x 4) 342 -> 223, 1308 (7K x 12)
-//                 175.7 -> 122.3, 1536 (3K x 32) 93.9 -> 90.5, 2080 (4K x 32) 136.0 -> 139.5, 8192 (16K x 32) 808 -> 973
-//   32-key blocks (fewer registers: two waves share a SIMD): 1536 96.8 -> 72.4, 2080 134.4 -> 112.0
-//   sparse FP8:   1024 84.3 -> 75.1, 1280 97.9 -> 97.7, 1536 111.9 -> 118.3
-//   dense bf16:   512 39.8 -> 27.4, 1024 66.4 -> 53.1, 1280 84.5 -> 80.4, 1536 97.6 -> 104.5
-//   dense FP8:    1024 87.5 -> 76.7, 1280 104.3 -> 107.1
-bool halves_of(long rows, bool dense, bool bk32, bool pv8) {
-  return rows <= (dense ? (pv8 ? 1024 : 1280) : bk32 ? 2080 : pv8 ? 1280 : 1536);
-}
-
 template <bool QK8, bool PV8>
 int launch_dense_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, uint16_t* o, float* o32,
-                      float* lse, hipStream_t st) {
+                      float* lse, bool halves, hipStream_t st) {
   const int units = g.n_qb * g.group;
   const RowFilter all = {nullptr, -1, 0, -1, 0, 0};
 #define SALE_DENSE_ARGS g, q, kp, vp, q8o, nullptr, nullptr, nullptr, o, o32, lse, all, nullptr, nullptr
-  if (halves_of((long)units * g.n_kvh, true, false, PV8))
+  if (halves)
     attn_rows_kernel<1, false, QK8, PV8, 1><<<dim3((unsigned)(units * g.n_kvh)), dim3(128), 0, st>>>(SALE_DENSE_ARGS);
   else
     attn_rows_kernel<4, false, QK8, PV8><<<dim3((unsigned)(((units + 3) / 4) * g.n_kvh)), dim3(256), 0, st>>>(SALE_DENSE_ARGS);
@@ -1041,18 +1029,17 @@ template <bool BK32, bool QK8, bool PV8 = false>
 int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, const uint64_t* mask,
                        const int32_t* row_counts, int32_t* order, int32_t* assign, LaneLoad* load, int32_t* slot_of,
                        int* slot_counter, int n_slots, uint16_t* o, float* o32, float* lse, f32x4* st_o, float* st_ml,
-                       hipStream_t st) {
+                       bool windows, bool halves, hipStream_t st) {
   const int units = g.n_qb * g.group;
   const int f = BK32 ? 2 : 1;          // mask bits per 64 keys
   const dim3 grid((unsigned)(units * g.n_kvh));
   const RowFilter all = {nullptr, -1, 0, -1, 0, 0};
-  const bool windows = use_windows(g, row_counts, n_slots);
   if (windows) {      // (otherwise the rows were sorted beside the copies)
     order_units_kernel<<<dim3((unsigned)g.n_kvh), dim3(1024), 0, st>>>(g, row_counts, order, slot_of, kLongRow * f, n_slots,
                                                                        slot_counter);
     if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   }
-  if (!windows && halves_of((long)units * g.n_kvh, false, BK32, PV8)) {
+  if (halves) {
     attn_rows_kernel<1, BK32, QK8, PV8, 1><<<grid, dim3(128), 0, st>>>(g, q, kp, vp, q8o, mask, row_counts ? order : nullptr, nullptr,
                                                                        o, o32, lse, all, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
@@ -1157,6 +1144,8 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const bool qk8 = (p->flags & SALE_FLAG_ATTN_INT8_QK) != 0;
   const bool pv8 = (p->flags & SALE_FLAG_ATTN_FP8_PV) != 0;      // (validated: only with qk8 and 64-key blocks)
   const bool windows = mask && use_windows(g, row_counts, n_slots);
+  const bool halves = !windows && two_waves_per_row((long)n_units, longest_sequence(p) / kBlockQ, g.n_kvh, g.group, !mask,
+                                                    mask && g.bk == 32, qk8, pv8);
   const OrderJob job = {mask && row_counts && !windows ? g.n_kvh : 0, row_counts, order};
   const dim3 kv_tiles((unsigned)(job.heads + g.n_kvh * (g.seq / 64)));
 #define SALE_REARRANGE_ARGS g, job, (const uint16_t*)k, (const uint16_t*)v, kp, vp, w.slot_counter
@@ -1183,15 +1172,15 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const bf16x8 *kpp = (const bf16x8*)kp, *vpp = (const bf16x8*)vp;
   if (mask) {
 #define SALE_SPARSE_ARGS g, qq, kpp, vpp, q8o, mask, row_counts, order, assign, w.load, w.slot_of, w.slot_counter, n_slots, \
-                         (uint16_t*)o, o32, lse, st_o, st_ml, st
+                         (uint16_t*)o, o32, lse, st_o, st_ml, windows, halves, st
     if (g.bk == 32) return qk8 ? launch_sparse_rows<true, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<true, false>(SALE_SPARSE_ARGS);
     if (pv8) return launch_sparse_rows<false, true, true>(SALE_SPARSE_ARGS);
     return qk8 ? launch_sparse_rows<false, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<false, false>(SALE_SPARSE_ARGS);
 #undef SALE_SPARSE_ARGS
   }
-  if (pv8) return launch_dense_rows<true, true>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st);
-  return qk8 ? launch_dense_rows<true, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st)
-             : launch_dense_rows<false, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, st);
+  if (pv8) return launch_dense_rows<true, true>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st);
+  return qk8 ? launch_dense_rows<true, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st)
+             : launch_dense_rows<false, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st);
 }
 
 }  // namespace sale

@@ -152,6 +152,7 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
 size_t attn_fixed_bytes(const sale_params_t* p, bool sparse);
 constexpr size_t kParkedRowBytes = 2048 * 16 + 256 * 4;      // fp32 O^T accumulators + running max / sum of one row block
 Geo make_geo(const sale_params_t* p);
+int longest_sequence(const sale_params_t* p);      // tokens
 // Variable-length batches: bytes of the per-block sequence table at the end of a workspace (0 without one), and
 // the kernel launches that fill it from the host offsets.
 size_t seq_table_bytes(const sale_params_t* p);

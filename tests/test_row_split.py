@@ -1,0 +1,62 @@
+"""The rule that says which attention calls run with two waves per row, against measurements: each point below is a call
+whose two forms were timed and differ by 4 % or more, and the rule has to take the faster one (compiled here: the rule is
+plain C++ on host values)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    out = tmp_path_factory.mktemp("row_split")
+    src, lib = out / "rule.cpp", out / "librule.so"
+    src.write_text('#include "row_split.h"\n'
+                   'extern "C" int rule(long rows, int longest, int kv_heads, int group, int dense, int bk32, int int8, int fp8) {\n'
+                   '  return sale::two_waves_per_row(rows, longest, kv_heads, group, dense, bk32, int8, fp8);\n}\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2505_24179_amd", "csrc"), str(src),
+                    "-o", str(lib)], check=True)
+    fn = ctypes.CDLL(str(lib)).rule
+    fn.argtypes = [ctypes.c_long] + [ctypes.c_int] * 7
+    return fn
+
+
+# (kind, 64-key blocks of the longest row, rows, KV heads, query heads per KV head): us with one wave per row, with two
+MEASURED = [
+    # short rows, more of them than places for their halves
+    ("dense", 1, 576, 64, 9, 12.2, 13.5), ("dense", 1, 660, 20, 33, 12.6, 14.0), ("sparse", 1, 768, 192, 4, 14.8, 16.7),
+    ("dense", 4, 1280, 80, 4, 27.1, 29.2), ("dense", 8, 1280, 40, 4, 31.6, 34.6), ("sparse", 8, 1280, 160, 1, 40.3, 42.0),
+    ("sparse32", 16, 2048, 32, 4, 50.8, 53.3), ("fp8", 8, 1024, 32, 4, 49.6, 51.7), ("fp8", 16, 1536, 24, 4, 66.5, 72.4),
+    # few rows, or long ones
+    ("dense", 1, 512, 128, 4, 13.3, 11.3), ("sparse", 4, 512, 32, 4, 18.0, 14.9), ("dense", 16, 512, 8, 4, 38.7, 26.5),
+    ("sparse", 16, 1024, 16, 4, 41.3, 34.1), ("sparse", 64, 1536, 6, 4, 115.2, 98.1), ("sparse32", 64, 2048, 8, 4, 115.5, 98.7),
+    ("sparse32", 32, 1792, 14, 4, 76.0, 69.2), ("fp8", 128, 1280, 5, 2, 211.7, 166.7), ("dense", 32, 1152, 4, 9, 66.8, 61.2),
+    ("dense", 16, 1024, 16, 4, 43.1, 35.3), ("fp8 dense", 64, 1024, 4, 4, 127.3, 108.9), ("sparse", 109, 1308, 4, 3, 175.7, 122.3),
+    # more rows than that
+    ("sparse", 32, 2048, 16, 4, 77.9, 88.0), ("dense", 64, 1536, 6, 4, 126.6, 137.7), ("fp8 dense", 128, 1280, 5, 2, 215.5, 225.7),
+    # many KV heads on every XCD
+    ("dense", 16, 1008, 63, 1, 48.9, 57.9), ("dense", 16, 1008, 21, 3, 46.3, 41.3), ("dense", 64, 1216, 19, 1, 127.9, 151.1),
+    ("int8 dense", 64, 1152, 18, 1, 136.8, 120.9), ("sparse32", 60, 1920, 8, 4, 122.9, 98.1), ("dense", 1, 580, 580, 1, 26.6, 20.2),
+    ("dense", 64, 960, 15, 1, 119.7, 107.7), ("dense", 256, 1280, 5, 1, 437.4, 499.4), ("dense", 256, 1280, 1, 5, 423.1, 405.9),
+]
+
+
+@pytest.mark.parametrize("kind,longest,rows,kv_heads,group,one,two", MEASURED)
+def test_rule_takes_the_faster_form(rule, kind, longest, rows, kv_heads, group, one, two):
+    assert abs(one - two) >= 0.04 * min(one, two)
+    got = rule(rows, longest, kv_heads, group, "dense" in kind, kind == "sparse32", "fp8" in kind or "int8" in kind, "fp8" in kind)
+    assert bool(got) == (two < one)
+
+
+def test_few_rows_always_and_many_never(rule):
+    """Up to 512 rows every half row has a place of its own; beyond the limits the form was measured with it is not used."""
+    for dense, bk32, int8, fp8, most in ((0, 0, 0, 0, 1536), (0, 0, 1, 0, 1536), (0, 1, 0, 0, 2080), (0, 1, 1, 0, 2080),
+                                         (0, 0, 1, 1, 1280), (1, 0, 0, 0, 1280), (1, 0, 1, 0, 1280), (1, 0, 1, 1, 1280)):
+        for kv_heads, group in ((1, 1), (8, 4), (63, 1), (5, 2), (512, 1)):
+            for longest in (1, 2, 3, 4, 7, 8, 16, 31, 64, 100, 4096):
+                on = [rule(rows, longest, kv_heads, group, dense, bk32, int8, fp8) for rows in range(1, 2200)]
+                limit = sum(on)
+                assert 512 <= limit <= most and all(on[:limit])
