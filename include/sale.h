@@ -265,7 +265,10 @@ int sale_sparse_attn(const sale_params_t* p, const void* q, const void* k, const
 /*
  * Dense causal attention (Eq. 1 with M = M_c): the same kernel with every
  * causally visible block kept.  The denominator of every reported speed-up.
- *   ws : workspace of sale_workspace_bytes(p, SALE_WS_DENSE_ATTN) bytes
+ *   ws : workspace of sale_workspace_bytes(p, SALE_WS_DENSE_ATTN) bytes.  With packed
+ *        sequences the last 4 * n_q_heads * (seq_len / 64) of them hold the order of
+ *        the rows; a workspace without them is accepted (same results, some calls
+ *        slower)
  */
 int sale_dense_attn(const sale_params_t* p, const void* q, const void* k, const void* v,
                     void* o, float* lse, void* ws, size_t ws_bytes, void* stream);

@@ -144,8 +144,8 @@ extern "C" size_t sale_workspace_bytes(const sale_params_t* p, int which_call) {
       return attn_fixed_bytes(p, true) + (rows / kBlockQ) * kParkedRowBytes;
     case SALE_WS_SPARSE_ATTN_MIN:      // the same without parking slots
       return attn_fixed_bytes(p, true);
-    case SALE_WS_DENSE_ATTN:           // K', V' (+ the 8-bit operand copies)
-      return attn_fixed_bytes(p, false);
+    case SALE_WS_DENSE_ATTN:           // K', V' (+ the 8-bit operand copies; packed sequences: + the order of the rows)
+      return attn_fixed_bytes(p, false) + dense_order_bytes(p);
     case SALE_WS_CALIBRATE:
       return calibrate_workspace_bytes(p);
     case SALE_WS_INT8_OPERANDS:

@@ -44,8 +44,8 @@
 
 namespace sale {
 
-// Counting sort of the units of each KV head by kept-block count, descending:
-// order[kvh][rank] = unit id (block * group + head-in-group).  One workgroup per KV head.
+// Counting sort of the units of each KV head by kept-block count (without row_counts: by the length of the row),
+// descending: order[kvh][rank] = unit id (block * group + head-in-group).  One workgroup per KV head.
 // slot_of (optional): rows keeping more than long_count blocks draw a parking slot from *slot_counter (cleared by
 // the K' / V' copy that precedes this kernel) as long as there are slots; every other row gets -1.
 constexpr int kOrderBins = kMaskWordsMax * 64 + 2;
@@ -58,14 +58,20 @@ __device__ __forceinline__ void order_units(const Geo& g, int kvh, int* bin, con
   for (int b = threadIdx.x; b < nbins; b += blockDim.x) bin[b] = 0;
   __syncthreads();
   auto count_of = [&](int id) {
-    const int c = row_counts[(size_t)(kvh * g.group + id % g.group) * g.n_qb + id / g.group];
+    const int i = id / g.group;
+    const int c = row_counts ? row_counts[(size_t)(kvh * g.group + id % g.group) * g.n_qb + i] : seq_pos(g, i).il + 1;
     return min(max(c, 0), max_count);
   };
   for (int id = threadIdx.x; id < units; id += blockDim.x) atomicAdd(&bin[count_of(id)], 1);
   __syncthreads();
-  if (threadIdx.x == 0) {          // start offset of every bin, largest count first
-    int run = 0;
-    for (int b = nbins - 1; b >= 0; --b) { const int n = bin[b]; bin[b] = run; run += n; }
+  if (threadIdx.x < 64) {          // start offset of every bin, largest count first: lane l has a 64th of the bins
+    const int per = (nbins + 63) / 64, hi = nbins - 1 - (int)threadIdx.x * per, lo = max(hi - per + 1, 0);
+    int sum = 0;
+    for (int b = hi; b >= lo; --b) sum += bin[b];
+    int run = sum;
+    for (int d = 1; d < 64; d *= 2) { const int o = __shfl_up(run, d, 64); if ((int)threadIdx.x >= d) run += o; }
+    run -= sum;
+    for (int b = hi; b >= lo; --b) { const int n = bin[b]; bin[b] = run; run += n; }
   }
   __syncthreads();
   for (int id = threadIdx.x; id < units; id += blockDim.x) {
@@ -94,7 +100,7 @@ __global__ __launch_bounds__(1024) void order_units_kernel(Geo g, const int32_t*
 // (attention call: one head of 2K tokens 21.2 -> 18.9 us, 4K x 32 heads 136.3 -> 134.0, 16K 820 -> 815).
 struct OrderJob {
   int heads;                      // 0: nothing to sort
-  const int32_t* row_counts;
+  const int32_t* row_counts;      // nullptr: rows by their length
   int32_t* order;
 };
 
@@ -1012,11 +1018,11 @@ bool use_windows(const Geo& g, const int32_t* row_counts, int n_slots) {
 }
 
 template <bool QK8, bool PV8>
-int launch_dense_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, uint16_t* o, float* o32,
-                      float* lse, bool halves, hipStream_t st) {
+int launch_dense_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, const int32_t* order,
+                      uint16_t* o, float* o32, float* lse, bool halves, hipStream_t st) {
   const int units = g.n_qb * g.group;
   const RowFilter all = {nullptr, -1, 0, -1, 0, 0};
-#define SALE_DENSE_ARGS g, q, kp, vp, q8o, nullptr, nullptr, nullptr, o, o32, lse, all, nullptr, nullptr
+#define SALE_DENSE_ARGS g, q, kp, vp, q8o, nullptr, order, nullptr, o, o32, lse, all, nullptr, nullptr
   if (halves)
     attn_rows_kernel<1, false, QK8, PV8, 1><<<dim3((unsigned)(units * g.n_kvh)), dim3(128), 0, st>>>(SALE_DENSE_ARGS);
   else
@@ -1027,7 +1033,7 @@ int launch_dense_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const b
 
 template <bool BK32, bool QK8, bool PV8 = false>
 int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, const uint64_t* mask,
-                       const int32_t* row_counts, int32_t* order, int32_t* assign, LaneLoad* load, int32_t* slot_of,
+                       const int32_t* row_counts, int32_t* order /* nullptr: as they come */, int32_t* assign, LaneLoad* load, int32_t* slot_of,
                        int* slot_counter, int n_slots, uint16_t* o, float* o32, float* lse, f32x4* st_o, float* st_ml,
                        bool windows, bool halves, hipStream_t st) {
   const int units = g.n_qb * g.group;
@@ -1040,14 +1046,14 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
     if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   }
   if (halves) {
-    attn_rows_kernel<1, BK32, QK8, PV8, 1><<<grid, dim3(128), 0, st>>>(g, q, kp, vp, q8o, mask, row_counts ? order : nullptr, nullptr,
+    attn_rows_kernel<1, BK32, QK8, PV8, 1><<<grid, dim3(128), 0, st>>>(g, q, kp, vp, q8o, mask, order, nullptr,
                                                                        o, o32, lse, all, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
   if (!windows) {
     // (one sweep per row: every row reads K', V' of the whole sequence, and moving rows to another XCD costs
     // more L2 misses than the balance gains: 3.1 against 2.7 ms at 32K)
-    attn_rows_kernel<1, BK32, QK8, PV8><<<grid, dim3(64), 0, st>>>(g, q, kp, vp, q8o, mask, row_counts ? order : nullptr, nullptr,
+    attn_rows_kernel<1, BK32, QK8, PV8><<<grid, dim3(64), 0, st>>>(g, q, kp, vp, q8o, mask, order, nullptr,
                                                              o, o32, lse, all, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
@@ -1084,7 +1090,8 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
 
 // Workspace of the attention calls.  Fixed part: K' | V' | (sparse: unit order | parking slot per row block | balanced
 // issue tables, room for 32 window launches | per-window head loads | slot counter) | 8-bit operand copies | FP8 copy
-// of V | per-block sequence table; then (sparse) the parking slots, 33 KB each: as many as the caller's workspace holds.
+// of V | per-block sequence table; then (sparse) the parking slots, 33 KB each: as many as the caller's workspace holds,
+// or (dense, packed sequences) the unit order, if it has room for it.
 namespace {
 struct AttnWs {
   u32x4 *kp, *vp;
@@ -1122,6 +1129,31 @@ AttnWs carve_attn_ws(const sale_params_t* p, bool sparse, void* base) {
 
 size_t attn_fixed_bytes(const sale_params_t* p, bool sparse) { return carve_attn_ws(p, sparse, nullptr).fixed_bytes; }
 
+// What the issue of a call's rows goes by.
+namespace {
+struct BatchShape {
+  int longest;             // 64-row blocks of the longest sequence
+  long even_rows;          // rows that make up as much work in sequences of that length
+  bool long_rows_wait;     // issued by position, 512 rows start before those of some sequence of 3/4 of that length or more
+};
+BatchShape batch_shape(const sale_params_t* p) {
+  BatchShape s = {longest_sequence(p) / kBlockQ, (long)p->batch * p->n_q_heads * (p->seq_len / kBlockQ), false};
+  if (p->n_seqs <= 0) return s;
+  long long work = 0;
+  for (int i = p->n_seqs - 1; i >= 0; --i) {
+    const long long n = (p->cu_seqlens[i + 1] - p->cu_seqlens[i]) / kBlockQ;
+    work += n * (n + 1);
+    if (4 * n >= 3 * s.longest) s.long_rows_wait = (long)p->n_q_heads * ((p->seq_len - p->cu_seqlens[i + 1]) / kBlockQ) >= 512;
+  }
+  s.even_rows = (long)(p->n_q_heads * work / (s.longest + 1));
+  return s;
+}
+}  // namespace
+
+size_t dense_order_bytes(const sale_params_t* p) {
+  return p->n_seqs > 0 ? (size_t)p->n_q_heads * (p->seq_len / kBlockQ) * sizeof(int32_t) : 0;
+}
+
 // o: bf16 output, or (o32 != nullptr) fp32 output instead.  mask == nullptr: dense causal attention
 // (independent of b_k).  ws_bytes >= attn_fixed_bytes (checked by the callers); what lies beyond holds parking slots.
 int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const void* v, const uint64_t* mask,
@@ -1140,13 +1172,23 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const int n_slots = (int)(n_slots_z < n_units ? n_slots_z : n_units);
   f32x4* st_o = (f32x4*)w.parked;                               // [slot] 32 KB
   float* st_ml = (float*)(w.parked + (size_t)n_slots * 2048 * 16);      // [slot] 1 KB
-  int32_t *order = w.order, *assign = w.assign;
   const bool qk8 = (p->flags & SALE_FLAG_ATTN_INT8_QK) != 0;
   const bool pv8 = (p->flags & SALE_FLAG_ATTN_FP8_PV) != 0;      // (validated: only with qk8 and 64-key blocks)
   const bool windows = mask && use_windows(g, row_counts, n_slots);
-  const bool halves = !windows && two_waves_per_row((long)n_units, longest_sequence(p) / kBlockQ, g.n_kvh, g.group, !mask,
-                                                    mask && g.bk == 32, qk8, pv8);
-  const OrderJob job = {mask && row_counts && !windows ? g.n_kvh : 0, row_counts, order};
+  const bool counts = mask && row_counts;
+  const BatchShape shape = batch_shape(p);
+  bool halves = !windows && two_waves_per_row({(long)n_units, shape.even_rows, shape.longest, g.n_kvh, g.group, !mask,
+                                               mask && g.bk == 32, qk8, pv8, p->n_seqs > 0 && !counts});
+  // Rows that do not all start at once have to start longest first.  Without counts they are issued from the last block
+  // on: longest first inside one sequence, not over packed ones.  With two waves per row (512 rows start at once) the long
+  // rows of an early sequence then started when most others had run: 64 sequences of 1024 tokens, one head, dense, 64.6 us
+  // (one wave per row 51.1) -> 46.0; where the long rows come early enough the sort is left out (it costs 2 - 3 %).
+  int32_t* const order_at = mask ? w.order : ws_bytes - w.fixed_bytes >= dense_order_bytes(p) ? (int32_t*)w.parked : nullptr;
+  const bool by_length = halves && !counts && shape.long_rows_wait;
+  if (by_length && !order_at) halves = false;      // (a dense workspace without the order's bytes)
+  const bool sort = !windows && (counts || (by_length && halves));
+  const OrderJob job = {sort ? g.n_kvh : 0, mask ? row_counts : nullptr, order_at};
+  int32_t* const order = sort || windows ? order_at : nullptr;
   const dim3 kv_tiles((unsigned)(job.heads + g.n_kvh * (g.seq / 64)));
 #define SALE_REARRANGE_ARGS g, job, (const uint16_t*)k, (const uint16_t*)v, kp, vp, w.slot_counter
   if (!qk8) rearrange_kv_kernel<true, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
@@ -1171,16 +1213,16 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const uint16_t* qq = (const uint16_t*)q;
   const bf16x8 *kpp = (const bf16x8*)kp, *vpp = (const bf16x8*)vp;
   if (mask) {
-#define SALE_SPARSE_ARGS g, qq, kpp, vpp, q8o, mask, row_counts, order, assign, w.load, w.slot_of, w.slot_counter, n_slots, \
+#define SALE_SPARSE_ARGS g, qq, kpp, vpp, q8o, mask, row_counts, order, w.assign, w.load, w.slot_of, w.slot_counter, n_slots, \
                          (uint16_t*)o, o32, lse, st_o, st_ml, windows, halves, st
     if (g.bk == 32) return qk8 ? launch_sparse_rows<true, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<true, false>(SALE_SPARSE_ARGS);
     if (pv8) return launch_sparse_rows<false, true, true>(SALE_SPARSE_ARGS);
     return qk8 ? launch_sparse_rows<false, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<false, false>(SALE_SPARSE_ARGS);
 #undef SALE_SPARSE_ARGS
   }
-  if (pv8) return launch_dense_rows<true, true>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st);
-  return qk8 ? launch_dense_rows<true, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st)
-             : launch_dense_rows<false, false>(g, qq, kpp, vpp, q8o, (uint16_t*)o, o32, lse, halves, st);
+  if (pv8) return launch_dense_rows<true, true>(g, qq, kpp, vpp, q8o, order, (uint16_t*)o, o32, lse, halves, st);
+  return qk8 ? launch_dense_rows<true, false>(g, qq, kpp, vpp, q8o, order, (uint16_t*)o, o32, lse, halves, st)
+             : launch_dense_rows<false, false>(g, qq, kpp, vpp, q8o, order, (uint16_t*)o, o32, lse, halves, st);
 }
 
 }  // namespace sale
@@ -1204,7 +1246,7 @@ extern "C" int sale_dense_attn(const sale_params_t* p, const void* q, const void
   if (!p || !q || !k || !v || !o) return SALE_ERR_NULL_ARG;
   int rc = validate_common(p, kGeomPath);
   if (rc != SALE_OK) return rc;
-  const size_t need = sale_workspace_bytes(p, SALE_WS_DENSE_ATTN);
+  const size_t need = attn_fixed_bytes(p, false);      // (what SALE_WS_DENSE_ATTN asks for beyond it only makes packed calls faster)
   if (!ws || ws_bytes < need || ((uintptr_t)ws & 15)) return SALE_ERR_WORKSPACE;
   return launch_attn_rows(p, q, k, v, nullptr, nullptr, o, nullptr, lse, ws, ws_bytes, (hipStream_t)stream);
 }

@@ -44,16 +44,34 @@ constexpr RowSplitLimit kRowSplitLimits[] = {
     {8, 960, 1152, 704, 1024, 1024},    {5, 832, 832, 704, 832, 896},       {4, 768, 768, 640, 704, 768},
     {3, 576, 704, 512, 512, 512},       {0, 512, 512, 512, 512, 512}};
 
-// rows: 64-row blocks of all heads and batch entries; longest: 64-key blocks of the longest row (of its sequence: what a mask
-// keeps is not known here, and where every row of a long sequence keeps as few as 13 blocks FP8 loses at 1024 rows, 67.8 ->
-// 74.3 us, and bf16 does not, 48.6 -> 49.5); kv_heads: of all batch entries; group: query heads per KV head; int8, fp8: the 8-bit products.
-inline bool two_waves_per_row(long rows, int longest, int kv_heads, int group, bool dense, bool bk32, bool int8, bool fp8) {
+struct RowSplitCall {
+  long rows;         // 64-row blocks of all heads and batch entries
+  long even_rows;    // rows as long as the longest sequence's that make up as much work: `rows` if all sequences are alike
+  int longest;       // 64-key blocks of the longest row (of its sequence: what a mask keeps is not known here, and where every
+                     // row of a long sequence keeps as few as 13 blocks two waves lose at 640 - 1024 rows: FP8 67.8 -> 74.3 us,
+                     // bf16 48.6 -> 49.5 and 55.5 -> 58.1)
+  int kv_heads;      // of all batch entries
+  int group;         // query heads per KV head
+  bool dense, bk32, int8, fp8;
+  bool by_position;  // packed sequences without row counts: whole rows are issued in the order of the tokens
+};
+
+inline bool two_waves_per_row(const RowSplitCall& c) {
   const RowSplitLimit* l = kRowSplitLimits;
-  while (longest < l->blocks) ++l;
-  int limit = dense ? (fp8 ? l->dense_fp8 : l->dense) : bk32 ? l->sparse32 : fp8 ? l->sparse_fp8 : l->sparse;
+  while (c.longest < l->blocks) ++l;
+  auto limit_of = [&](const RowSplitLimit& r) {
+    return c.dense ? (c.fp8 ? r.dense_fp8 : r.dense) : c.bk32 ? r.sparse32 : c.fp8 ? r.sparse_fp8 : r.sparse;
+  };
+  const int most = limit_of(kRowSplitLimits[0]);
+  int limit = limit_of(*l);
+  if (c.rows > most) return false;
+  // Whole rows issued by position start some of the longest last once there are more of them than places; halves are sorted
+  // (packed, dense: 78 x 1024 tokens, one head 84.3 -> 66.3 us; 3 x 4096, 6 / 2 heads 128 -> 117; 10 x 256, 32 / 8 heads 38.0 ->
+  // 31.7).
+  if (c.by_position && c.rows > 1024 && c.longest >= 4 && (c.longest >= 16 || c.rows <= 1536)) return true;
   // Half or more of the dense kernel's four-row workgroups is padding when a KV head has one or two rows: 64 tokens x 512 /
   // 1024 / 1280 heads 1.3 - 1.4 times as fast with two waves per row, 128 tokens 1.1 - 1.2 times.
-  if (dense && group == 1 && longest <= 2) return rows <= kRowSplitLimits[0].dense;
+  if (c.dense && c.group == 1 && c.longest <= 2) return true;
   // Workgroup b runs on XCD b % 8 and serves KV head b % kv_heads.  Where every XCD reads more KV heads at a time than four,
   // few query heads share them, and a KV head's rows are spread over the XCDs, the operands do not stay in the L2s, and halves,
   // with twice the loads, lose more: dense, 1K x 63 heads 48.9 -> 57.9 us, 4K x 19 heads 128 -> 151, 256 x 191 24.7 -> 27.3
@@ -62,12 +80,13 @@ inline bool two_waves_per_row(long rows, int longest, int kv_heads, int group, b
   // 71.0 -> 74.7 (6K x 15 heads 175 -> 121).  (The 8-bit first product loads half as much for it and does not lose: 1K x 63 67.3 -> 67.7, 33 KV heads
   // of 2K 91.7 -> 87.8.)
   int share = 1;      // gcd(kv_heads, 8): KV head h is served by 8 / share of the XCDs
-  while (share < 8 && kv_heads % (2 * share) == 0) share *= 2;
-  if (!int8 && !bk32 && group < 3 && share < 4 && kv_heads / share > 4) {
-    const int crowded = !dense ? (longest >= 48 ? limit : 1280) : longest >= 32 ? 1024 : share == 2 ? 896 : longest >= 8 ? 768 : 640;
+  while (share < 8 && c.kv_heads % (2 * share) == 0) share *= 2;
+  if (!c.int8 && !c.bk32 && c.group < 3 && share < 4 && c.kv_heads / share > 4) {
+    const int crowded =
+        !c.dense ? (c.longest >= 48 ? limit : 1280) : c.longest >= 32 ? 1024 : share == 2 ? 896 : c.longest >= 8 ? 768 : 640;
     if (crowded < limit) limit = crowded;
   }
-  return rows <= limit;
+  return c.even_rows <= limit;
 }
 
 }  // namespace sale

@@ -150,6 +150,7 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
                      const int32_t* row_counts, void* o, float* o32, float* lse, void* ws, size_t ws_bytes, hipStream_t st);
 // Bytes of an attention workspace without parking slots (sparse) / of the dense kernel's workspace.
 size_t attn_fixed_bytes(const sale_params_t* p, bool sparse);
+size_t dense_order_bytes(const sale_params_t* p);      // order in which a dense call of packed sequences issues its rows
 constexpr size_t kParkedRowBytes = 2048 * 16 + 256 * 4;      // fp32 O^T accumulators + running max / sum of one row block
 Geo make_geo(const sale_params_t* p);
 int longest_sequence(const sale_params_t* p);      // tokens

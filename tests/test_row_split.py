@@ -15,12 +15,14 @@ def rule(tmp_path_factory):
     out = tmp_path_factory.mktemp("row_split")
     src, lib = out / "rule.cpp", out / "librule.so"
     src.write_text('#include "row_split.h"\n'
-                   'extern "C" int rule(long rows, int longest, int kv_heads, int group, int dense, int bk32, int int8, int fp8) {\n'
-                   '  return sale::two_waves_per_row(rows, longest, kv_heads, group, dense, bk32, int8, fp8);\n}\n')
+                   'extern "C" int rule(long rows, long even_rows, int longest, int kv_heads, int group, int dense, int bk32, int int8,\n'
+                   '                    int fp8, int by_position) {\n'
+                   '  return sale::two_waves_per_row({rows, even_rows, longest, kv_heads, group, dense != 0, bk32 != 0, int8 != 0,\n'
+                   '                                  fp8 != 0, by_position != 0});\n}\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2505_24179_amd", "csrc"), str(src),
                     "-o", str(lib)], check=True)
     fn = ctypes.CDLL(str(lib)).rule
-    fn.argtypes = [ctypes.c_long] + [ctypes.c_int] * 7
+    fn.argtypes = [ctypes.c_long] * 2 + [ctypes.c_int] * 8
     return fn
 
 
@@ -47,7 +49,8 @@ MEASURED = [
 @pytest.mark.parametrize("kind,longest,rows,kv_heads,group,one,two", MEASURED)
 def test_rule_takes_the_faster_form(rule, kind, longest, rows, kv_heads, group, one, two):
     assert abs(one - two) >= 0.04 * min(one, two)
-    got = rule(rows, longest, kv_heads, group, "dense" in kind, kind == "sparse32", "fp8" in kind or "int8" in kind, "fp8" in kind)
+    got = rule(rows, rows, longest, kv_heads, group, "dense" in kind, kind == "sparse32", "fp8" in kind or "int8" in kind,
+               "fp8" in kind, False)
     assert bool(got) == (two < one)
 
 
@@ -57,6 +60,6 @@ def test_few_rows_always_and_many_never(rule):
                                          (0, 0, 1, 1, 1280), (1, 0, 0, 0, 1280), (1, 0, 1, 0, 1280), (1, 0, 1, 1, 1280)):
         for kv_heads, group in ((1, 1), (8, 4), (63, 1), (5, 2), (512, 1)):
             for longest in (1, 2, 3, 4, 7, 8, 16, 31, 64, 100, 4096):
-                on = [rule(rows, longest, kv_heads, group, dense, bk32, int8, fp8) for rows in range(1, 2200)]
+                on = [rule(rows, rows, longest, kv_heads, group, dense, bk32, int8, fp8, False) for rows in range(1, 2200)]
                 limit = sum(on)
                 assert 512 <= limit <= most and all(on[:limit])
