@@ -86,6 +86,31 @@ def test_strided_inputs_and_output_equal_the_contiguous_call(sale, layout, flags
         assert hard == 0
 
 
+# 2112 rows: more than any call takes with two waves per row (the case above has 264), so these go through the one-wave
+# kernels, sparse and dense, that layers of real sizes use.
+@pytest.mark.parametrize("layout", ["bnhd", "padded"])
+@pytest.mark.parametrize("flags_name,block_k", [("bf16", 64), ("bf16", 32), ("int8qk", 64), ("int8qk", 32), ("fp8pv", 64)])
+def test_strided_calls_of_many_rows_equal_the_contiguous_call(sale, layout, flags_name, block_k):
+    w = inputs.scaled(inputs.LLAMA_32K, 2112, 4, 2, "strided-2k")
+    q, k, v = inputs.make_inputs(w)
+    B = 16
+    g = torch.Generator().manual_seed(4)
+    scale = (0.8 + 0.4 * torch.rand(B, 1, 1, 1, generator=g)).cuda()
+    qb, kb, vb = ((t[None].cuda().float() * scale).bfloat16() for t in (q, k, v))
+    flags = {"bf16": 0, "int8qk": sale.FLAG_ATTN_INT8_QK, "fp8pv": sale.FLAG_ATTN_INT8_QK | sale.FLAG_ATTN_FP8_PV}[flags_name]
+    p = sale.Params(B, w.n_q_heads, w.n_kv_heads, w.seq_len, block_k=block_k, flags=flags)
+    tau = torch.tensor([w.tau], dtype=torch.float32, device="cuda")
+    ref = _run(sale, p, qb, kb, vb, torch.empty_like(qb), tau)
+    view = _bnhd_view if layout == "bnhd" else _padded_view
+    os_ = view(torch.zeros_like(qb))
+    got = _run(sale, p, view(qb), view(kb), view(vb), os_, tau)
+    for name in ref:
+        assert torch.equal(ref[name], got[name]), name
+    if layout == "padded":      # nothing was written outside the rows of O
+        base = os_._base if os_._base is not None else os_
+        assert torch.isnan(base[:, w.n_q_heads:].float()).all() and torch.isnan(base[:, :, :, w.head_dim:].float()).all()
+
+
 def test_strided_calibration_equals_contiguous(sale):
     w = inputs.scaled(inputs.LLAMA_32K, 1024, 2, 1, "strided-cal")
     q, k, v = inputs.make_inputs(w)
