@@ -20,10 +20,20 @@ def _qkv(tokens, q_heads, kv_heads):
     return w, [t.unsqueeze(0).cuda() for t in inputs.make_inputs(w)]
 
 
-# Key blocks per wave at these batches (64-key blocks, 32 / 8 heads): 65 blocks: 8, 16, 32, 64, whole rows; 198 blocks:
-# 32, 64, 128, whole rows.  6 / 2 heads: one head per wave; 4 / 2: two.
+def _blocks_per_wave(p):
+    """Key blocks of a row that one wave scores (0: the whole row): the cut of the library."""
+    group = p.n_q_heads // p.n_kv_heads
+    heads = 4 if p.block_k == 64 and group % 4 == 0 else 2 if group % 2 == 0 else 1
+    waves, blocks, chunk = p.n_q * (p.n_q_heads // heads) * p.batch, p.words * 64, 8
+    while chunk * 16384 < blocks * waves:
+        chunk *= 2
+    return chunk if chunk < blocks else 0
+
+
+# Every batch takes another cut than the single call (asserted).  In 64-key blocks: 65 blocks, 32 / 8 heads: 8, 16, 32, 64, whole
+# rows; 198 blocks: 32, 64, 128, whole rows.  6 / 2 heads: one head per wave; 4 / 2: two.
 @pytest.mark.parametrize("tokens,q_heads,kv_heads,batches", [(4160, 32, 8, (2, 4, 8, 16)), (12672, 32, 8, (2, 4, 8)),
-                                                             (4160, 6, 2, (2, 11, 22)), (4160, 4, 2, (33, 64)), (64, 4, 1, (3,))])
+                                                             (4160, 6, 2, (4, 11, 22)), (4160, 4, 2, (33, 64)), (64, 4, 1, (2400,))])
 @pytest.mark.parametrize("block_k,segments", [(64, False), (32, True)])
 def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv_heads, batches, block_k, segments):
     w, (q, k, _) = _qkv(tokens, q_heads, kv_heads)
@@ -37,11 +47,12 @@ def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv
         out = (torch.full((n, q_heads, p.n_q, p.words), -1, dtype=torch.int64, device="cuda"),
                torch.full((n, q_heads, p.n_q), -1, dtype=torch.int32, device="cuda"))
         mask, counts, _, _ = sale.select(p, qn, kn, *codes, tau, out=out)
-        return mask, counts
+        return mask, counts, _blocks_per_wave(p)
 
-    mask, counts = choose(1)
+    mask, counts, alone = choose(1)
     for n in batches:
-        mask_n, counts_n = choose(n)
+        mask_n, counts_n, cut = choose(n)
+        assert cut != alone, (n, cut)
         assert torch.equal(mask_n, mask.expand_as(mask_n)) and torch.equal(counts_n, counts.expand_as(counts_n)), n
 
 
@@ -59,12 +70,19 @@ def test_attention_does_not_depend_on_waves_per_row(sale, attn, block_k, tokens,
     p1 = sale.Params(1, q_heads, kv_heads, tokens, block_k=block_k, flags=flags)
     # random masks: odd counts, rows that keep only early blocks
     mask = torch.randint(-2 ** 62, 2 ** 62, (1, q_heads, p1.n_q, p1.words), generator=gen, dtype=torch.int64, device="cuda") | 1
+    bits = (mask[..., None] >> torch.arange(64, device="cuda")) & 1
+    last = (torch.arange(p1.n_q, device="cuda") + 1) * (64 // block_k) - 1      # last visible block of a row
+    counts = (bits.flatten(-2) * (torch.arange(64 * p1.words, device="cuda") <= last[:, None])).sum(-1).to(torch.int32)
 
     def attend(m):
         p = sale.Params(m, q_heads, kv_heads, tokens, block_k=block_k, flags=flags)
         qm, km, vm = (t.expand(m, -1, -1, -1).contiguous() for t in (q, k, v))
-        out = [torch.full_like(qm, float("nan")) for _ in range(2)]
-        o, lse = sale.sparse_attn(p, qm, km, vm, mask.expand(m, -1, -1, -1).contiguous(), want_lse=True, out=out[0])
+        out = [torch.full_like(qm, float("nan")) for _ in range(3)]
+        masks = mask.expand(m, -1, -1, -1).contiguous()
+        o, lse = sale.sparse_attn(p, qm, km, vm, masks, want_lse=True, out=out[0])
+        # with counts the rows are sorted: another order of the same work
+        oc, lsec = sale.sparse_attn(p, qm, km, vm, masks, counts.expand(m, -1, -1).contiguous(), want_lse=True, out=out[2])
+        assert torch.equal(oc, o) and torch.equal(lsec, lse)
         od, lsed = sale.dense_attn(p, qm, km, vm, want_lse=True, out=out[1])
         return o, lse, od, lsed
 
