@@ -4,7 +4,8 @@
 // Design for gfx950
 // -----------------
 // * One wave = one unit (query head, 64-row query block) walking its OWN mask
-//   row.  The masks of the query heads that share a KV head differ block by
+//   row; in calls of few rows the two halves of a unit go to two waves
+//   (row_split.h).  The masks of the query heads that share a KV head differ block by
 //   block, so staging a tile once for several heads only pays when their bits
 //   coincide; instead each wave streams the operands of exactly the blocks its
 //   row keeps straight from global memory into MFMA operand registers: no LDS
@@ -24,10 +25,12 @@
 //   (exactly) whenever no row maximum grew; O accumulates in fp32.  The finished
 //   bf16 tile is transposed through LDS (each wave its own 17 KB, no barrier) so
 //   that it leaves as whole 256-byte rows.
-// * Scheduling.  Dense: a workgroup is the 4 units of one GQA group at the same
-//   query block (they read the same blocks in step, so three of four loads hit
-//   L1), longest rows first, workgroups round-robin over KV heads (blockIdx %
-//   n_kv_heads: one KV head per XCD / L2 when there are 8).
+// * Scheduling.  Few rows, dense and sparse: a workgroup is one unit, its two
+//   waves take 32 queries each.  Otherwise, dense: a workgroup is 4 successive
+//   units of one KV head (with 4 query heads per KV head the same query block:
+//   they read the same blocks in step, so three of four loads hit L1).  Longest
+//   rows first, workgroups round-robin over KV heads (blockIdx % n_kv_heads: one
+//   KV head per XCD / L2 when there are 8).
 //   Sparse: row lengths are heavy-tailed (a query block with one weak row keeps
 //   everything) and differ between heads, so every unit is its own 64-thread
 //   workgroup.  Short sequences: one sweep per row, rows issued by decreasing
@@ -213,11 +216,12 @@ struct Qk8 {
 // bytes and half the MFMA time of that product; see the PV8 section of the kernel.
 constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_half)
 
-//
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
-// and key block, the same operand loads (the second wave of a row hits in L1), about 250 registers, so two waves share
-// a SIMD.  A query's arithmetic is the same in both, bit for bit.
+// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 268 - 352
+// registers (bf16 352, with 32-key blocks 298; int8 328 and 268; FP8 348) against 373 - 440, where two waves would need
+// 256 or less.  So a row gains because its work is on two SIMDs, not because one wave covers the other's latency.  A
+// query's arithmetic is the same in both, bit for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
 __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g, const uint16_t* __restrict__ q,
                                                                const bf16x8* __restrict__ kp,
@@ -1094,7 +1098,7 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
 // or (dense, packed sequences) the unit order, if it has room for it.
 namespace {
 struct AttnWs {
-  u32x4 *kp, *vp;
+  u32x4 *kp, *vp;      // (room for both in every call; the 8-bit first product leaves K', the FP8 second one V' unused)
   int32_t *order, *slot_of, *assign;
   LaneLoad* load;
   int* slot_counter;
@@ -1193,7 +1197,7 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
 #define SALE_REARRANGE_ARGS g, job, (const uint16_t*)k, (const uint16_t*)v, kp, vp, w.slot_counter
   if (!qk8) rearrange_kv_kernel<true, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
   else if (!pv8) rearrange_kv_kernel<false, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
-  else if (w.slot_counter) rearrange_kv_kernel<false, false><<<dim3(job.heads + 1u), dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);      // (clears the counter)
+  else if (w.slot_counter) rearrange_kv_kernel<false, false><<<dim3(job.heads + 1u), dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);      // (the sort, and the counter's clearing)
 #undef SALE_REARRANGE_ARGS
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   Qk8 q8o = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};

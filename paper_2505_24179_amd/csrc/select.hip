@@ -623,8 +623,9 @@ namespace {
 
 // Key blocks of a row that one wave of select_kernel scores (0: the whole row).  With one wave per row a call of few
 // rows is as long as its longest row (4K tokens, 32 / 8 heads: 520 waves for 2048 places, 65 blocks one after the
-// other), and up to 32K the last rows leave places empty.  The rows are cut so that about 2.5 * 16384 / blocks-per-row
-// waves come to work, in powers of two from 8 blocks on (below, the re-encoding of Q~ costs more than the blocks:
+// other), and up to 32K the last rows leave places empty.  The rows are cut so that at most
+// 16384 (row, cut) waves are launched, more than half as many where the limits below do not stop it (about half of them lie
+// above the diagonal and end at once), in powers of two from 8 blocks on (below, the re-encoding of Q~ costs more than the blocks:
 // 4K took 62 us with 4).  Select call, before -> after (the faster re-encoding of Q~ is part of it; without the cut it
 // gave 79.7, 321 and 13100): 4K tokens 85.7 -> 54.8 us, 16K 338 -> 301, 32K 1020 -> 990, 128K (not cut) 13400 -> 13090.
 // With twice as many waves 16K took 314 us, with four times 360; with half as many 304.
@@ -646,8 +647,9 @@ int launch_select(const Geo& g, bool est16, const void* q, const void* k, const 
   const ClearRows clear = {chunk ? row_counts : nullptr, chunk && chunk < 64 ? block_mask : nullptr};
   const long kgroups = est16 ? 0 : (long)g.n_kvh * (g.seq / 32);
   const bool shared = g.group % 4 == 0;      // (then 4 heads of one KV head at one query block share K)
-  // Two waves per row while every row still finds a CU of its own: one head of 2K tokens (32 rows) 20.2 -> 18.2 us a
-  // select call; at 1308 rows it loses (52.7 -> 58.5).  (Where K is shared it changes nothing: 50.8, 50.9 us at 4K.)
+  // Two waves per row while every row still finds a CU of its own.  Select call, us, one wave -> two: 252 rows (2.7K x 6
+  // heads) 20.5 -> 14.5, 256 (8K x 2) 28.6 -> 22.0; beyond, 512 rows (8K x 4) 32.6 -> 31.7, 576 (6K x 6) 30.6 -> 34.5,
+  // 1308 (7K x 12) 52.7 -> 58.5.  (Where K is shared it changes nothing: 50.8, 50.9 us at 4K.)
   const bool halves = !shared && (long)g.n_qb * g.n_qh <= 256;
   const int threads = halves ? 128 : 256;
   const PackFp6 pack = {k4, k6, kgroups, halves ? g.n_qb * g.n_qh : tiles * g.n_kvh};
