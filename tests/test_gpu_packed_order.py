@@ -32,11 +32,17 @@ def test_packed_rows_longest_first_give_the_bits_of_each_sequence_alone(sale, le
     p = sale.Params(1, q_heads, kv_heads, total, block_k=block_k, cu_seqlens=tuple(cu))
     gen = torch.Generator(device="cuda").manual_seed(5)
     mask = torch.randint(-2 ** 62, 2 ** 62, (1, q_heads, p.n_q, p.words), generator=gen, dtype=torch.int64, device="cuda") | 1
+    bits = (mask[..., None] >> torch.arange(64, device="cuda")) & 1
+    starts = torch.repeat_interleave(torch.tensor(cu[:-1]), torch.tensor(lengths) // 64) // 64
+    last = ((torch.arange(p.n_q) - starts + 1) * (64 // block_k) - 1).cuda()      # last visible block of a row
+    counts = (bits.flatten(-2) * (torch.arange(64 * p.words, device="cuda") <= last[:, None])).sum(-1).to(torch.int32)
     full = sale.workspace_bytes(p, sale.WS_DENSE_ATTN)
     order = total // 64 * q_heads * 4
     for size in (full, full - order):      # without the order's bytes the rows are issued as they come, one wave each
         ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         o, lse = sale.sparse_attn(p, q, k, v, mask, want_lse=True, out=torch.full_like(q, float("nan")))
+        oc, lsec = sale.sparse_attn(p, q, k, v, mask, counts, want_lse=True, out=torch.full_like(q, float("nan")))
+        assert torch.equal(oc, o) and torch.equal(lsec, lse)
         od, lsed = sale.dense_attn(p, q, k, v, want_lse=True, out=torch.full_like(q, float("nan")), ws=ws)
         for a, b in zip(cu[:-1], cu[1:]):
             one = sale.Params(1, q_heads, kv_heads, b - a, block_k=block_k)
