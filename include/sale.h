@@ -248,7 +248,8 @@ int sale_select_static(const sale_params_t* p, const void* q, const void* k,
  *   ws            : workspace (2 * sizeof(K) bytes, into which K and V are copied once
  *                   per call in the kernel's operand order - unused for K with
  *                   SALE_FLAG_ATTN_INT8_QK and for V with SALE_FLAG_ATTN_FP8_PV, which
- *                   have operands of their own; tables; then parking slots).  Any ws_bytes >= sale_workspace_bytes(p, SALE_WS_SPARSE_ATTN_MIN)
+ *                   have operands of their own; tables; then parking slots).  Any
+ *                   ws_bytes >= sale_workspace_bytes(p, SALE_WS_SPARSE_ATTN_MIN)
  *                   is accepted.  Above 16K tokens, rows keeping more than 192 x 64 keys
  *                   are swept window by window (so that a window of K, V stays in L2)
  *                   with their accumulators parked in a slot of SALE_PARKED_ROW_BYTES

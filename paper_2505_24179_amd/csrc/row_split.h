@@ -77,8 +77,8 @@ inline bool two_waves_per_row(const RowSplitCall& c) {
   // with twice the loads, lose more: dense, 1K x 63 heads 48.9 -> 57.9 us, 4K x 19 heads 128 -> 151, 256 x 191 24.7 -> 27.3
   // (21 groups of 3, 1K: 46.3 -> 41.3; 1K x 50 heads 46.8 -> 38.9, 62 heads 48.1 -> 46.9), and up to these limits they do
   // not: 2K x 31 74.4 -> 73.4, 4K x 15 120 -> 108, 1K x 43 45.8 -> 40.7.  Sparse: 2.1K x 45 heads 92.9 -> 108, 1.7K x 45
-  // 71.0 -> 74.7 (6K x 15 heads 175 -> 121).  (The 8-bit first product loads half as much for it and does not lose: 1K x 63 67.3 -> 67.7, 33 KV heads
-  // of 2K 91.7 -> 87.8.)
+  // 71.0 -> 74.7 (6K x 15 heads 175 -> 121).  (The 8-bit first product loads half as much for it and does not lose:
+  // 1K x 63 67.3 -> 67.7, 33 KV heads of 2K 91.7 -> 87.8.)
   int share = 1;      // gcd(kv_heads, 8): KV head h is served by 8 / share of the XCDs
   while (share < 8 && c.kv_heads % (2 * share) == 0) share *= 2;
   if (!c.int8 && !c.bk32 && c.group < 3 && share < 4 && c.kv_heads / share > 4) {
