@@ -14,17 +14,21 @@
 //   transposed for free) a pre-pass copies K and V once into "fragment order"
 //   (layouts at rearrange_kv_kernel).
 // * Each wave computes the TRANSPOSED score tile S^T = K Q^T (keys x queries)
-//   with v_mfma_f32_32x32x16_bf16: a lane then owns 16 keys of one query
-//   column, so row max / row sum / rescale factors are per-lane scalars and
-//   the only cross-lane traffic of the online softmax is one exchange with
-//   lane^32.  The accumulator layout of S^T is, register for register, the B
-//   operand layout of the second product O^T = V^T P^T (up to a permutation
-//   of the contraction index that the V copy applies as well), so P never
-//   leaves registers.
-// * Softmax in fp32 with exp2 and the scale folded in; the O rescale is skipped
-//   (exactly) whenever no row maximum grew; O accumulates in fp32.  The finished
-//   bf16 tile is transposed through LDS (each wave its own 17 KB, no barrier) so
-//   that it leaves as whole 256-byte rows.
+//   with v_mfma_f32_16x16x32_bf16: a lane then owns 4 keys of one query column
+//   per tile, and the accumulators of two 16-key tiles are, register for
+//   register, the B operand of the second product O^T = V^T P^T (up to a
+//   permutation of the contraction index that the V copy applies as well), so P
+//   never leaves registers.
+// * The 16x16x32 shape, because the long calls run at the card's power limit (a
+//   step of 64 keys x 64 queries in 2570 cycles, but at 1.5 GHz): contracting 32
+//   instead of 16 deep it reads and writes its accumulators half as often per
+//   FLOP.  Random operands, matrix stream with the softmax's instructions beside
+//   it, per SIMD: 48.2 MFLOP x 32768 / us with 32x32x16, 52.9 with 16x16x32; the
+//   8-bit product alone 54.8 and 64.7.  Dense, 32K x 32 heads: 6.82 -> 6.26 ms.
+// * Softmax in fp32 with exp2 and the scale folded in, against a reference that
+//   a row takes from its first half-tile and keeps (max_of); O accumulates in
+//   fp32.  The finished bf16 tile is transposed through LDS (each wave its own
+//   17 KB, no barrier) so that it leaves as whole 256-byte rows.
 // * Scheduling.  Few rows, dense and sparse: a workgroup is one unit, its two
 //   waves take 32 queries each.  Otherwise, dense: a workgroup is 4 successive
 //   units of one KV head (with 4 query heads per KV head the same query block:
@@ -41,6 +45,7 @@
 //   the lanes of under-loaded ones, and the short rows ride at the tail of the
 //   window launches (details at launch_sparse_rows and balance_kernel).
 #include <type_traits>
+#include <utility>
 
 #include "row_split.h"
 #include "sale_common.h"
@@ -117,9 +122,9 @@ struct OrderJob {
 // barriers, a skipped block costs nothing.  To make those loads full 1 KB
 // coalesced transactions (and to get V transposed for free) a pre-pass copies
 // K and V once into "fragment order":
-//   K' [kv head][block j][mt 0..1][s 0..7][lane 0..63] : 8 channels 16s + 8(lane/32).. of key row 32mt + lane%32
-//   V' [kv head][block j][dt 0..3][s 0..3][lane 0..63] : channel 32dt + lane%32 of the 8 keys
-//                                                        16s + 8(e/4) + 4(lane/32) + e%4,  e = 0..7
+//   K' [kv head][block j][kt 0..3][s 0..3][lane 0..63]   : 8 channels 32s + 8(lane/16).. of key row 16kt + lane%16
+//   V' [kv head][block j][half 0..1][dt 0..7][lane 0..63] : channel 16dt + lane%16 of the 8 keys
+//                                                           32half + 16(e/4) + 4(lane/16) + e%4,  e = 0..7
 // (the key order inside V' is the order in which the S^T accumulator registers
 // hand P^T to the second product).
 // ---------------------------------------------------------------------------
@@ -157,21 +162,21 @@ __global__ __launch_bounds__(256) void rearrange_kv_kernel(Geo g, OrderJob job, 
 #pragma unroll
   for (int r = 0; r < (K ? 4 : 0); ++r) {
     const int oc = tid + 256 * r;
-    const int lane = oc & 63, s = (oc >> 6) & 7, mt = oc >> 9;
-    kp[tile * 1024 + oc] = *(const u32x4*)(kt + (size_t)(32 * mt + (lane & 31)) * lk.st + 16 * s + 8 * (lane >> 5));
+    const int lane = oc & 63, s = (oc >> 6) & 3, kt16 = oc >> 8;
+    kp[tile * 1024 + oc] = *(const u32x4*)(kt + (size_t)(16 * kt16 + (lane & 15)) * lk.st + 32 * s + 8 * (lane >> 4));
   }
   if constexpr (!V) return;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int oc = tid + 256 * r;
-    const int lane = oc & 63, s = (oc >> 6) & 3, dt = oc >> 8;
-    const int d = 32 * dt + (lane & 31), h = lane >> 5;
+    const int lane = oc & 63, dt = (oc >> 6) & 7, half = oc >> 9;
+    const int d = 16 * dt + (lane & 15), grp = lane >> 4;
     uint32_t w[4];
 #pragma unroll
     for (int e2 = 0; e2 < 4; ++e2) {
       const int e = 2 * e2;
-      const int key = 16 * s + 8 * (e >> 2) + 4 * h + (e & 3);
+      const int key = 32 * half + 16 * (e >> 2) + 4 * grp + (e & 3);
       w[e2] = (uint32_t)sv[key * (kHeadDim + 2) + d] | ((uint32_t)sv[(key + 1) * (kHeadDim + 2) + d] << 16);
     }
     u32x4 out;
@@ -216,11 +221,28 @@ struct Qk8 {
 // bytes and half the MFMA time of that product; see the PV8 section of the kernel.
 constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_half)
 
+// The matrix stream of one phase of the pipeline (see the kernel): nq MFMAs of the first product (kind 0) and np of the
+// second (kind 1), taken in turn by groups of four that share an operand, then the row sums (kind 2), which give the last
+// scores time to arrive.
+struct PhaseStep { int kind, n; };
+constexpr PhaseStep phase_step(int i, int nq, int np, int group) {
+  if (i >= nq + np) return {2, i - nq - np};
+  int iq = 0, ip = 0;
+  for (int k = 0;; ++k) {
+    const bool first = iq < nq && ip % group == 0 && (iq % group != 0 || iq * np <= ip * nq);
+    if (k == i) return {first ? 0 : 1, first ? iq : ip};
+    if (first) ++iq; else ++ip;
+  }
+}
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
+
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
-// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 268 - 352
-// registers (bf16 352, with 32-key blocks 298; int8 328 and 268; FP8 348) against 373 - 440, where two waves would need
-// 256 or less.  So a row gains because its work is on two SIMDs, not because one wave covers the other's latency.  A
+// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 276 - 348
+// registers (bf16 316, int8 277, FP8 348) against 374 - 466, where two waves would need 256 or less.  So a row gains because its work is on two SIMDs, not because one wave covers the other's latency.  A
 // query's arithmetic is the same in both, bit for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
 __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g, const uint16_t* __restrict__ q,
@@ -234,9 +256,14 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
                                                                RowFilter flt, f32x4* __restrict__ st_o,
                                                                float* __restrict__ st_ml) {
   static_assert(NT == 2 || WAVES == 1, "the two halves of a row share a workgroup of their own");
-  const int tid = threadIdx.x, wave = NT == 1 ? 0 : tid >> 6, lane = tid & 63;
-  const int q0 = NT == 1 ? (tid >> 6) * 32 : 0;      // first query of this wave inside the row block
-  const int c = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // (wave-uniform by construction: the unit and its addresses are scalars; the FP8 pass spills with it)
+  const int wave_id = PV8 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = NT == 1 ? 0 : wave_id;
+  const int q0 = NT == 1 ? wave_id * 32 : 0;      // first query of this wave inside the row block
+  constexpr int NQ = 2 * NT;                      // 16-query tiles of this wave
+  const int c = lane & 31, h = lane >> 5;         // column and row group of a lane in a 32x32 tile (PV8)
+  const int n16 = lane & 15, g16 = lane >> 4;     // ... in a 16x16 tile
   const int units = g.n_qb * g.group;
   Unit u;
   const bool tail = WAVES == 1 && flt.tail_from >= 0 && (int)blockIdx.x >= flt.tail_from;
@@ -285,27 +312,38 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     resume = nonzero != 0ull;
   }
 
+  constexpr int kRowPad = kHeadDim + 8;      // bf16 elements per LDS row of the staged output
+  __shared__ __attribute__((aligned(16))) uint16_t o_lds[WAVES * 64 * kRowPad];
+
   // ---- operands -----------------------------------------------------------------------
-  // Q fragments (B operand of S^T = K Q^T), resident for the whole row.
-  bf16x8 qf[QK8 ? 1 : NT][QK8 ? 1 : 8];
-  i32x4 qf8[QK8 ? NT : 1][QK8 ? 4 : 1];
+  // Q fragments (B operand of S^T = K Q^T), resident for the whole row: query n16 of tile qt, channels 32 s + 8 g16 ..
+  // (8-bit: 64 s + 16 g16 ..).
+  bf16x8 qf[QK8 ? 1 : NQ][QK8 ? 1 : 4];
+  i32x4 qf8[QK8 ? (PV8 ? NT : NQ) : 1][QK8 ? (PV8 ? 4 : 2) : 1];
+  if constexpr (PV8) {
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if constexpr (QK8) {
+    for (int nt = 0; nt < NT; ++nt) {
       const int8_t* row = q8o.q8 + ((size_t)u.qh * g.seq + u.i * 64 + q0 + 32 * nt + c) * kHeadDim + 16 * h;
 #pragma unroll
       for (int s = 0; s < 4; ++s) qf8[nt][s] = *(const i32x4*)(row + 32 * s);
-    } else {
-      const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 32 * nt + c) + 8 * h;
+    }
+  } else {
 #pragma unroll
-      for (int s = 0; s < 8; ++s) qf[nt][s] = *(const bf16x8*)(row + 16 * s);
+    for (int qt = 0; qt < NQ; ++qt) {
+      if constexpr (QK8) {
+        const int8_t* row = q8o.q8 + ((size_t)u.qh * g.seq + u.i * 64 + q0 + 16 * qt + n16) * kHeadDim + 16 * g16;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) qf8[qt][s] = *(const i32x4*)(row + 64 * s);
+      } else {
+        const uint16_t* row = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 16 * qt + n16) + 8 * g16;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qf[qt][s] = *(const bf16x8*)(row + 32 * s);
+      }
     }
   }
   const float cs = 0.08838834764831845f * 1.4426950408889634f;   // log2(e) / sqrt(d)
   // Logits are handled in log2 units: x = (raw product) * cl[slot], cl = log2(e) / sqrt(d), times the
   // scales of the 8-bit operands of the slot's key block when QK8.
-  float cl[2] = {cs, cs};
-  float ks_pend[2] = {1.0f, 1.0f};      // QK8: K scale of the half-tile whose operands were requested last
   float sq_cs = cs;
   const int first_tile = __builtin_amdgcn_readfirstlane((int)((size_t)u.kvh * g.seq / 64) + (u.i - il));
   const int tiles = __builtin_amdgcn_readfirstlane(il) + 1;      // (64-key tiles up to the diagonal)
@@ -320,60 +358,54 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   // (the sequence's first key tile: u.i - il 64-row blocks into the KV head)
   const __amdgpu_buffer_rsrc_t kt = operand_buffer(kp + (size_t)first_tile * 1024, tiles * 16384);     // 1024 16-byte chunks per 64 keys
   const __amdgpu_buffer_rsrc_t vt = operand_buffer(vp + (size_t)first_tile * 1024, tiles * 16384);
-  // Work proceeds in pairs of 32-key half-tiles held in slots 0 and 1; half-tile hb covers keys
-  // 32hb .. 32hb+31 (half hb % 2 of the 64-key tile hb / 2 of K', V').  K operands of slot mt: kf[mt][s];
-  // V operands of slot mt: vf[mt][dt][s2].
-  bf16x8 kf[QK8 ? 1 : 2][QK8 ? 1 : 8], vf[2][4][2];
-  i32x4 kf8[QK8 ? 2 : 1][QK8 ? 4 : 1];
-  auto load_k = [&](int hb, int mt) __attribute__((always_inline)) {
-    if constexpr (QK8) {
-      const int hu = __builtin_amdgcn_readfirstlane(hb);
+  f32x16 oacc[PV8 ? 4 : 1][PV8 ? NT : 1];      // PV8: O^T in 32x32 tiles
+  f32x4 o16[PV8 ? 1 : 8][PV8 ? 1 : NQ];        // otherwise: O^T in 16x16 tiles, channels 16 dt + 4 g16 .. of query n16 of tile qt
+  float m_run[NQ], l_run[NQ];      // m_run in log2 units (PV8: [nt])
 #pragma unroll
-      for (int s = 0; s < 4; ++s) kf8[mt][s] = load_chunk<i32x4>(k8t, lane16, hu * 4096, s);
-      ks_pend[mt] = ks8[hb >> 1];
-    } else {
-      const int t = __builtin_amdgcn_readfirstlane(hb) * 8192;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) kf[mt][s] = load_chunk<bf16x8>(kt, lane16, t, s);
-    }
-  };
-  auto load_v = [&](int hb, int mt) __attribute__((always_inline)) {
-    const int hu = __builtin_amdgcn_readfirstlane(hb);
-    const int t = (hu >> 1) * 16384 + (hu & 1) * 2048;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) vf[mt][dt][s2] = load_chunk<bf16x8>(vt, lane16, t, dt * 4 + s2);
-  };
-
-  f32x16 oacc[4][NT];
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[dt][nt][r] = 0.0f;
-  float m_run[NT], l_run[NT];      // m_run in log2 units
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) { m_run[nt] = -INFINITY; l_run[nt] = 0.0f; }
-
-  if constexpr (NT == 2) if (resume) {
-    const f32x4* so = st_o + (size_t)slot * 2048 + lane;       // [dt][nt][quarter][lane] 16-byte chunks
+  for (int qt = 0; qt < NQ; ++qt) { m_run[qt] = -INFINITY; l_run[qt] = 0.0f; }
+  if constexpr (PV8) {
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          const f32x4 w = so[((dt * 2 + nt) * 4 + qd) * 64];
+        for (int r = 0; r < 16; ++r) oacc[dt][nt][r] = 0.0f;
+  } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) oacc[dt][nt][4 * qd + e] = w[e];
-        }
-    const float* sml = st_ml + (size_t)slot * 256 + lane;       // [m nt0, m nt1, l nt0, l nt1][lane]
-    m_run[0] = sml[0]; m_run[1] = sml[64]; l_run[0] = sml[128]; l_run[1] = sml[192];
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o16[dt][qt][r] = 0.0f;
+  }
+
+  if constexpr (NT == 2) if (resume) {
+    const f32x4* so = st_o + (size_t)slot * 2048 + lane;       // 32 chunks of [lane] 16 bytes
+    const float* sml = st_ml + (size_t)slot * 256;             // PV8: [m nt0, m nt1, l nt0, l nt1][lane]; otherwise [m, l][query]
+    if constexpr (PV8) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int qd = 0; qd < 4; ++qd) {
+            const f32x4 w = so[((dt * 2 + nt) * 4 + qd) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[dt][nt][4 * qd + e] = w[e];
+          }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) { m_run[nt] = sml[64 * nt + lane]; l_run[nt] = sml[128 + 64 * nt + lane]; }
+    } else {
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) o16[dt][qt] = so[(dt * NQ + qt) * 64];
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt) { m_run[qt] = sml[16 * qt + n16]; l_run[qt] = sml[128 + 16 * qt + n16]; }
+    }
   }
   int wc_it = word_lo;
-  uint64_t cur = row_word(word_lo);
+  uint64_t cur = PV8 ? row_word(word_lo) : 0ull;
   auto next_block = [&]() -> int {
     while (cur == 0) {
       if (++wc_it > word_hi) return -1;
@@ -522,306 +554,383 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) l_run[nt] = 0.5f * lacc[nt][0];
   } else {
-  // ---- pipeline stages ----------------------------------------------------------------
-  // Half-tile score accumulators S[mt][nt] (keys 32mt.. x queries 32nt..) and the bf16 P^T operands
-  // P[mt][nt][s2] made from them.  The MFMA stream and the softmax VALU stream of DIFFERENT half-tiles
-  // are written side by side so that they overlap inside one wave:
-  //   stage A: O += V^T P^T of the previous block's half 1   ||  row max of S[0], rescale test
-  //   stage B: S[1] = K Q^T of this block's half 1            ||  P[0] = exp2(S[0] - max), row sums
-  //   stage C: O += V^T P^T of this block's half 0            ||  row max of S[1], rescale test
-  //   stage D: S[0] = K Q^T of the NEXT block's half 0        ||  P[1] = exp2(S[1] - max), row sums
-  f32x16 S[2][NT];
-  bf16x8 P[2][NT][2];
+  // ---- one sweep over the row's kept half-tiles ----------------------------------------------------------
+  // A software pipeline over half-tiles (32 keys x all queries of the wave), two of them (a pair) per iteration.  Phase t
+  //   S(t + 1) = K(t + 1) Q^T       MFMA
+  //   O += V(t - 1)^T P(t - 1)^T    MFMA, and the row sums of P(t - 1)
+  //   P(t) = exp2(S(t) - reference) VALU
+  //   loads of K(t + 3), V(t + 1) into the registers that the two products have just read
+  // has no branch and no dependency between its three streams, so that they are laid side by side by hand: micro-group i is
+  // one MFMA, its share of the VALU stream and of the loads, closed by a scheduling barrier.  (A wave alone on its SIMD
+  // issues one vector instruction inside the 16 cycles of an MFMA for free, two for 4 cycles more; a phase asks for 1.2.)
+  // Before, a step found every block's row maxima, rescaled O where one had grown and walked its mask bits in vector
+  // registers: 290 vector instructions besides the MFMAs instead of 160, and branches that cut the schedule in pieces.
+  // Attention call, before -> after: dense 32K 7.52 -> 6.26 ms, sparse 16K 904 -> 772 us, 32K 2.51 -> 2.19 ms, 128K 33.0 ->
+  // 29.2, 64K with 32-key blocks 6.52 -> 5.88; int8 at 25K 1.52 -> 1.28 ms.
+  f32x4 S[QK8 ? 1 : 2][2][NQ];      // [slot][16-key tile][query tile]: keys 4 g16 .. of query n16
+  i32x4 A[QK8 ? 2 : 1][2][NQ];      // QK8: the integer accumulators (see qk_mfma)
+  bf16x8 P[2][NQ];                  // keys 4 g16 .. of both 16-key tiles: the B operand of the second product as it is
+  f32x4 lacc;                       // row sums: every register of lane (n16, g16) holds the sum over all keys of query n16 of tile g16
+  bf16x8 kf[QK8 ? 1 : 2][QK8 ? 1 : 8], vf[2][8];      // operands of slot mt: K chunk 4 kt + s, V chunk dt
+  i32x4 kf8[QK8 ? 2 : 1][QK8 ? 4 : 1];                // K chunk 2 kt + s
+  bf16x8 rows_of[NQ];               // A operand of the row sums of tile qt: ones in rows 4 qt .. 4 qt + 3
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) rows_of[qt][e] = (__bf16)(n16 >> 2 == qt ? 1.0f : 0.0f);
+  }
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) asm("" : "+a"(rows_of[qt]));      // (operands that stay go to accumulation registers: the
+  // results of both products and what the vector unit makes take nearly all of the 256 ordinary ones, and a spill in front
+  // of the sweep makes its waits for the operand loads those of the reload)
+  if constexpr (!QK8) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) asm("" : "+a"(qf[qt][ks]));
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) lacc[r] = 0.0f;
+  if (resume) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lacc[r] = g16 == qt ? l_run[qt] : lacc[r];
+  }
+  const i32x4 magic = {0x4B400000, 0x4B400000, 0x4B400000, 0x4B400000};
+  constexpr int kSteps = QK8 ? 2 : 4;                                                   // contraction steps of the first product
+  constexpr int kQk = 2 * kSteps * NQ, kPv = 8 * NQ, kElems = 8 * NQ;                   // MFMAs of the two products and scores per lane of a phase
 
-  auto qk_half = [&](int mt) __attribute__((always_inline)) {                       // S[mt][*] = K(half mt) Q^T
+  // MFMA n of S[y] = K(slot y) Q^T: a K fragment serves all query tiles in a row
+  auto qk_mfma = [&](int y, int n) __attribute__((always_inline)) {
+    const int kt = n / (kSteps * NQ), ks = n / NQ % kSteps, qt = n % NQ;
     if constexpr (QK8) {
       // The integer accumulators start at the bit pattern of kIntOffset = 1.5 * 2^23: an integer x with |x| < 2^22
       // added to it (the sums are below 127 * 127 * 128 < 2^21) gives the bit pattern of the FLOAT kIntOffset + x,
       // so the sums are read as floats without a conversion each; the offset leaves with the scaling FMAs.
-      i32x16 a[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) a[nt][r] = 0x4B400000;
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          a[nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf8[mt][s], qf8[nt][s], a[nt], 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) S[mt][nt][r] = int_bits_as_float(a[nt][r]);
+      A[y][kt][qt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf8[y][kSteps * kt + ks], qf8[qt][ks], ks == 0 ? magic : A[y][kt][qt], 0, 0, 0);
     } else {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[mt][nt][r] = 0.0f;
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          S[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mt][s], qf[nt][s], S[mt][nt], 0, 0, 0);
+      const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+      S[y][kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[y][kSteps * kt + ks], qf[qt][ks], ks == 0 ? z : S[y][kt][qt], 0, 0, 0);
     }
   };
-  auto pv_half = [&](int mt) __attribute__((always_inline)) {                       // O^T += V^T(half mt) P^T(half mt)
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          oacc[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mt][dt][s2], P[mt][nt][s2], oacc[dt][nt], 0, 0, 0);
+  // MFMA n of O^T += V^T(slot y) P^T(slot y)
+  auto pv_mfma = [&](int y, int n) __attribute__((always_inline)) {
+    const int dt = n / NQ, qt = n % NQ;
+    o16[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[y][dt], P[y][qt], o16[dt][qt], 0, 0, 0);
   };
-  // Row maxima of the half-tile in slot mt (after causal masking where `diag` asks for it): mx[nt].
-  // koff[mt]: first key of the slot's half-tile minus the first query row of the block (b_k = 32 only;
-  // with b_k = 64 the masked pair is the diagonal block: 0 and 32).  A huge koff empties the slot.
-  float mx[NT];
-  int koff[2] = {0, 32};
-  auto max_half = [&](int mt, auto diag) __attribute__((always_inline)) {
+  // Row sums of the ROUNDED probabilities, on the matrix unit (v_dot2c_f32_bf16, one per two probabilities, held up the MFMAs
+  // next to it by 18 cycles each).  The query tiles share one accumulator, four rows each.
+  auto sum_mfma = [&](int y, int qt) __attribute__((always_inline)) {
+    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows_of[qt], P[y][qt], lacc, 0, 0, 0);
+  };
+  auto load_k1 = [&](int t, int y, int n) __attribute__((always_inline)) {      // chunk n of a half-tile's K operands
+    if constexpr (QK8) kf8[y][n] = load_chunk<i32x4>(k8t, lane16, t * 4096, n);
+    else kf[y][n] = load_chunk<bf16x8>(kt, lane16, t * 8192, n);
+  };
+  auto load_v1 = [&](int t, int y, int n) __attribute__((always_inline)) { vf[y][n] = load_chunk<bf16x8>(vt, lane16, t * 8192, n); };
+  auto load_k = [&](int hb, int y) __attribute__((always_inline)) {
+    const int t = __builtin_amdgcn_readfirstlane(hb);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      if constexpr (decltype(diag)::value) {
-        const int ko = BK32 ? koff[mt] : 32 * mt;
+    for (int n = 0; n < 2 * kSteps; ++n) load_k1(t, y, n);
+  };
+  auto load_v = [&](int hb, int y) __attribute__((always_inline)) {
+    const int t = __builtin_amdgcn_readfirstlane(hb);
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (ko + mfma32_row(r, lane) > q0 + 32 * nt + c) S[mt][nt][r] = -INFINITY;
-      }
-      float v = fmaxf(S[mt][nt][0], S[mt][nt][1]);
+    for (int n = 0; n < 8; ++n) load_v1(t, y, n);
+  };
+  auto scores = [&](int x, int kt, int qt) __attribute__((always_inline)) -> f32x4 {
+    if constexpr (QK8) return int_bits_as_floats(A[x][kt][qt]); else return S[x][kt][qt];
+  };
+  // keys after the query: koff = first key of the half-tile minus first query row of the block (a huge koff empties it)
+  auto hide = [&](int x, int koff) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 2; r < 16; r += 2) v = fmaxf(fmaxf(v, S[mt][nt][r]), S[mt][nt][r + 1]);
-      if constexpr (QK8) mx[nt] = __builtin_fmaf(max_with_other_half(v), cl[mt], -kIntOffset * cl[mt]);
-      else mx[nt] = max_with_other_half(v) * cl[mt];
+    for (int qt = 0; qt < NQ; ++qt) {
+      const int seen = q0 + 16 * qt + n16 - 4 * g16 - koff;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * kt + r > seen) {
+            if constexpr (QK8) A[x][kt][qt][r] = (int)0xFF800000; else S[x][kt][qt][r] = -INFINITY;
+          }
     }
   };
-  // Lazy rescale: O and l are rescaled only when some row's maximum grew (exact: otherwise the factor
-  // is 1).  Rows of the diagonal block that see no key of a half keep their (finite) maximum.
-  auto rescale = [&]() __attribute__((always_inline)) {
-    if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1]) != 0ull) {
+  // Reference of the exponents, m_run: the row maximum over the first half-tile, and no running maximum after it.  A softmax
+  // is exact for any reference that lets neither the probabilities overflow nor the largest of them vanish: bf16 and fp32 share
+  // their exponent range, so a row may rise 2^100 above its first half-tile.  One that rises further is swept a second time
+  // from its true maximum (below).
+  auto max_of = [&](int x, float ch, float (&mx)[NQ]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const float m_new = fmaxf(m_run[nt], mx[nt]);
-        float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m_new);
-        // b_k = 32: a query row may have seen no key yet (its first half-tile lies above the diagonal)
-        if constexpr (BK32) alpha = m_new == -INFINITY ? 1.0f : alpha;
-        l_run[nt] *= alpha;
-        m_run[nt] = m_new;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[dt][nt][r] *= alpha;
-      }
-    }
-  };
-  // Interleave hint for the instruction scheduler: n times {1 MFMA, `valu` VALU, `vmem` loads}.
-#define SALE_PIPE(n, valu, vmem)                                        \
-  _Pragma("unroll") for (int i_ = 0; i_ < (n); ++i_) {                   \
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   \
-    if ((valu) > 0) __builtin_amdgcn_sched_group_barrier(0x002, (valu), 0); \
-    if ((vmem) > 0) __builtin_amdgcn_sched_group_barrier(0x020, (vmem), 0); \
-  }
-  auto exp_half = [&](int mt) __attribute__((always_inline)) {                      // P[mt] = exp2(S[mt] * cs - m * cs), l += row sums
-    bf16x2 ones;
-    ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const float ch = cl[mt];
-      float mb = (BK32 && m_run[nt] == -INFINITY) ? 0.0f : m_run[nt];
-      if constexpr (QK8) mb += kIntOffset * ch;        // S carries the accumulators' offset
-      float sum = l_run[nt];
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        u32x4 packed;
-#pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-          const int r = 8 * s2 + 2 * e2;
-          bf16x2 pk;
-          pk[0] = (__bf16)__builtin_amdgcn_exp2f(S[mt][nt][r] * ch - mb);
-          pk[1] = (__bf16)__builtin_amdgcn_exp2f(S[mt][nt][r + 1] * ch - mb);
-          sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, sum, false);   // row sum of the rounded P
-          packed[e2] = __builtin_bit_cast(unsigned, pk);
-        }
-        P[mt][nt][s2] = __builtin_bit_cast(bf16x8, packed);
-      }
-      l_run[nt] = sum;
+    for (int qt = 0; qt < NQ; ++qt) {
+      const f32x4 e = scores(x, 0, qt), f = scores(x, 1, qt);
+      float v = fmaxf(fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])), fmaxf(fmaxf(f[0], f[1]), fmaxf(f[2], f[3])));
+      v = fmaxf(v, __shfl_xor(v, 16, 64));
+      v = fmaxf(v, __shfl_xor(v, 32, 64));
+      if constexpr (QK8) mx[qt] = __builtin_fmaf(v, ch, -kIntOffset * ch);
+      else mx[qt] = v * ch;
     }
   };
 
-  // One pair of half-tiles (slot 0: cur.a, slot 1: cur.b).  first: no previous pair whose slot 1 is still
-  // to be multiplied.  last: no next pair (nxt is then unused).  diag: apply the causal mask (and, with
-  // b_k = 32, the emptying of a slot that has no half-tile).
-  // Every load and MFMA of a variant is unconditional, so the compiler can count outstanding loads
-  // exactly and never has to drain the queue.
-  struct Pair { int a, b; };
-  auto block_step = [&](Pair cur, Pair nxt, auto first, auto last, auto diag) __attribute__((always_inline)) {
-    constexpr bool kLast = decltype(last)::value;
-    // stage A
-    if constexpr (!decltype(first)::value) pv_half(1);
-    max_half(0, diag);
-    load_v(cur.b, 1);
-    if constexpr (!decltype(first)::value) { SALE_PIPE(8 * NT, 2, 1) }
-    rescale();
-    // stage B
-    qk_half(1);
-    exp_half(0);
-    // stage C
-    if constexpr (QK8) cl[1] = ks_pend[1] * sq_cs;      // scale of slot 1's key block, requested a step ago
-    pv_half(0);
-    max_half(1, diag);
-    if constexpr (!kLast) { load_k(nxt.b, 1); load_v(nxt.a, 0); }
-    SALE_PIPE(8 * NT, 6, 0)
-    SALE_PIPE(8 * NT, 2, 2 / NT)
-    rescale();
-    // stage D (kf[0] of the next pair was requested before stage A)
-    if constexpr (!kLast) qk_half(0);
-    exp_half(1);
-    if constexpr (!kLast) {
-      if constexpr (QK8) { SALE_PIPE(4 * NT, 14, 0) } else { SALE_PIPE(8 * NT, 6, 0) }      // (the 8-bit first product has half the MFMAs)
+  struct Pair { int a, b; float ka, kb; };      // half-tiles of the two slots; QK8: the K scales of their blocks
+  auto factor = [&](float k_scale) __attribute__((always_inline)) { return QK8 ? k_scale * sq_cs : cs; };      // score -> logit in log2 units
+  // One phase.  x: slot whose probabilities are made; y = 1 - x: slot of the two products and of the loads.
+  auto phase = [&](auto xc, float k_scale, int k_next, int v_next) __attribute__((always_inline)) {
+    constexpr int x = decltype(xc)::value, y = 1 - x;
+    constexpr int groups = kQk + kPv + NQ, slots = (kElems / 2 + 1) * 5;
+    const float ch = factor(k_scale);
+    float mb[NQ], E[kElems];
+    f32x4 F[kElems / 4];
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      mb[qt] = (BK32 && m_run[qt] == -INFINITY) ? 0.0f : m_run[qt];
+      if constexpr (QK8) mb[qt] = __builtin_fmaf(kIntOffset, ch, mb[qt]);      // the accumulators' offset
     }
-    if constexpr (QK8 && !kLast) cl[0] = ks_pend[0] * sq_cs;      // slot 0 now holds the next pair's first half-tile
-  };
-  const auto T = std::true_type{};
-  const auto F = std::false_type{};
-
-  // b_k = 32: an odd number of kept half-tiles leaves one without a partner.  It goes FIRST, next to an
-  // emptied slot 1 (which re-reads the same half-tile), so that every later pair is complete and the
-  // half-tiles of the diagonal block, the largest indices of a row, fall into the last pair.  The first
-  // and the last pair of a sweep take the masked variant.
-  bool lone_first = false;
-  if constexpr (BK32) {
-    const int wcl = word_lo + lane;
-    const int bits = wcl <= word_hi ? __popcll(row_word(wcl)) : 0;
-    lone_first = (__popcll(__builtin_amdgcn_ballot_w64((bits & 1) != 0)) & 1) != 0;
-  }
-  constexpr int kEmptySlot = 1 << 24;
-  auto next_pair = [&](Pair& pr) -> bool {
-    const int a = next_block();
-    if (a < 0) return false;
-    if constexpr (BK32) {
-      pr.a = a;
-      const int b = next_block();
-      pr.b = b < 0 ? a : b;      // (b < 0 cannot happen once the lone half-tile has gone first)
-    } else {
-      pr.a = 2 * a;
-      pr.b = 2 * a + 1;
-    }
-    return true;
-  };
-  auto set_koff = [&](Pair pr, bool empty_b) {
-    if constexpr (BK32) {
-      koff[0] = (pr.a - 2 * il) * 32;
-      koff[1] = empty_b ? kEmptySlot : (pr.b - 2 * il) * 32;
-    }
-  };
-
-  Pair pc = {0, 0}, pn = {0, 0}, pa = {0, 0};
-  bool have;
-  if (BK32 && lone_first) {
-    const int a = next_block();
-    have = a >= 0;
-    pc.a = pc.b = a;
-  } else {
-    have = next_pair(pc);
-  }
-  if (have) {
-    load_k(pc.a, 0);
-    load_k(pc.b, 1);
-    load_v(pc.a, 0);
-    qk_half(0);
-    if constexpr (QK8) cl[0] = ks_pend[0] * sq_cs;
-    bool has_next = next_pair(pn);
-    set_koff(pc, lone_first);
-    if (!has_next) {
-      if (BK32 || pc.a == 2 * il) block_step(pc, pc, T, T, T); else block_step(pc, pc, T, T, F);
-    } else {
-      // the list is read one pair ahead of the loads so that no control flow separates the stages
-      load_k(pn.a, 0);
-      bool has_aft = next_pair(pa);
-      if constexpr (BK32) block_step(pc, pn, T, F, T); else block_step(pc, pn, T, F, F);
-      pc = pn; pn = pa; has_next = has_aft;
-      while (has_next) {
-        load_k(pn.a, 0);
-        has_aft = next_pair(pa);
-        block_step(pc, pn, F, F, F);
-        pc = pn; pn = pa; has_next = has_aft;
+    // The VALU stream, five instructions per two scores (score e: query tile e / 8, 16-key tile e / 4 % 2, register e % 4):
+    // scale e, exp2 e - 1, scale e + 1, exp2 e, pack e - 2 and e - 1
+    auto valu = [&](int n) __attribute__((always_inline)) {
+      const int e0 = 2 * (n / 5), o = n % 5;
+      const int e = o == 0 ? e0 : o == 1 ? e0 - 1 : o == 2 ? e0 + 1 : o == 3 ? e0 : e0 - 2;
+      if (e < 0 || e >= kElems) return;
+      if (o == 0 && e % 4 == 0) F[e / 4] = scores(x, e / 4 % 2, e / 8);
+      if (o == 0 || o == 2) E[e] = __builtin_fmaf(F[e / 4][e % 4], ch, -mb[e / 8]);
+      else if (o == 1 || o == 3) E[e] = __builtin_amdgcn_exp2f(E[e]);
+      else { P[x][e / 8][e % 8] = (__bf16)E[e]; P[x][e / 8][e % 8 + 1] = (__bf16)E[e + 1]; }
+    };
+    static_for<groups>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      constexpr PhaseStep st = phase_step(i, kQk, kPv, NQ);
+      if constexpr (st.kind == 0) {
+        qk_mfma(y, st.n);
+        if constexpr (st.n % NQ == NQ - 1) load_k1(k_next, y, st.n / NQ);
+      } else if constexpr (st.kind == 1) {
+        pv_mfma(y, st.n);
+        if constexpr (st.n % NQ == NQ - 1) load_v1(v_next, y, st.n / NQ);
+      } else {
+        sum_mfma(y, st.n);
       }
-      set_koff(pc, false);
-      if (BK32 || pc.a == 2 * il) block_step(pc, pc, F, T, T); else block_step(pc, pc, F, T, F);
-    }
-    pv_half(1);
-  }
+      constexpr int from = i * slots / groups, to = (i + 1) * slots / groups;
+      static_for<to - from>([&](auto vc) __attribute__((always_inline)) { valu(from + decltype(vc)::value); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  const auto slot0 = std::integral_constant<int, 0>{};
+  const auto slot1 = std::integral_constant<int, 1>{};
 
+  // ---- the row's kept blocks, in ascending order, as a list in LDS (this wave's part of the output staging area) ----
+  // BK32: with an odd number of kept half-tiles the first one comes twice, the first time emptied, so that there are whole
+  // pairs and the half-tiles of the diagonal block, the largest indices of a row, fall into the last one.
+  uint16_t* const list = o_lds + (wave * 64 + q0) * kRowPad;
+  static_assert(32 * NT * kRowPad >= kMaskWordsMax * 64 + 16, "the list of the longest row fits the staging area");
+  constexpr bool kListed = WAVES == 1;          // (the four-row workgroups are the dense kernel's: every block)
+  int n_pairs = 0;
+  bool lone = false;
+  auto build_list = [&](int lo, int hi) {
+    const uint64_t mine = lane >= lo && lane <= hi ? row_word(lane) : 0ull;
+    lone = BK32 && (__popcll(__builtin_amdgcn_ballot_w64((__popcll(mine) & 1) != 0)) & 1) != 0;
+    int n = lone ? 1 : 0, first = -1, last = 0;
+    for (uint64_t any = __builtin_amdgcn_ballot_w64(mine != 0ull); any != 0ull; any &= any - 1) {
+      const int w = __builtin_ctzll(any);
+      const uint64_t word = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, w) |
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), w) << 32;
+      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0));
+      if ((word >> lane) & 1) list[n + before] = (uint16_t)(w * 64 + lane);
+      if (first < 0) first = w * 64 + __builtin_ctzll(word);
+      last = w * 64 + 63 - __builtin_clzll(word);
+      n += __popcll(word);
+    }
+    if (lone && lane == 0) list[0] = (uint16_t)first;
+    if (lane < 8) list[n + lane] = (uint16_t)last;      // (the loads run up to two pairs ahead, the list is read three ahead)
+    n_pairs = BK32 ? n >> 1 : n;
+  };
+  auto entry = [&](int n) __attribute__((always_inline)) -> uint32_t {      // of pair n
+    if constexpr (!kListed) return (uint32_t)min(n, tiles - 1);
+    else if constexpr (BK32) return *(const uint32_t*)(list + 2 * n);
+    else return list[n];
+  };
+  auto pair_of = [&](uint32_t raw) __attribute__((always_inline)) -> Pair {
+    const uint32_t w = kListed ? (uint32_t)__builtin_amdgcn_readfirstlane((int)raw) : raw;
+    Pair p;
+    p.a = BK32 ? (int)(w & 0xFFFFu) : 2 * (int)w;
+    p.b = BK32 ? (int)(w >> 16) : p.a + 1;
+    p.ka = p.kb = 1.0f;
+    if constexpr (QK8) { p.ka = ks8[p.a >> 1]; p.kb = BK32 ? ks8[p.b >> 1] : p.ka; }
+    return p;
+  };
+
+  if constexpr (kListed) build_list(word_lo, word_hi); else n_pairs = tiles;
+  asm("" : "+v"(n_pairs));      // (a vector register on purpose: with scalar loop conditions the register allocator copies O^T between the loop's exits and spills)
+  for (bool again = false; n_pairs > 0; again = true) {
+    Pair c0 = pair_of(entry(0)), c1 = pair_of(entry(1));
+    uint32_t ahead = entry(2);
+    load_k(c0.a, 0);
+    load_k(c0.b, 1);
+    load_v(c0.a, 0);
+#pragma unroll
+    for (int n = 0; n < kQk; ++n) qk_mfma(0, n);
+    load_k(c1.a, 0);
+    if (!resume && !again) {
+      if (n_pairs == 1) hide(0, (c0.a - 2 * il) * 32);
+      max_of(0, factor(c0.ka), m_run);
+    }
+    if (BK32 && lone) hide(0, 1 << 24);
+    // (nothing to multiply by yet: the first phase adds zeros)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vf[1][dt][e] = (__bf16)0.0f;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) P[1][qt][e] = (__bf16)0.0f;
+    for (int n = 1; n < n_pairs; ++n) {
+      const Pair c2 = pair_of(ahead);
+      ahead = entry(n + 2);
+      phase(slot0, c0.ka, c1.b, c0.b);
+      phase(slot1, c0.kb, c2.a, c1.a);
+      c0 = c1; c1 = c2;
+    }
+    // the last pair: the diagonal block, if it is kept (its phases make scores that nobody reads)
+    hide(0, lone && n_pairs == 1 ? 1 << 24 : (c0.a - 2 * il) * 32);
+    phase(slot0, c0.ka, c0.b, c0.b);
+    hide(1, (c0.b - 2 * il) * 32);
+    phase(slot1, c0.kb, c0.b, c0.b);
+#pragma unroll
+    for (int n = 0; n < kPv; ++n) pv_mfma(1, n);
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) sum_mfma(1, n);
+    if (park || again) break;
+    // Did the row stay within reach of its reference?  (O can only have overflowed where the sums are large, or V is beyond
+    // what the sums of probabilities below 1 could stand.)
+    if (__builtin_amdgcn_ballot_w64(!(lacc[0] <= 65536.0f)) == 0ull) break;
+    float odd = !(lacc[0] <= 0x1p100f) ? 1.0f : 0.0f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int qt = 0; qt < NQ; ++qt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) odd = !(__builtin_fabsf(o16[dt][qt][r]) <= 3.0e38f) ? 1.0f : odd;
+    if (__builtin_amdgcn_ballot_w64(odd != 0.0f) == 0ull) break;
+    // It did not: the row's true maximum, over all its windows, and the sweep again from there.
+    if constexpr (kListed) build_list(0, last_word);
+    asm("" : "+v"(n_pairs));
+    resume = false;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      m_run[qt] = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lacc[r] = 0.0f;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o16[dt][qt][r] = 0.0f;
+    }
+    for (int n = 0; n < n_pairs; ++n) {
+      const Pair p = pair_of(entry(n));
+      load_k(p.a, 0);
+      load_k(p.b, 1);
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+#pragma unroll
+        for (int e = 0; e < kQk; ++e) qk_mfma(y, e);
+        hide(y, ((y ? p.b : p.a) - 2 * il) * 32);
+        float mx[NQ];
+        max_of(y, factor(y ? p.kb : p.ka), mx);
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) m_run[qt] = fmaxf(m_run[qt], mx[qt]);
+      }
+    }
+  }
+#pragma unroll
+  for (int qt = 0; qt < NQ; ++qt) l_run[qt] = __shfl(lacc[0], 16 * qt + n16, 64);
   }
 
   if constexpr (NT == 2) if (park) {
     f32x4* so = st_o + (size_t)slot * 2048 + lane;
+    float* sml = st_ml + (size_t)slot * 256;
+    if constexpr (PV8) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          f32x4 w;
+          for (int qd = 0; qd < 4; ++qd) {
+            f32x4 w;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = oacc[dt][nt][4 * qd + e];
-          so[((dt * 2 + nt) * 4 + qd) * 64] = w;
-        }
-    float* sml = st_ml + (size_t)slot * 256 + lane;
-    sml[0] = m_run[0]; sml[64] = m_run[1]; sml[128] = l_run[0]; sml[192] = l_run[1];
+            for (int e = 0; e < 4; ++e) w[e] = oacc[dt][nt][4 * qd + e];
+            so[((dt * 2 + nt) * 4 + qd) * 64] = w;
+          }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) { sml[64 * nt + lane] = m_run[nt]; sml[128 + 64 * nt + lane] = l_run[nt]; }
+    } else {
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) so[(dt * NQ + qt) * 64] = o16[dt][qt];
+      if (g16 == 0) {
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt) { sml[16 * qt + n16] = m_run[qt]; sml[128 + 16 * qt + n16] = l_run[qt]; }
+      }
+    }
     return;
   }
-  // Output.  A lane holds, per (nt, dt, q4), four consecutive channels of one query row: stored from there a
-  // store instruction touches 32 rows, 16 bytes each.  The bf16 tile goes through LDS instead (rows padded by
+  // Output.  A lane holds, per tile, four consecutive channels of one query row: stored from there a
+  // store instruction touches 16 or 32 rows.  The bf16 tile goes through LDS instead (rows padded by
   // four banks) and leaves as whole 256-byte rows, 4 rows per instruction.
-  constexpr int kRowPad = kHeadDim + 8;      // bf16 elements per LDS row
-  __shared__ __attribute__((aligned(16))) uint16_t o_lds[WAVES * 64 * kRowPad];
   uint16_t* const tile = o_lds + (wave * 64 + q0) * kRowPad;
+  // channels ch .. ch + 3 of query r of this wave
+  auto put4 = [&](int r, int ch, f32x4 w) __attribute__((always_inline)) {
+    if (o32) {     // calibration reads the output before it is rounded to bf16
+      *(f32x4*)(o32 + ((size_t)u.qh * g.seq + u.i * 64 + q0 + r) * kHeadDim + ch) = w;
+    } else {
+      bf16x4 b;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const float l_tot = l_run[nt] + swap_half(l_run[nt]);
-    const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-    if constexpr (PV8) {      // O = v_scale[channel] * (sum P8 V8) / (sum P8)
+      for (int e = 0; e < 4; ++e) b[e] = (__bf16)w[e];
+      *(bf16x4*)(tile + r * kRowPad + ch) = b;
+    }
+  };
+  auto put_lse = [&](int r, float m, float l_tot) __attribute__((always_inline)) {
+    const size_t row = (size_t)u.qh * g.seq + u.i * 64 + q0 + r;
+    // (PV8: the sum is that of 448 p)
+    // (the FMA is spelled out so that every instance of the kernel rounds alike)
+    float v = l_tot > 0.0f ? __builtin_fmaf(m, 0.6931471805599453f, __logf(PV8 ? l_tot * (1.0f / 448.0f) : l_tot)) : -INFINITY;
+    if constexpr (QK8) {
+      // The 8-bit logits are those of K minus its mean key, i.e. Eq. 1's logits of this row minus q_r . mean /
+      // sqrt(d) (which the softmax cancels in O); lse is reported for Eq. 1's S, so the shift goes back in.
+      const uint16_t* qr = q + row_off(g.sq, u.qh, u.i * 64 + q0 + r);
+      const float* mean = q8o.k_mean + (size_t)u.kvh * kHeadDim;
+      float dot = 0.0f;
+      for (int ch = 0; ch < kHeadDim; ++ch) dot = __builtin_fmaf(bf16_bits_to_float(qr[ch]), mean[ch], dot);
+      v += dot * 0.08838834764831845f;
+    }
+    lse[row] = v;
+  };
+  if constexpr (PV8) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const float l_tot = l_run[nt] + swap_half(l_run[nt]);
+      const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+      // O = v_scale[channel] * (sum P8 V8) / (sum P8)
       const float* vs = q8o.v_scale + (size_t)u.kvh * kHeadDim + 4 * h;
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           const f32x4 sc = *(const f32x4*)(vs + 32 * dt + 8 * q4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) oacc[dt][nt][4 * q4 + e] *= sc[e];
-        }
-    }
-    const size_t row = (size_t)u.qh * g.seq + u.i * 64 + q0 + 32 * nt + c;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        if (o32) {     // calibration reads the output before it is rounded to bf16
           f32x4 w;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = oacc[dt][nt][4 * q4 + e] * inv;
-          *(f32x4*)(o32 + row * kHeadDim + 4 * h + 32 * dt + 8 * q4) = w;
-        } else {
-          bf16x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = (__bf16)(oacc[dt][nt][4 * q4 + e] * inv);
-          *(bf16x4*)(tile + (32 * nt + c) * kRowPad + 4 * h + 32 * dt + 8 * q4) = w;
+          for (int e = 0; e < 4; ++e) w[e] = oacc[dt][nt][4 * q4 + e] * sc[e] * inv;
+          put4(32 * nt + c, 4 * h + 32 * dt + 8 * q4, w);
         }
-      }
-    if (lse && h == 0) {
-      // (PV8: the sum is that of 448 p)
-      // (the FMA is spelled out so that every instance of the kernel rounds alike)
-      float v = l_tot > 0.0f ? __builtin_fmaf(m_run[nt], 0.6931471805599453f, __logf(PV8 ? l_tot * (1.0f / 448.0f) : l_tot)) : -INFINITY;
-      if constexpr (QK8) {
-        // The 8-bit logits are those of K minus its mean key, i.e. Eq. 1's logits of this row minus q_r . mean /
-        // sqrt(d) (which the softmax cancels in O); lse is reported for Eq. 1's S, so the shift goes back in.
-        const uint16_t* qr = q + row_off(g.sq, u.qh, u.i * 64 + q0 + 32 * nt + c);
-        const float* mean = q8o.k_mean + (size_t)u.kvh * kHeadDim;
-        float dot = 0.0f;
-        for (int ch = 0; ch < kHeadDim; ++ch) dot = __builtin_fmaf(bf16_bits_to_float(qr[ch]), mean[ch], dot);
-        v += dot * 0.08838834764831845f;
-      }
-      lse[row] = v;
+      if (lse && h == 0) put_lse(32 * nt + c, m_run[nt], l_tot);
+    }
+  } else {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      const float inv = l_run[qt] > 0.0f ? 1.0f / l_run[qt] : 0.0f;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) put4(16 * qt + n16, 16 * dt + 4 * g16, o16[dt][qt] * inv);
+      if (lse && g16 == 0) put_lse(16 * qt + n16, m_run[qt], l_run[qt]);
     }
   }
   if (!o32) {
@@ -1203,7 +1312,7 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   Qk8 q8o = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (qk8) {
     const Int8Operands w8i = carve_int8_operands(p, (void*)w.ops8);
-    int rc = launch_int8_operands(p, q, k, w8i, true, st);
+    int rc = launch_int8_operands(p, q, k, w8i, pv8 ? 32 : 16, st);
     if (rc != SALE_OK) return rc;
     q8o = {w8i.q8, (const u32x4*)w8i.k8, w8i.q_scale, w8i.k_scale, w8i.k_mean, nullptr, nullptr};
     if (pv8) {

@@ -48,10 +48,13 @@ __global__ __launch_bounds__(1024) void kmean_kernel(const double* __restrict__ 
 }
 
 // One workgroup per (head, 64-row block).  Thread t holds 32 channels (32 (t % 4) ..) of row t / 4.
-// FRAG: codes go out in the operand order of v_mfma_i32_32x32x32_i8 for the keys-as-rows product,
-//   [head][tile][mt 0..1][ks 0..3][lane 0..63] 16 bytes: channels 32ks + 16(lane/32) .. of key row 32mt + lane%32;
-// otherwise row-major [head][row][128 bytes].
-template <bool FRAG>
+// FRAG: codes go out in the operand order of the keys-as-rows product,
+//   16: of v_mfma_i32_16x16x64_i8, [head][tile][kt 0..3][ks 0..1][lane 0..63] 16 bytes: channels 64ks + 16(lane/16) .. of
+//       key row 16kt + lane%16;
+//   32: of v_mfma_i32_32x32x32_i8, [head][tile][mt 0..1][ks 0..3][lane 0..63] 16 bytes: channels 32ks + 16(lane/32) .. of
+//       key row 32mt + lane%32;
+//   0: row-major [head][row][128 bytes].
+template <int FRAG>
 __global__ __launch_bounds__(256) void quantize8_kernel(const uint16_t* __restrict__ x, Strided lx,
                                                         const float* __restrict__ mean, int tiles_per_head,
                                                         int8_t* __restrict__ codes, float* __restrict__ scale) {
@@ -100,7 +103,11 @@ __global__ __launch_bounds__(256) void quantize8_kernel(const uint16_t* __restri
   u32x4 lo, hi;
   lo[0] = packed[0]; lo[1] = packed[1]; lo[2] = packed[2]; lo[3] = packed[3];
   hi[0] = packed[4]; hi[1] = packed[5]; hi[2] = packed[6]; hi[3] = packed[7];
-  if (FRAG) {
+  if (FRAG == 16) {
+    u32x4* dst = (u32x4*)codes + blk * 512 + ((r >> 4) * 2 + (cq >> 1)) * 64 + 32 * (cq & 1) + (r & 15);
+    dst[0] = lo;      // channels 32cq .. +15   -> lanes 32 (cq % 2) .. +15
+    dst[16] = hi;     // channels 32cq+16 .. +31 -> the next 16 lanes
+  } else if (FRAG == 32) {
     u32x4* dst = (u32x4*)codes + blk * 512 + ((r >> 5) * 4 + cq) * 64 + (r & 31);
     dst[0] = lo;      // channels 32cq .. +15   -> lanes 0..31
     dst[32] = hi;     // channels 32cq+16 .. +31 -> lanes 32..63
@@ -273,8 +280,8 @@ Int8Operands carve_int8_operands(const sale_params_t* p, void* base) {
   return w;
 }
 
-// Fills the operand copies: Q codes row-major, K codes in fragment order (frag_k) or row-major.
-int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, bool frag_k,
+// Fills the operand copies: Q codes row-major, K codes in fragment order (frag_k = 16 or 32, see quantize8_kernel) or row-major (0).
+int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, int frag_k,
                          hipStream_t st) {
   const int n_kvh = p->batch * p->n_kv_heads, n_qh = p->batch * p->n_q_heads, tiles = p->seq_len / 64;
   const Geo g = make_geo(p);
@@ -282,14 +289,17 @@ int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, c
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   kmean_kernel<<<dim3((unsigned)n_kvh), dim3(1024), 0, st>>>(w.partial, tiles, p->seq_len, w.k_mean);
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  quantize8_kernel<false><<<dim3((unsigned)(n_qh * tiles)), dim3(256), 0, st>>>((const uint16_t*)q, g.sq, nullptr, tiles,
+  quantize8_kernel<0><<<dim3((unsigned)(n_qh * tiles)), dim3(256), 0, st>>>((const uint16_t*)q, g.sq, nullptr, tiles,
                                                                                w.q8, w.q_scale);
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  if (frag_k)
-    quantize8_kernel<true><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
-                                                                                 w.k8, w.k_scale);
+  if (frag_k == 16)
+    quantize8_kernel<16><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
+                                                                               w.k8, w.k_scale);
+  else if (frag_k == 32)
+    quantize8_kernel<32><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
+                                                                               w.k8, w.k_scale);
   else
-    quantize8_kernel<false><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
+    quantize8_kernel<0><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
                                                                                   w.k8, w.k_scale);
   return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
 }
@@ -309,7 +319,7 @@ extern "C" int sale_attn_int8_operands(const sale_params_t* p, const void* q, co
   Int8Operands w;
   w.q8 = q8; w.k8 = k8; w.q_scale = q_scale8; w.k_scale = k_scale8; w.k_mean = k_mean;
   w.partial = (double*)ws;
-  return launch_int8_operands(p, q, k, w, false, (hipStream_t)stream);
+  return launch_int8_operands(p, q, k, w, 0, (hipStream_t)stream);
 }
 
 extern "C" int sale_attn_fp8_operands(const sale_params_t* p, const void* v, uint8_t* v8, float* v_scale, void* ws,

@@ -90,6 +90,12 @@ __device__ __forceinline__ float int_bits_as_float(int x) {
   return __builtin_bit_cast(float, x);
 }
 
+__device__ __forceinline__ f32x4 int_bits_as_floats(i32x4 x) {      // (the same for four)
+  f32x4 y = __builtin_bit_cast(f32x4, x);
+  asm("" : "+v"(y));
+  return y;
+}
+
 // max(x, x of lane ^ 32) without going through LDS: v_permlane32_swap exchanges the upper 32 lanes of its
 // first register with the lower 32 lanes of its second, so with x in both it leaves the lower half's values in
 // both halves of one register and the upper half's in the other.  Written as inline assembly on purpose: through
@@ -181,7 +187,7 @@ Fp8Operands carve_fp8_operands(const sale_params_t* p, void* base);
 int launch_fp8_operands(const sale_params_t* p, const void* v, const Fp8Operands& w, bool frag, hipStream_t st);
 size_t int8_operand_bytes(const sale_params_t* p);
 Int8Operands carve_int8_operands(const sale_params_t* p, void* base);
-int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, bool frag_k,
+int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, int frag_k,
                          hipStream_t st);
 
 }  // namespace sale
