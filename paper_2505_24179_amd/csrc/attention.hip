@@ -44,9 +44,6 @@
 //   is balanced over the XCDs by a table that moves rows of over-loaded heads to
 //   the lanes of under-loaded ones, and the short rows ride at the tail of the
 //   window launches (details at launch_sparse_rows and balance_kernel).
-#include <type_traits>
-#include <utility>
-
 #include "row_split.h"
 #include "sale_common.h"
 
@@ -234,11 +231,6 @@ constexpr PhaseStep phase_step(int i, int nq, int np, int group) {
     if (first) ++iq; else ++ip;
   }
 }
-template <class F, int... I>
-__device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
-
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
 // and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 276 - 348

@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "sale.h"
 
 namespace sale {
@@ -27,6 +30,12 @@ constexpr int kBlockK = 64;     // b_k of the Computation-Pass (the Selection-Pa
 constexpr int kSegmentBlocks = 4;            // key blocks per segment (Appendix C)
 constexpr int kMaskWordsMax = 64;            // longest mask row, in 64-bit words
 constexpr int kMaxSeqLen = kMaskWordsMax * 64 * kBlockK;   // 262144 tokens (131072 with b_k = 32)
+
+// f(integral_constant 0), f(integral_constant 1), ..: unrolled whatever its size, with indices that are constants.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
 
 // How one of Q, K, V, O is laid out: element (flat head f = b * heads + h, token t, channel c) lies at
 // (f / heads) * sb + (f % heads) * sh + t * st + c.

@@ -4,8 +4,8 @@
 // bit per (query block, key block).
 //
 // Both kernels compute the TRANSPOSED tile, keys x queries (A operand = K rows,
-// B operand = Q rows).  In the 32x32 MFMA accumulator layout a lane then owns
-// 16 keys of ONE query column, so the per-query maximum over a key block is an
+// B operand = Q rows).  In the MFMA accumulator layouts a lane then owns keys of
+// ONE query column per tile, so the per-query maximum over a key block is an
 // in-lane max chain, the per-query threshold is a single register, and the
 // "any row of the block passes" reduction is the wave-wide compare mask.
 //
@@ -39,14 +39,17 @@ __device__ __forceinline__ bool in_sink_local(const Geo& g, int j, int j_last, i
 // FP6 E2M3 (1 sign, 2 exponent, 3 mantissa bits, bias 1: 1 = 0b001000, 2 =
 // 0b010000, 3 = 0b010100, 4 = 0b011000, 5 = 0b011010, 6 = 0b011100, 7 =
 // 0b011110), products are at most 49 and a 128-term sum at most 6272 < 2^24, so
-// v_mfma_f32_32x32x64_f8f6f4 with both operands in E2M3 and unit scales returns
+// v_mfma_f32_16x16x128_f8f6f4 with both operands in E2M3 and unit scales returns
 // the integer product EXACTLY in its fp32 accumulator (checked on hardware
 // against integer arithmetic, including all-(+-7) operands) at twice the int8
-// MFMA rate.  A pre-pass re-encodes the nibble codes of K~ once into MFMA operand
-// order ("X6"; Q~ is re-encoded by the wave that uses it): per group of 32 rows 2 fragments ks (channels 64ks..); lane l of a
-// fragment owns row l%32 of the group, channels 64ks + 32(l/32) + e, e = 0..31, as
+// MFMA rate.  (That shape because the kernel runs at the card's power limit: it contracts all 128 channels at once, so no
+// accumulator is read back.  A loop of random operands with the maxima beside it: 44 products of 32x32x64 per us and
+// SIMD, 94 of these, half as large; 96 if neighbours share an operand throughout.)
+// A pre-pass re-encodes the nibble codes of K~ once into MFMA operand
+// order ("X6"; Q~ is re-encoded by the wave that uses it): per group of 32 rows 2 fragments f (rows 16f..); lane l of a
+// fragment owns row 16f + l%16 of the group, channels 32(l/16) + e, e = 0..31, as
 // 32 six-bit codes = 6 dwords, stored as
-//   [group][ks][lane] 16 bytes (dwords 0..3)  followed by  [group][ks][lane] 8 bytes (dwords 4..5).
+//   [group][f][lane] 16 bytes (dwords 0..3)  followed by  [group][f][lane] 8 bytes (dwords 4..5).
 constexpr int kX6GroupBytes = 2 * 64 * 24;   // 3072 bytes per 32 rows
 
 // (about 30 vector instructions per 8 codes; code by code it took 64 and was 7 us of a wave of select_kernel)
@@ -91,8 +94,8 @@ struct PackFp6 {
   __device__ __forceinline__ void run(int block) const {
     const long grp = (long)(block - first) * (blockDim.x >> 7) + (threadIdx.x >> 7);
     if (grp >= groups) return;
-    const int ks = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63;
-    const u32x4 w = *(const u32x4*)(x + ((size_t)grp * 32 + (lane & 31)) * 64 + 32 * ks + 16 * (lane >> 5));
+    const int f = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63;
+    const u32x4 w = *(const u32x4*)(x + ((size_t)grp * 32 + 16 * f + (lane & 15)) * 64 + 16 * (lane >> 4));
     uint32_t d[6];
     pack_fp6(w, d);
     uint8_t* yg = y + (size_t)grp * kX6GroupBytes;
@@ -100,8 +103,8 @@ struct PackFp6 {
     lo[0] = d[0]; lo[1] = d[1]; lo[2] = d[2]; lo[3] = d[3];
     u32x2 hi;
     hi[0] = d[4]; hi[1] = d[5];
-    *(u32x4*)(yg + (ks * 64 + lane) * 16) = lo;
-    *(u32x2*)(yg + 2048 + (ks * 64 + lane) * 8) = hi;
+    *(u32x4*)(yg + (f * 64 + lane) * 16) = lo;
+    *(u32x2*)(yg + 2048 + (f * 64 + lane) * 8) = hi;
   }
 };
 
@@ -346,39 +349,45 @@ __global__ __launch_bounds__(256) void stats_shared_kernel(Geo g, const uint16_t
   }
 }
 
-// The 2 operand fragments (ks = 0, 1) of 32-row group `grp` of an X6 array.
-__device__ __forceinline__ void load_x6(__amdgpu_buffer_rsrc_t base, int grp, int lane, i32x8 f[2]) {
+// The 2 operand fragments (16 rows each) of 32-row group `grp` of an X6 array.
+__device__ __forceinline__ void load_x6(__amdgpu_buffer_rsrc_t base, int grp, int lane, i32x8* f) {
   const int b = grp * kX6GroupBytes;
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const u32x4 lo = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(base, lane * 16 + ks * 1024, b, 0));
-    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(base, lane * 8 + 2048 + ks * 512, b, 0));
-    f[ks][0] = lo[0]; f[ks][1] = lo[1]; f[ks][2] = lo[2]; f[ks][3] = lo[3];
-    f[ks][4] = hi[0]; f[ks][5] = hi[1]; f[ks][6] = 0; f[ks][7] = 0;
+  for (int i = 0; i < 2; ++i) {
+    const u32x4 lo = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(base, lane * 16 + i * 1024, b, 0));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(base, lane * 8 + 2048 + i * 512, b, 0));
+    f[i][0] = lo[0]; f[i][1] = lo[1]; f[i][2] = lo[2]; f[i][3] = lo[3];
+    f[i][4] = hi[0]; f[i][5] = hi[1]; f[i][6] = 0; f[i][7] = 0;
   }
 }
-
-// acc[mt][nt] = (K~ row tile mt) (Q~ row tile nt)^T, keys x queries, exact integers held in fp32.
-template <int MT>
-__device__ __forceinline__ void qk_tile_fp6(const i32x8 kf[MT][2], const i32x8 qf[2][2], f32x16 acc[MT][2]) {
-  // the two k-steps of a tile depend on each other: issue all tiles' first steps, then their second
+// The same of 16 rows of nibble codes (64 bytes each).
+__device__ __forceinline__ i32x8 fragment_of_nibbles(const uint8_t* rows16, int lane) {
+  uint32_t d[6];
+  pack_fp6(*(const u32x4*)(rows16 + (lane & 15) * 64 + 16 * (lane >> 4)), d);
+  i32x8 f;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const f32x16 z = {0};
-      acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf[mt][0], qf[nt][0], z, 2, 2, 0, 0, 0, 0);
-    }
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-      acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf[mt][1], qf[nt][1], acc[mt][nt], 2, 2, 0, 0, 0, 0);
+  for (int e = 0; e < 6; ++e) f[e] = d[e];
+  f[6] = 0; f[7] = 0;
+  return f;
 }
 
-// Maximum over the keys of a block of what one lane holds for query tile nt.
+// acc[kt][qt] = (16 K~ rows kt) (16 Q~ rows qt)^T, keys x queries, exact integers held in fp32: register r of a lane is key
+// 4 (lane / 16) + r of query lane % 16.  Neighbouring products share an operand.
 template <int MT>
-__device__ __forceinline__ float lane_max(const f32x16 acc[MT][2], int nt) {
+__device__ __forceinline__ void qk_tile_fp6(const i32x8 kf[2 * MT], const i32x8 qf[4], f32x4 acc[2 * MT][4]) {
+#pragma unroll
+  for (int kt = 0; kt < 2 * MT; ++kt)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int qt = kt & 1 ? 3 - n : n;
+      const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+      acc[kt][qt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf[kt], qf[qt], z, 2, 2, 0, 0, 0, 0);
+    }
+}
+
+// Maximum over the keys of a block of what one lane holds for query tile nt (16-bit estimate).
+template <int MT>
+__device__ __forceinline__ float lane_max32(const f32x16 acc[MT][2], int nt) {
   float mx = acc[0][nt][0];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -388,7 +397,9 @@ __device__ __forceinline__ float lane_max(const f32x16 acc[MT][2], int nt) {
 }
 
 // One wave scores HPW query heads of one GQA group at the same query block, so every K~ fragment it
-// loads feeds HPW x 2 MFMAs (HPW = 4 when the group allows).  A workgroup is 4 such waves (consecutive head sets / query blocks of one
+// loads feeds HPW x 4 MFMAs (HPW up to 4: launch_select).  What bounds it: 64 MFMAs of 16 cycles and 160 vector instructions
+// per 64-key block and four heads on two waves per SIMD; the matrix pipe is busy 72 % of the clocks, which the power limit
+// holds at 1.9 GHz.  (128K x 32 heads: 13.3 -> 12.7 ms against 32x32x64 products with their maxima taken head by head.)  A workgroup is 4 such waves (consecutive head sets / query blocks of one
 // KV head); workgroups go round-robin over KV heads, longest rows first.  chunk > 0 (select_chunk): a wave scores
 // blockIdx.y's `chunk` blocks of its rows only.  A mask word belongs to one wave if chunk is a multiple of 64,
 // otherwise (a divisor of 64) its bits are joined by atomics, as are the counts (whole numbers: any order gives the same).
@@ -400,7 +411,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     const float* __restrict__ k_scale, const float* __restrict__ thr, uint64_t* __restrict__ mask,
     int32_t* __restrict__ row_counts, int chunk) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform by construction
-  const int c = lane & 31;
+  const int c = lane & 15;
   const int sets = g.group / HPW;                 // head sets per (KV head, query block)
   const int units = g.n_qb * sets;
   const int tiles = (units + 3) / 4;
@@ -409,7 +420,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   if (id >= units) return;
   const int i = id / sets;
   const int qh0 = kvh * g.group + (id % sets) * HPW;
-  const SeqPos sp = seq_pos(g, i);
+  SeqPos sp = seq_pos(g, i);
+  sp.il = __builtin_amdgcn_readfirstlane(sp.il);      // (the same for the whole wave: all control flow below is scalar)
+  sp.kb0 = __builtin_amdgcn_readfirstlane(sp.kb0);
   const int j_last = j_last_of(g, sp.il), local = local_of(g, j_last);
   // This wave's blocks of the row: r_lo .. r_hi - 1.
   const int r_lo = chunk ? (int)blockIdx.y * chunk : 0, r_hi = chunk ? min(r_lo + chunk, g.words * 64) : g.words * 64;
@@ -422,27 +435,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     return;
   }
 
-  i32x8 qf[HPW][2][2];
-  float th[HPW][2], cq[HPW];
+  i32x8 qf[HPW][4];
+  float th[HPW][4], cq[HPW];
 #pragma unroll
   for (int a = 0; a < HPW; ++a) {
     // Q~ is used by this wave alone: its nibble codes are re-encoded here, once per row (K~, which every query
-    // block reads again, comes re-encoded from the pre-pass).  Lane (c, h) of fragment (row tile nt, ks) owns row
-    // 32 nt + c, channels 64 ks + 32 h ..: 16 bytes of the row.
+    // block reads again, comes re-encoded from the pre-pass).
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const uint8_t* row = q4 + ((size_t)(qh0 + a) * g.seq + i * 64 + 32 * nt + c) * 64 + 16 * (lane >> 5);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        uint32_t d[6];
-        pack_fp6(*(const u32x4*)(row + 32 * ks), d);
-#pragma unroll
-        for (int e = 0; e < 6; ++e) qf[a][nt][ks][e] = d[e];
-        qf[a][nt][ks][6] = 0; qf[a][nt][ks][7] = 0;
-      }
+    for (int qt = 0; qt < 4; ++qt) {
+      qf[a][qt] = fragment_of_nibbles(q4 + ((size_t)(qh0 + a) * g.seq + i * 64 + 16 * qt) * 64, lane);
+      th[a][qt] = thr[(size_t)(qh0 + a) * g.seq + i * 64 + 16 * qt + c];
     }
-    th[a][0] = thr[(size_t)(qh0 + a) * g.seq + i * 64 + c];
-    th[a][1] = thr[(size_t)(qh0 + a) * g.seq + i * 64 + 32 + c];
     cq[a] = q_scale[(size_t)(qh0 + a) * g.n_qb + i] * 0.08838834764831845f;   // s_q / sqrt(d)
   }
   const float* ks = k_scale + (size_t)kvh * g.n_kb;
@@ -484,27 +487,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   // The operands of a key block are requested one block ahead (two register sets that swap roles): the loads of
   // block j + 1 are in flight while block j is scored.  The last block requests itself again, so every step
   // issues the same loads and the wait counts stay exact.
-  i32x8 kfa[MT][2], kfb[MT][2];
+  i32x8 kfa[2 * MT], kfb[2 * MT];
   float ska = 0.0f, skb = 0.0f;
-  auto fetch = [&](int j, i32x8 (&kf)[MT][2], float& sk) __attribute__((always_inline)) {
+  auto fetch = [&](int j, i32x8 (&kf)[2 * MT], float& sk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) load_x6(kbuf, j * MT + mt, lane, kf[mt]);
+    for (int mt = 0; mt < MT; ++mt) load_x6(kbuf, j * MT + mt, lane, kf + 2 * mt);
     sk = ks[sp.kb0 + j];
   };
-  auto score = [&](int j, const i32x8 (&kf)[MT][2], float sk, i32x8 (&kn)[MT][2], float& skn) __attribute__((always_inline)) {
+  // (as assembly, which says that the word is a scalar: the compiler kept the words in vector registers, 8 instructions a head)
+  auto set_bits_if_any = [](uint64_t& w, uint64_t bits, uint64_t lanes) __attribute__((always_inline)) {
+    uint64_t t;
+    asm("s_cmp_lg_u64 %2, 0\n\ts_cselect_b64 %1, %3, 0\n\ts_or_b64 %0, %0, %1" : "+s"(w), "=&s"(t) : "s"(lanes), "s"(bits) : "scc");
+  };
+  auto score = [&](int j, const i32x8 (&kf)[2 * MT], float sk, i32x8 (&kn)[2 * MT], float& skn) __attribute__((always_inline)) {
+    float cj[HPW];
+#pragma unroll
+    for (int a = 0; a < HPW; ++a) cj[a] = cq[a] * sk;
+    __builtin_amdgcn_sched_barrier(0);      // (the wait for this block's scale must not become one for the next block's: scalar loads have no order)
     fetch(min(j + 1, mid_hi), kn, skn);
     while (wc < (j >> 6)) flush();
+    // Unit u: query tile u % 4 of head u / 4, 2 MT products and the maximum over their 8 MT values per lane.  The products of
+    // a unit are laid beside the maxima of the unit before it, one by one; neighbours share an operand.  (v_maximum3_f32:
+    // for v_max3_f32 the compiler first quiets every product that enters, a fifth of the vector instructions.  All tiles are
+    // always scored: most blocks fail, and a short-circuit is a branch.)
+    constexpr int kTiles = 2 * MT, kUnits = 4 * HPW, kOps = 4 * MT + 2;
+    f32x4 acc[2][kTiles];
+    float m0 = 0.0f, m1 = 0.0f;
+    bool pass[HPW];
+    static_for<kUnits + 1>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value, v = u - 1;
+      static_for<kTiles>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value, kt = u % 2 ? kTiles - 1 - k : k;
+        if constexpr (u < kUnits) {
+          const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+          acc[u % 2][kt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf[kt], qf[u / 4][u % 4], z, 2, 2, 0, 0, 0, 0);
+        }
+        if constexpr (v >= 0)
+          static_for<(k + 1) * kOps / kTiles - k * kOps / kTiles>([&](auto oc) __attribute__((always_inline)) {
+            constexpr int o = k * kOps / kTiles + decltype(oc)::value, a = v / 4, half = o / 2;
+            auto at = [&](int n) { return acc[v % 2][n / 4][n % 4]; };
+            auto max3 = [](float x, float y, float w) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), w); };
+            constexpr int n1 = 4 * MT;      // the second chain's first value
+            if constexpr (o < 4 * MT - 2) {      // two chains in turn
+              if constexpr (half == 0) (o % 2 ? m1 : m0) = max3(at(o % 2 * n1), at(o % 2 * n1 + 1), at(o % 2 * n1 + 2));
+              else if constexpr (o % 2 == 0) m0 = max3(m0, at(2 * half + 1), at(2 * half + 2));
+              else m1 = max3(m1, at(n1 + 2 * half + 1), at(n1 + 2 * half + 2));
+            } else if constexpr (o == 4 * MT - 2) m0 = max3(m0, at(n1 - 1), at(2 * n1 - 1));
+            else if constexpr (o == 4 * MT - 1) m0 = __builtin_elementwise_maximum(m0, m1);
+            else if constexpr (o == 4 * MT) m0 = m0 * cj[a];
+            else pass[a] = (v % 4 == 0 ? false : pass[a]) | (m0 >= th[a][v % 4]);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
 #pragma unroll
-    for (int a = 0; a < HPW; ++a) {
-      f32x16 acc[MT][2];
-      qk_tile_fp6<MT>(kf, qf[a], acc);
-      const float cj = cq[a] * sk;
-      // (both halves always: a short-circuit would put the second maximum chain behind a branch, where it
-      // cannot be interleaved with the next head's MFMAs; most blocks fail the first test anyway)
-      const bool p0 = lane_max<MT>(acc, 0) * cj >= th[a][0];
-      const bool p1 = lane_max<MT>(acc, 1) * cj >= th[a][1];
-      word[a] |= (uint64_t)(__ballot(p0 | p1) != 0ull) << (j & 63);
-    }
+    for (int a = 0; a < HPW; ++a) set_bits_if_any(word[a], 1ull << (j & 63), __builtin_amdgcn_ballot_w64(pass[a]));
   };
   if (mid_lo <= mid_hi) {
     fetch(mid_lo, kfa, ska);
@@ -570,7 +607,7 @@ __global__ __launch_bounds__(256) void select16_kernel(Geo g, const uint16_t* __
           acc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[1][s], acc[mt][1], 0, 0, 0);
         }
       }
-      const bool pass = (lane_max<MT>(acc, 0) * rsd >= th[0]) || (lane_max<MT>(acc, 1) * rsd >= th[1]);
+      const bool pass = (lane_max32<MT>(acc, 0) * rsd >= th[0]) || (lane_max32<MT>(acc, 1) * rsd >= th[1]);
       word |= (uint64_t)(__ballot(pass) != 0ull) << jj;
     }
     if (lane == 0) mrow[wc] = word;
@@ -584,34 +621,24 @@ __global__ __launch_bounds__(256) void select16_kernel(Geo g, const uint16_t* __
 template <int MT>
 __global__ __launch_bounds__(64) void products_kernel(const uint8_t* __restrict__ q4_head, const uint8_t* __restrict__ k4_head,
                                                       int q_block, int k_begin, int n_kblocks, int32_t* __restrict__ out) {
-  const int lane = threadIdx.x, c = lane & 31;
+  const int lane = threadIdx.x, c = lane & 15;
   const int jb = blockIdx.x;
-  auto frag = [&](const uint8_t* rows32, int ks, i32x8& f) __attribute__((always_inline)) {
-    uint32_t d[6];
-    pack_fp6(*(const u32x4*)(rows32 + (size_t)c * 64 + 32 * ks + 16 * (lane >> 5)), d);
+  i32x8 qf[4], kf[2 * MT];
 #pragma unroll
-    for (int e = 0; e < 6; ++e) f[e] = d[e];
-    f[6] = 0; f[7] = 0;
-  };
-  i32x8 qf[2][2], kf[MT][2];
+  for (int qt = 0; qt < 4; ++qt) qf[qt] = fragment_of_nibbles(q4_head + ((size_t)q_block * 4 + qt) * 1024, lane);
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) frag(q4_head + ((size_t)q_block * 2 + nt) * 2048, ks, qf[nt][ks]);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) frag(k4_head + ((size_t)(k_begin + jb) * MT + mt) * 2048, ks, kf[mt][ks]);
-  }
-  f32x16 acc[MT][2];
+  for (int kt = 0; kt < 2 * MT; ++kt) kf[kt] = fragment_of_nibbles(k4_head + ((size_t)(k_begin + jb) * 2 * MT + kt) * 1024, lane);
+  f32x4 acc[2 * MT][4];
   qk_tile_fp6<MT>(kf, qf, acc);
   const size_t ld = (size_t)n_kblocks * (32 * MT);
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int kt = 0; kt < 2 * MT; ++kt)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int qt = 0; qt < 4; ++qt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * mt + mfma32_row(r, lane), qr = 32 * nt + c;
-        out[(size_t)qr * ld + jb * (32 * MT) + key] = (int32_t)acc[mt][nt][r];
+      for (int r = 0; r < 4; ++r) {
+        const int key = 16 * kt + 4 * (lane >> 4) + r, qr = 16 * qt + c;
+        out[(size_t)qr * ld + jb * (32 * MT) + key] = (int32_t)acc[kt][qt][r];
       }
 }
 
@@ -641,8 +668,10 @@ int launch_select(const Geo& g, bool est16, const void* q, const void* k, const 
                   const float* q_scale, const float* k_scale, const float* tau, int tau_len, const float* thr_c,
                   float* thr, uint64_t* block_mask, int32_t* row_counts, float* m_out, float* l_out, hipStream_t st) {
   const int tiles = (g.n_qb * g.group + 3) / 4;
-  // Heads per wave of select_kernel (with 32-key blocks two are faster than four: 15.8 against 17.1 ms at 128K).
-  const int hpw = MT == 2 && g.group % 4 == 0 ? 4 : g.group % 2 == 0 ? 2 : 1;
+  // Heads per wave of select_kernel: four, so that a K~ fragment feeds twice as many products, where there are waves enough
+  // (select call, four / two heads: 128K x 32 heads 12.7 / 13.3 ms, 32K 974 / 984 us; 16K 302 / 287, 4K 56.6 / 49.8).  With
+  // 32-key blocks, which have half the maxima per product, two are as fast at 64K (3.66 / 3.70 ms) and use fewer registers.
+  const int hpw = MT == 2 && g.group % 4 == 0 && (long)g.n_qb * g.n_qh >= 16384 ? 4 : g.group % 2 == 0 ? 2 : 1;
   const int chunk = est16 ? 0 : select_chunk(g, hpw);
   const ClearRows clear = {chunk ? row_counts : nullptr, chunk && chunk < 64 ? block_mask : nullptr};
   const long kgroups = est16 ? 0 : (long)g.n_kvh * (g.seq / 32);
