@@ -231,6 +231,21 @@ constexpr PhaseStep phase_step(int i, int nq, int np, int group) {
     if (first) ++iq; else ++ip;
   }
 }
+// The same for a step of the FP8 pass: np MFMAs of the second product (kind 1), 64 cycles each, nt of the row sums (kind 2)
+// and nq of the first product (kind 0), 32 cycles each.  fp8_upto: how many of `ops` vector instructions are issued by the end
+// of step i, in proportion to time: from the third MFMA on (the last scores are still on their way) until the first product
+// turns to the second query tile, whose old scores are then used up (with both sets of scores the step spills).
+constexpr PhaseStep fp8_step(int i, int nq, int np, int nt) {
+  const int per = np / nt + 1;      // products and sum of one query tile
+  return i >= np + nt ? PhaseStep{0, i - np - nt} : i % per == per - 1 ? PhaseStep{2, i / per} : PhaseStep{1, i - i / per};
+}
+constexpr int fp8_upto(int i, int nq, int np, int nt, int ops) {
+  const int lead = 4, span = nt == 2 ? nq / 2 : nq, total = 2 * np + nt + span - lead;      // (in 32 cycles)
+  int done = -lead;
+  for (int k = 0; k <= i; ++k) done += fp8_step(k, nq, np, nt).kind == 1 ? 2 : 1;
+  return done <= 0 ? 0 : done >= total ? ops : (ops * done + total - 1) / total;
+}
+
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
 // and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 276 - 348
@@ -249,8 +264,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
                                                                float* __restrict__ st_ml) {
   static_assert(NT == 2 || WAVES == 1, "the two halves of a row share a workgroup of their own");
   const int tid = threadIdx.x, lane = tid & 63;
-  // (wave-uniform by construction: the unit and its addresses are scalars; the FP8 pass spills with it)
-  const int wave_id = PV8 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);      // (wave-uniform by construction: the unit and its addresses are scalars)
   const int wave = NT == 1 ? 0 : wave_id;
   const int q0 = NT == 1 ? wave_id * 32 : 0;      // first query of this wave inside the row block
   constexpr int NQ = 2 * NT;                      // 16-query tiles of this wave
@@ -340,16 +354,17 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   const int first_tile = __builtin_amdgcn_readfirstlane((int)((size_t)u.kvh * g.seq / 64) + (u.i - il));
   const int tiles = __builtin_amdgcn_readfirstlane(il) + 1;      // (64-key tiles up to the diagonal)
   const int lane16 = lane * 16;
-  __amdgpu_buffer_rsrc_t k8t;      // (the FP8 pass reads through plain pointers: with descriptors its loop took 8.5 ms at 64K instead of 7.5)
+  __amdgpu_buffer_rsrc_t k8t;
   const float* ks8 = nullptr;
   if constexpr (QK8) {
     sq_cs = q8o.q_scale[unit_flat] * cs;
     k8t = operand_buffer(q8o.k8p + (size_t)first_tile * 512, tiles * 8192);      // 512 16-byte chunks per 64 keys
-    ks8 = PV8 ? q8o.k_scale + (size_t)u.kvh * (g.seq / 64) + (u.i - il) : q8o.k_scale + first_tile;
+    ks8 = q8o.k_scale + first_tile;
   }
   // (the sequence's first key tile: u.i - il 64-row blocks into the KV head)
   const __amdgpu_buffer_rsrc_t kt = operand_buffer(kp + (size_t)first_tile * 1024, tiles * 16384);     // 1024 16-byte chunks per 64 keys
-  const __amdgpu_buffer_rsrc_t vt = operand_buffer(vp + (size_t)first_tile * 1024, tiles * 16384);
+  const __amdgpu_buffer_rsrc_t vt = PV8 ? operand_buffer(q8o.v8p + (size_t)first_tile * 512, tiles * 8192)
+                                        : operand_buffer(vp + (size_t)first_tile * 1024, tiles * 16384);
   f32x16 oacc[PV8 ? 4 : 1][PV8 ? NT : 1];      // PV8: O^T in 32x32 tiles
   f32x4 o16[PV8 ? 1 : 8][PV8 ? 1 : NQ];        // otherwise: O^T in 16x16 tiles, channels 16 dt + 4 g16 .. of query n16 of tile qt
   float m_run[NQ], l_run[NQ];      // m_run in log2 units (PV8: [nt])
@@ -396,155 +411,221 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       for (int qt = 0; qt < NQ; ++qt) { m_run[qt] = sml[16 * qt + n16]; l_run[qt] = sml[128 + 16 * qt + n16]; }
     }
   }
-  int wc_it = word_lo;
-  uint64_t cur = PV8 ? row_word(word_lo) : 0ull;
-  auto next_block = [&]() -> int {
-    while (cur == 0) {
-      if (++wc_it > word_hi) return -1;
-      cur = row_word(wc_it);
+  // ---- the row's kept blocks, in ascending order, as a list in LDS (this wave's part of the output staging area) ----
+  // BK32: with an odd number of kept half-tiles the first one comes twice, the first time emptied, so that there are whole
+  // pairs and the half-tiles of the diagonal block, the largest indices of a row, fall into the last one.
+  uint16_t* const list = o_lds + (wave * 64 + q0) * kRowPad;
+  static_assert(32 * NT * kRowPad >= kMaskWordsMax * 64 + 16, "the list of the longest row fits the staging area");
+  constexpr bool kListed = WAVES == 1;          // (the four-row workgroups are the dense kernel's: every block)
+  int n_pairs = 0;
+  bool lone = false;
+  auto build_list = [&](int lo, int hi) {
+    const uint64_t mine = lane >= lo && lane <= hi ? row_word(lane) : 0ull;
+    lone = BK32 && (__popcll(__builtin_amdgcn_ballot_w64((__popcll(mine) & 1) != 0)) & 1) != 0;
+    int n = lone ? 1 : 0, first = -1, last = 0;
+    for (uint64_t any = __builtin_amdgcn_ballot_w64(mine != 0ull); any != 0ull; any &= any - 1) {
+      const int w = __builtin_ctzll(any);
+      const uint64_t word = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, w) |
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), w) << 32;
+      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0));
+      if ((word >> lane) & 1) list[n + before] = (uint16_t)(w * 64 + lane);
+      if (first < 0) first = w * 64 + __builtin_ctzll(word);
+      last = w * 64 + 63 - __builtin_clzll(word);
+      n += __popcll(word);
     }
-    const int b = __builtin_ctzll(cur);
-    cur &= cur - 1;
-    return wc_it * 64 + b;
+    if (lone && lane == 0) list[0] = (uint16_t)first;
+    if (lane < 8) list[n + lane] = (uint16_t)last;      // (the loads run up to two pairs ahead, the list is read three ahead)
+    n_pairs = BK32 ? n >> 1 : n;
   };
-
+  auto entry = [&](int n) __attribute__((always_inline)) -> uint32_t {      // of pair n
+    if constexpr (!kListed) return (uint32_t)min(n, tiles - 1);
+    else if constexpr (BK32) return *(const uint32_t*)(list + 2 * n);
+    else return list[n];
+  };
   if constexpr (PV8) {
     // ---- fully quantized pass: 8-bit first product, FP8 second product ---------------------------------
-    // One 64-key block per step, nothing deferred: S^T = K8 Q8^T (16 MFMAs), causal mask on the diagonal block,
-    // ONE row maximum over the block's 64 keys, rescale, P8 = fp8(448 * exp2(x - m)) packed straight into the B
-    // operand of the FP8 MFMA (a lane's 16 + 16 accumulator values of the two half-tiles are its 32 contraction
-    // elements; the V8' copy is in the same key order), O^T += V8^T P8^T (8 MFMAs, K = 64).  The row sums are
-    // one more MFMA per query tile with an all-ones A operand: numerator and denominator are then sums of the
-    // SAME rounded probabilities.  The next block's K8 is requested once the first product has consumed this
-    // block's, the next V8 once the second product has.
+    // S^T = K8 Q8^T (16 MFMAs per 64-key block), causal mask on the diagonal block, ONE row maximum over the block's 64 keys,
+    // rescale, P8 = fp8(448 * exp2(x - m)) packed straight into the B operand of the FP8 MFMA (a lane's 16 + 16 accumulator
+    // values of the two half-tiles are its 32 contraction elements; the V8' copy is in the same key order),
+    // O^T += V8^T P8^T (8 MFMAs, K = 64).  The row sums are MFMAs with ones in 16 rows of the A operand per query tile:
+    // numerator and denominator are then sums of the SAME rounded probabilities.
+    // The definition takes a running maximum block by block, so a step cannot do without it; but the products of its
+    // neighbours run meanwhile: step t is  O += V8(t - 1) P8(t - 1), the row sums, S(t + 1) = K8(t + 1) Q8  on the matrix unit,
+    // beside the maximum and the exponentials of S(t) on the vector unit, laid side by side as in `phase` below; operands are
+    // requested again, for the next step, by the MFMA that has read them.  A row maximum that grew is applied to O at the end
+    // of the step, before P8(t) is multiplied.  (One block after the other a step was its 1152 MFMA cycles plus about 2000 of
+    // vector instructions.)
     static_assert(QK8 && !BK32, "the FP8 second product comes with the 8-bit first product on 64-key blocks");
-    const u32x4* const v8t = q8o.v8p + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 8 + lane;   // 512 chunks per 64 keys
-    const i32x4* const k8g = (const i32x4*)q8o.k8p + ((size_t)u.kvh * g.seq + (size_t)(u.i - il) * 64) * 8 + lane;
     const float kLog2Top = 8.807354922057604f;      // log2(448)
+    constexpr int kQ8 = 8 * NT, kP8 = 4 * NT, kOps = 103 * NT;
     i32x4 k8[2][4];
     u32x4 v8[4][2];
-    float k_sc = 1.0f;
-    auto fetch_k = [&](int j) __attribute__((always_inline)) {
-      const i32x4* t = k8g + (size_t)j * 512;
+    i32x16 S[2][NT];         // [half-tile][query tile]: the integer accumulators, as in the QK8 pass below
+    // Row sums: the B operand of the 32x32x64 product, read as that of a 16x16x128 one, holds in lane l keys of query l % 32 as
+    // column l % 16, contraction group l / 16.  A operand for query tile nt: row i is 1 (E4M3: 0x38) in the groups of parity
+    // i / 4 % 2 if i / 8 == nt.  Lane (c, h) then gets, in all four registers, the sum of query c of tile h over both lane halves.
+    i32x8 P8[NT], rows_of[NT];
+    f32x4 lacc;
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+    for (int r = 0; r < 4; ++r) lacc[r] = 2.0f * (h == 0 ? l_run[0] : l_run[NT - 1]);      // (parked as half the sum: see below)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) k8[mt][s] = t[(mt * 4 + s) * 64];
-      k_sc = ks8[j];
-    };
-    auto fetch_v = [&](int j) __attribute__((always_inline)) {
-      const u32x4* t = v8t + (size_t)j * 512;
+    for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) v8[dt][jj] = t[(dt * 2 + jj) * 64];
-    };
-    f32x16 lacc[NT];      // every register: sum over the row's keys of P8 (all 32 rows of the ones product are equal)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) lacc[nt][r] = 2.0f * l_run[nt];      // (parked as half the sum: see below)
-    i32x8 ones8;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) ones8[w] = 0x38383838;                   // 1.0 in E4M3
+      for (int w = 0; w < 8; ++w) rows_of[nt][w] = (n16 >> 2 & 1) == (g16 & 1) && n16 >> 3 == nt ? 0x38383838 : 0;
+      asm("" : "+a"(rows_of[nt]));
+    }
     i32x16 magic;
 #pragma unroll
     for (int r = 0; r < 16; ++r) magic[r] = 0x4B400000;
-    // one block; `diag`: apply the causal mask (the diagonal block) - a variant of its own, so that the other
-    // blocks pay nothing for it
-    auto step8 = [&](int jn_or_j, auto diag) __attribute__((always_inline)) {
-      // (the accumulators start at the bit pattern of kIntOffset and are read as floats, as in qk_half)
-      i32x16 a[2][NT];
+    auto qk8 = [&](int n) __attribute__((always_inline)) {      // MFMA n of S = K8 Q8^T
+      const int nt = n / 8, s = n / 2 % 4, mt = n % 2;
+      S[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(k8[mt][s], qf8[nt][s], s == 0 ? magic : S[mt][nt], 0, 0, 0);
+    };
+    auto pv8 = [&](int n) __attribute__((always_inline)) {      // MFMA n of O^T += V8^T P8^T
+      const int dt = n % 4, nt = n / 4;      // (a query tile at a time: the registers of its probabilities are the next step's)
+      i32x8 va;
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int w = 0; w < 4; ++w) { va[w] = (int)v8[dt][0][w]; va[4 + w] = (int)v8[dt][1][w]; }
+      oacc[dt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, P8[nt], oacc[dt][nt], 0, 0, 0, 0, 0, 0);
+    };
+    auto sum8 = [&](int nt) __attribute__((always_inline)) {
+      lacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(rows_of[nt], P8[nt], lacc, 0, 0, 0, 0, 0, 0);
+    };
+    auto load_k8 = [&](int j, int mt, int s) __attribute__((always_inline)) { k8[mt][s] = load_chunk<i32x4>(k8t, lane16, j * 8192, mt * 4 + s); };
+    auto load_v8 = [&](int j, int dt, int jj) __attribute__((always_inline)) { v8[dt][jj] = load_chunk<u32x4>(vt, lane16, j * 8192, dt * 2 + jj); };
+    auto hide8 = [&]() __attribute__((always_inline)) {           // the diagonal block: keys after the query
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int seen = q0 + 32 * nt + c - 4 * h;
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            a[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(k8[mt][s], qf8[nt][s], s == 0 ? magic : a[mt][nt], 0, 0, 0);
-      const float cj = k_sc * sq_cs;                 // raw integer product -> logit in log2 units
-      const float off = kIntOffset * cj;                 // what the offset amounts to in logit units
-      fetch_k(jn_or_j);                              // (unconditional: the last block re-reads its own)
-      float S[2][NT][16];
+          for (int r = 0; r < 16; ++r)
+            if (32 * mt + 8 * (r >> 2) + (r & 3) > seen) S[mt][nt][r] = (int)0xFF800000;
+      }
+    };
+    float m_new[NT];
+    // One step: k_scale of the block whose scores are in S; blocks to request K8 and V8 of.  Returns whether
+    // some row's maximum grew: O, the sums and m_run are then to be rescaled before the next step.
+    auto step8 = [&](float k_scale, int k_next, int v_next) __attribute__((always_inline)) -> bool {
+#pragma clang fp contract(off)      // (every copy of the step rounds alike)
+      const float cj = k_scale * sq_cs;              // raw integer product -> logit in log2 units
+      const float off = kIntOffset * cj;             // what the accumulators' offset amounts to in logit units
+      float mx[NT], mb[NT], E[NT][32];
+      f32x16 F[NT][2];
+      int top[NT][2];
+      i32x8 P_new[NT];
+      i32x16 now[2][NT];      // the scores of this step (the first product writes S meanwhile)
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            S[mt][nt][r] = int_bits_as_float(a[mt][nt][r]);
-            if constexpr (decltype(diag)::value) {
-              if (32 * mt + mfma32_row(r, lane) > q0 + 32 * nt + c) S[mt][nt][r] = -INFINITY;
-            }
-          }
-      float mx[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        float v = fmaxf(S[0][nt][0], S[1][nt][0]);
-#pragma unroll
-        for (int r = 1; r < 16; ++r) v = fmaxf(fmaxf(v, S[0][nt][r]), S[1][nt][r]);
-        mx[nt] = __builtin_fmaf(max_with_other_half(v), cj, -off);
-      }
-      if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1]) != 0ull) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const float m_new = fmaxf(m_run[nt], mx[nt]);
-          const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m_new);
-          m_run[nt] = m_new;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) lacc[nt][r] *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][nt][r] *= alpha;
+        for (int nt = 0; nt < NT; ++nt) now[mt][nt] = S[mt][nt];
+      // The VALU stream, per query tile: 16 maxima in two chains (of integers: with the offset all scores are positive floats
+      // of one exponent, hidden ones negative), the row maximum, then five instructions per two scores as in `phase`.
+      auto valu = [&](int n) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        const int nt = n / 103, o = n % 103;
+        if (o < 16) {
+          auto max3 = [](int a, int b, int w) { return max(max(a, b), w); };
+          const int mt = o % 2, i = o / 2;
+          if (i == 0) top[nt][mt] = max3(now[mt][nt][0], now[mt][nt][1], now[mt][nt][2]);
+          else if (i < 7) top[nt][mt] = max3(top[nt][mt], now[mt][nt][2 * i + 1], now[mt][nt][2 * i + 2]);
+          else if (mt == 0) top[nt][0] = max3(top[nt][0], now[0][nt][15], now[1][nt][15]);
+          else top[nt][0] = max(top[nt][0], top[nt][1]);
+        } else if (o == 16) {
+          mx[nt] = __builtin_fmaf(max_with_other_half(int_bits_as_float(top[nt][0])), cj, -off);
+        } else if (o == 17) {
+          m_new[nt] = fmaxf(m_run[nt], mx[nt]);
+          mb[nt] = m_new[nt] - kLog2Top + off;       // exp2(x - m) * 448, x = (S - offset) * cj
+        } else {
+          const int q = o - 18, e0 = 2 * (q / 5), k = q % 5;
+          const int e = k == 0 ? e0 : k == 1 ? e0 - 1 : k == 2 ? e0 + 1 : k == 3 ? e0 : e0 - 2;
+          if (e < 0 || e >= 32) return;
+          if (k == 0 && e % 16 == 0) F[nt][e / 16] = int_bits_as_floats(now[e / 16][nt]);
+          if (k == 0 || k == 2) E[nt][e] = __builtin_fmaf(F[nt][e / 16][e % 16], cj, -mb[nt]);
+          else if (k == 1 || k == 3) E[nt][e] = __builtin_amdgcn_exp2f(E[nt][e]);
+          else P_new[nt][e / 4] = e % 4 == 0 ? __builtin_amdgcn_cvt_pk_fp8_f32(E[nt][e], E[nt][e + 1], any_int(), false)
+                                             : __builtin_amdgcn_cvt_pk_fp8_f32(E[nt][e], E[nt][e + 1], P_new[nt][e / 4], true);
         }
-      }
-      i32x8 p8[NT];
+      };
+      static_for<kQ8 + kP8 + NT>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        constexpr PhaseStep st = fp8_step(i, kQ8, kP8, NT);
+        if constexpr (st.kind == 1) {
+          pv8(st.n);
+          if constexpr (st.n >= 4 * (NT - 1)) { load_v8(v_next, st.n % 4, 0); load_v8(v_next, st.n % 4, 1); }
+        } else if constexpr (st.kind == 2) {
+          sum8(st.n);
+        } else {
+          qk8(st.n);
+          if constexpr (st.n >= 8 * (NT - 1)) load_k8(k_next, st.n % 2, st.n / 2 % 4);
+        }
+        constexpr int from = i == 0 ? 0 : fp8_upto(i - 1, kQ8, kP8, NT, kOps), to = fp8_upto(i, kQ8, kP8, NT, kOps);
+        static_for<to - from>([&](auto vc) __attribute__((always_inline)) { valu(from + decltype(vc)::value); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) P8[nt] = P_new[nt];
+      return __builtin_expect_with_probability(__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] || mx[NT - 1] > m_run[NT - 1]) != 0ull, 0, 0.999);
+    };
+    auto rescale8 = [&]() __attribute__((always_inline)) {
+      float alpha[NT];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const float mb = m_run[nt] - kLog2Top + off;       // exp2(x - m) * 448, x = (S - offset) * cj
+        alpha[nt] = __builtin_amdgcn_exp2f(m_run[nt] - m_new[nt]);
+        m_run[nt] = m_new[nt];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mt][nt][4 * w], cj, -mb));
-            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mt][nt][4 * w + 1], cj, -mb));
-            const float p2 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mt][nt][4 * w + 2], cj, -mb));
-            const float p3 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mt][nt][4 * w + 3], cj, -mb));
-            int word = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, 0, false);
-            word = __builtin_amdgcn_cvt_pk_fp8_f32(p2, p3, word, true);
-            p8[nt][4 * mt + w] = word;
-          }
+          for (int r = 0; r < 16; ++r) oacc[dt][nt][r] *= alpha[nt];
       }
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        i32x8 va;
+      for (int r = 0; r < 4; ++r) lacc[r] *= h == 0 ? alpha[0] : alpha[NT - 1];
+    };
+    auto block_of = [&](uint32_t raw) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane((int)raw); };
+
+    if constexpr (kListed) build_list(word_lo, word_hi); else n_pairs = tiles;
+    asm("" : "+v"(n_pairs));      // (in a vector register for the register allocator's sake: see the other passes)
+    if (n_pairs > 0) {
+      int j0 = block_of(entry(0)), j1 = block_of(entry(1));      // blocks of this step and the next
+      uint32_t ahead = entry(2);
+      float s0 = ks8[j0], s1 = ks8[j1];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) { va[w] = (int)v8[dt][0][w]; va[4 + w] = (int)v8[dt][1][w]; }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          oacc[dt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, p8[nt], oacc[dt][nt], 0, 0, 0, 0, 0, 0);
-      }
+      for (int n = 0; n < 8; ++n) load_k8(j0, n / 4, n % 4);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-        lacc[nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones8, p8[nt], lacc[nt], 0, 0, 0, 0, 0, 0);
-      fetch_v(jn_or_j);                              // (unconditional as well: every path leaves the same loads in flight,
-                                                     // so the next step waits for exactly the K8 it needs, not for everything)
-    };
-    int j = next_block();
-    if (j >= 0) {
-      fetch_k(j);
-      fetch_v(j);
-      while (true) {
-        const int jn = next_block();
-        if (j == il) step8(jn >= 0 ? jn : j, std::true_type{}); else step8(jn >= 0 ? jn : j, std::false_type{});
-        if (jn < 0) break;
-        j = jn;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) P8[nt][w] = 0;      // (the first step multiplies by zero)
+#pragma unroll
+      for (int n = 0; n < 8; ++n) v8[n / 2][n % 2] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int n = 0; n < kQ8; ++n) qk8(n);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) load_k8(j1, n / 4, n % 4);
+      // (an inner loop that a grown maximum leaves: with the rescaling inside it the compiler moves O^T about in every step)
+      for (int n = 1; n < n_pairs;) {
+        bool grew = false;
+        while (n < n_pairs && !grew) {
+          const int j2 = block_of(ahead);
+          const float s2 = ks8[j2];
+          ahead = entry(n + 2);
+          grew = step8(s0, j2, block_of((uint32_t)j0));
+          j0 = j1; j1 = j2; s0 = s1; s1 = s2;
+          ++n;
+        }
+        if (grew) rescale8();
       }
+      j0 = block_of((uint32_t)j0);
+      if (j0 == tiles - 1) hide8();
+      if (step8(s0, j0, j0)) rescale8();
+#pragma unroll
+      for (int n = 0; n < kP8; ++n) pv8(n);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) sum8(nt);
     }
     // the common tail adds the two lane halves' partial sums; here every lane already holds the whole sum
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) l_run[nt] = 0.5f * lacc[nt][0];
+    for (int nt = 0; nt < NT; ++nt) l_run[nt] = 0.5f * __shfl(lacc[0], c + 32 * nt, 64);
   } else {
   // ---- one sweep over the row's kept half-tiles ----------------------------------------------------------
   // A software pipeline over half-tiles (32 keys x all queries of the wave), two of them (a pair) per iteration.  Phase t
@@ -709,37 +790,6 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   const auto slot0 = std::integral_constant<int, 0>{};
   const auto slot1 = std::integral_constant<int, 1>{};
 
-  // ---- the row's kept blocks, in ascending order, as a list in LDS (this wave's part of the output staging area) ----
-  // BK32: with an odd number of kept half-tiles the first one comes twice, the first time emptied, so that there are whole
-  // pairs and the half-tiles of the diagonal block, the largest indices of a row, fall into the last one.
-  uint16_t* const list = o_lds + (wave * 64 + q0) * kRowPad;
-  static_assert(32 * NT * kRowPad >= kMaskWordsMax * 64 + 16, "the list of the longest row fits the staging area");
-  constexpr bool kListed = WAVES == 1;          // (the four-row workgroups are the dense kernel's: every block)
-  int n_pairs = 0;
-  bool lone = false;
-  auto build_list = [&](int lo, int hi) {
-    const uint64_t mine = lane >= lo && lane <= hi ? row_word(lane) : 0ull;
-    lone = BK32 && (__popcll(__builtin_amdgcn_ballot_w64((__popcll(mine) & 1) != 0)) & 1) != 0;
-    int n = lone ? 1 : 0, first = -1, last = 0;
-    for (uint64_t any = __builtin_amdgcn_ballot_w64(mine != 0ull); any != 0ull; any &= any - 1) {
-      const int w = __builtin_ctzll(any);
-      const uint64_t word = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, w) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), w) << 32;
-      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0));
-      if ((word >> lane) & 1) list[n + before] = (uint16_t)(w * 64 + lane);
-      if (first < 0) first = w * 64 + __builtin_ctzll(word);
-      last = w * 64 + 63 - __builtin_clzll(word);
-      n += __popcll(word);
-    }
-    if (lone && lane == 0) list[0] = (uint16_t)first;
-    if (lane < 8) list[n + lane] = (uint16_t)last;      // (the loads run up to two pairs ahead, the list is read three ahead)
-    n_pairs = BK32 ? n >> 1 : n;
-  };
-  auto entry = [&](int n) __attribute__((always_inline)) -> uint32_t {      // of pair n
-    if constexpr (!kListed) return (uint32_t)min(n, tiles - 1);
-    else if constexpr (BK32) return *(const uint32_t*)(list + 2 * n);
-    else return list[n];
-  };
   auto pair_of = [&](uint32_t raw) __attribute__((always_inline)) -> Pair {
     const uint32_t w = kListed ? (uint32_t)__builtin_amdgcn_readfirstlane((int)raw) : raw;
     Pair p;

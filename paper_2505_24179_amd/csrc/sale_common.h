@@ -105,6 +105,19 @@ __device__ __forceinline__ f32x4 int_bits_as_floats(i32x4 x) {      // (the same
   return y;
 }
 
+__device__ __forceinline__ f32x16 int_bits_as_floats(i32x16 x) {
+  f32x16 y = __builtin_bit_cast(f32x16, x);
+  asm("" : "+v"(y));
+  return y;
+}
+
+// Some value, for an operand that does not matter: no instruction.
+__device__ __forceinline__ int any_int() {
+  int x;
+  asm volatile("" : "=v"(x));      // (volatile: one register for all of them would be copied for each)
+  return x;
+}
+
 // max(x, x of lane ^ 32) without going through LDS: v_permlane32_swap exchanges the upper 32 lanes of its
 // first register with the lower 32 lanes of its second, so with x in both it leaves the lower half's values in
 // both halves of one register and the upper half's in the other.  Written as inline assembly on purpose: through
