@@ -1162,7 +1162,12 @@ __global__ __launch_bounds__(1024) void balance_kernel(Geo g, const uint64_t* __
 }
 
 constexpr int kLongRow = 192;        // rows keeping more than this (12K tokens) are swept window by window
-constexpr int kWindowWords = 2;      // window width in mask words of 64 x 64 keys: 8K tokens, 4 MB of K', V' per KV head
+// Window width in mask words of 64 x 64 keys.  bf16: 8K tokens, 4 MB of K', V' per KV head.  The 8-bit passes read three
+// quarters or half as much per block and shorter steps pay more for every further window: 16K tokens.  Attention call, 8K / 12K /
+// 16K / 32K tokens: FP8 64K 5.39 / 5.26 / 5.19 / 5.36 ms, 128K 20.5 / 19.7 / 19.4 / 20.3; int8 25K 1.33 / 1.28 / 1.26 / 1.25, 64K
+// 6.29 / 6.26 / 6.30 / 6.57, 128K 24.1 / 23.8 / 23.8 / 26.0, 64K with 32-key blocks 5.12 / 5.05 / 4.97 / 5.22; bf16 128K 29.3 /
+// 29.5 / 30.2 / 39.0, 64K with 32-key blocks 5.87 / 5.87 / 6.02 / 6.90.
+constexpr int kWindowWords = 2, kWindowWords8 = 4;
 constexpr int kWindowMinWords = 4;   // sequences of up to 16K tokens use one sweep per row
 
 namespace {
@@ -1224,7 +1229,7 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
   // Short rows keep little besides the sink, the local band and the heavy columns everyone shares.
   // They are dealt over the window launches: launch number n ends with ranks n, n + launches, ... of every
   // KV head's sorted list (the tail of the grid), which fill the chip while its last long rows finish.
-  const int step = kWindowWords * f, launches = (g.words + step - 1) / step;
+  const int step = (QK8 ? kWindowWords8 : kWindowWords) * f, launches = (g.words + step - 1) / step;
   const int tail_wgs = ((units + launches - 1) / launches) * g.n_kvh;
   window_load_kernel<<<dim3((unsigned)(launches * g.n_kvh)), dim3(1024), 0, st>>>(g, mask, slot_of, order, step, f, load,
                                                                                  assign);
