@@ -8,7 +8,8 @@ from __future__ import annotations
 
 import ctypes
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, fields
+from functools import cached_property
 
 import torch
 
@@ -73,6 +74,26 @@ class Params:
             cp._offsets = offsets      # (the host array lives as long as the struct)
         return cp
 
+    # What follows from the fields alone is made once: a call of a small layer is as long as its host side.
+    @cached_property
+    def _contiguous(self):
+        """The C struct of contiguous tensors, as an argument.  (The library reads it during the call and never writes it, so
+        calls and threads may share it.)"""
+        return ctypes.byref(self.c())
+
+    @cached_property
+    def _ws_bytes(self) -> dict:
+        return {}
+
+    @cached_property
+    def _numels(self):
+        """Elements of Q (and O), of K (and V)."""
+        n = self.batch * self.seq_len * self.head_dim
+        return self.n_q_heads * n, self.n_kv_heads * n
+
+    def __reduce__(self):      # (copies and pickles carry the fields, not what was made from them)
+        return type(self), tuple(getattr(self, f.name) for f in fields(self))
+
     @property
     def n_q(self) -> int:
         return self.seq_len // self.block_q
@@ -133,6 +154,9 @@ def _expect(name: str, t, dtype, numel: int, optional: bool = False):
     """Host-side check of one tensor argument before anything is launched: the C ABI takes raw device pointers
     of contiguous buffers, so a wrong dtype, a strided view or a short buffer would be read or written out of
     bounds on the GPU."""
+    if t is not None and t.dtype in (dtype if isinstance(dtype, tuple) else (dtype,)) and t.numel() == numel and t.is_cuda and \
+            t.is_contiguous():
+        return
     if t is None:
         if optional:
             return
@@ -166,6 +190,25 @@ def _expect_bhnd(name: str, t, p: "Params", heads: int):
     _expect(name, t, torch.bfloat16, p.batch * heads * p.seq_len * p.head_dim)
 
 
+_NO = object()
+
+
+def _args(p: "Params", q, k, v=_NO, o=_NO):
+    """Checks Q, K, V, O as _expect_bhnd does -> the C struct for them, as an argument."""
+    nq, nk = p._numels
+    plain = True
+    for name, t, numel, heads in (("q", q, nq, p.n_q_heads), ("k", k, nk, p.n_kv_heads), ("v", v, nk, p.n_kv_heads),
+                                  ("o", o, nq, p.n_q_heads)):
+        if t is _NO:
+            continue
+        if t is None or t.dtype is not torch.bfloat16 or t.numel() != numel or not t.is_cuda or not t.is_contiguous():
+            _expect_bhnd(name, t, p, heads)
+            plain = False
+    if plain:
+        return p._contiguous
+    return ctypes.byref(p.c(*(None if t is _NO else t for t in (q, k, v, o))))
+
+
 def _expect_ws(ws):
     """-> the workspace's size in BYTES (whatever its dtype).  Size and alignment are the library's to judge
     (SALE_ERR_WORKSPACE)."""
@@ -189,7 +232,10 @@ def raw():
 
 
 def workspace_bytes(p: Params, which: int) -> int:
-    return int(_lib.sale_workspace_bytes(ctypes.byref(p.c()), which))
+    n = p._ws_bytes.get(which)
+    if n is None:
+        n = p._ws_bytes[which] = int(_lib.sale_workspace_bytes(p._contiguous, which))
+    return n
 
 
 def status_string(status: int) -> str:
@@ -206,12 +252,13 @@ def quantize_qk(p: Params, q: torch.Tensor, k: torch.Tensor, out=None):
         ks = torch.empty(p.batch, p.n_kv_heads, p.seq_len // p.block_k, dtype=torch.float32, device=dev)
     else:
         q4, k4, qs, ks = out
-    nq, nk = _qkv_numel(p)
-    _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads)
-    _expect("q4", q4, torch.uint8, nq // 2); _expect("k4", k4, torch.uint8, nk // 2)
-    _expect("q_scale", qs, torch.float32, p.batch * p.n_q_heads * (p.seq_len // p.block_q))
-    _expect("k_scale", ks, torch.float32, p.batch * p.n_kv_heads * (p.seq_len // p.block_k))
-    _check(_lib.sale_quantize_qk(ctypes.byref(p.c(q, k)), _ptr(q), _ptr(k), _ptr(q4), _ptr(k4), _ptr(qs), _ptr(ks), _stream()))
+    args = _args(p, q, k)
+    if out is not None:      # (what was allocated above fits)
+        nq, nk = p._numels
+        _expect("q4", q4, torch.uint8, nq // 2); _expect("k4", k4, torch.uint8, nk // 2)
+        _expect("q_scale", qs, torch.float32, p.batch * p.n_q_heads * (p.seq_len // p.block_q))
+        _expect("k_scale", ks, torch.float32, p.batch * p.n_kv_heads * (p.seq_len // p.block_k))
+    _check(_lib.sale_quantize_qk(args, _ptr(q), _ptr(k), _ptr(q4), _ptr(k4), _ptr(qs), _ptr(ks), _stream()))
     return q4, k4, qs, ks
 
 
@@ -229,18 +276,19 @@ def select(p: Params, q, k, q4, k4, q_scale, k_scale, tau: torch.Tensor, want_st
         l = torch.empty_like(m)
     if ws is None:
         ws = torch.empty(max(1, workspace_bytes(p, WS_SELECT)), dtype=torch.uint8, device=dev)
-    nq, nk = _qkv_numel(p)
+    nq, nk = p._numels
     est16 = bool(p.flags & FLAG_SELECT_16BIT)          # the 16-bit estimate does not read the codes
-    _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads)
+    args = _args(p, q, k)
     _expect("q4", q4, torch.uint8, nq // 2, optional=est16); _expect("k4", k4, torch.uint8, nk // 2, optional=est16)
     _expect("q_scale", q_scale, torch.float32, p.batch * p.n_q_heads * p.n_q, optional=est16)
     _expect("k_scale", k_scale, torch.float32, p.batch * p.n_kv_heads * p.n_k, optional=est16)
     if tau.numel() not in (1, p.n_q_heads):
         raise ValueError(f"tau: expected 1 or {p.n_q_heads} thresholds, got {tau.numel()}")
     _expect("tau", tau, torch.float32, tau.numel())
-    _expect("block_mask", mask, (torch.int64, torch.uint64), p.batch * p.n_q_heads * p.n_q * p.words)
-    _expect("row_counts", counts, torch.int32, p.batch * p.n_q_heads * p.n_q)
-    _check(_lib.sale_select(ctypes.byref(p.c(q, k)), _ptr(q), _ptr(k), _ptr(q4), _ptr(k4), _ptr(q_scale), _ptr(k_scale),
+    if out is not None:
+        _expect("block_mask", mask, (torch.int64, torch.uint64), p.batch * p.n_q_heads * p.n_q * p.words)
+        _expect("row_counts", counts, torch.int32, p.batch * p.n_q_heads * p.n_q)
+    _check(_lib.sale_select(args, _ptr(q), _ptr(k), _ptr(q4), _ptr(k4), _ptr(q_scale), _ptr(k_scale),
                             _ptr(tau), tau.numel(), _ptr(mask), _ptr(counts), _ptr(m), _ptr(l),
                             _ptr(ws), _expect_ws(ws), _stream()))
     return mask, counts, m, l
@@ -273,12 +321,10 @@ def sparse_attn(p: Params, q, k, v, block_mask, row_counts=None, want_lse: bool 
     lse = torch.empty(p.batch, p.n_q_heads, p.seq_len, dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
         ws = torch.empty(max(1, workspace_bytes(p, WS_SPARSE_ATTN)), dtype=torch.uint8, device=q.device)
-    nq, nk = _qkv_numel(p)
-    _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads); _expect_bhnd("v", v, p, p.n_kv_heads)
-    _expect_bhnd("o", o, p, p.n_q_heads)
+    args = _args(p, q, k, v, o)
     _expect("block_mask", block_mask, (torch.int64, torch.uint64), p.batch * p.n_q_heads * p.n_q * p.words)
     _expect("row_counts", row_counts, torch.int32, p.batch * p.n_q_heads * p.n_q, optional=True)
-    _check(_lib.sale_sparse_attn(ctypes.byref(p.c(q, k, v, o)), _ptr(q), _ptr(k), _ptr(v), _ptr(block_mask), _ptr(row_counts),
+    _check(_lib.sale_sparse_attn(args, _ptr(q), _ptr(k), _ptr(v), _ptr(block_mask), _ptr(row_counts),
                                  _ptr(o), _ptr(lse), _ptr(ws), _expect_ws(ws), _stream()))
     return o, lse
 
@@ -289,10 +335,8 @@ def dense_attn(p: Params, q, k, v, want_lse: bool = False, out=None, ws=None):
     lse = torch.empty(p.batch, p.n_q_heads, p.seq_len, dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
         ws = torch.empty(max(1, workspace_bytes(p, WS_DENSE_ATTN)), dtype=torch.uint8, device=q.device)
-    nq, nk = _qkv_numel(p)
-    _expect_bhnd("q", q, p, p.n_q_heads); _expect_bhnd("k", k, p, p.n_kv_heads); _expect_bhnd("v", v, p, p.n_kv_heads)
-    _expect_bhnd("o", o, p, p.n_q_heads)
-    _check(_lib.sale_dense_attn(ctypes.byref(p.c(q, k, v, o)), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
+    args = _args(p, q, k, v, o)
+    _check(_lib.sale_dense_attn(args, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
                                 _ptr(ws), _expect_ws(ws), _stream()))
     return o, lse
 
