@@ -5,30 +5,37 @@
 // places: what a row costs besides its blocks (start, Q in, O out) is then paid one after the other, twice as often as
 // with whole rows, and the operand loads, twice as many per FLOP, begin to count.  So the limit goes by the longest row.
 // Attention call, us, one wave per row -> two (group of 4 where the rows allow it; rows of one batch, all alike):
-//                        rows  512             768             1024            1280            1536            2048
-//   sparse bf16,    1 block    12.5 -> 11.3    14.8 -> 16.7    17.2 -> 18.3    24.3 -> 23.1    25.8 -> 25.7    30.7 -> 30.7
-//                   4 blocks   18.0 -> 14.9    21.3 -> 20.0    23.7 -> 23.2    26.9 -> 29.0    30.0 -> 30.8    35.6 -> 39.2
-//                   8          21.0 -> 16.3    24.1 -> 22.9    26.8 -> 26.5    29.6 -> 32.8    33.8 -> 35.0    42.7 -> 43.4
-//                  16          35.4 -> 24.8    41.2 -> 30.4    41.3 -> 34.1    46.0 -> 43.2    44.8 -> 45.7    53.0 -> 57.4
-//                  32          58.1 -> 40.6    63.1 -> 45.8    62.1 -> 48.7    68.2 -> 62.1    72.0 -> 70.8    77.9 -> 88.0
-//                  64          98.7 -> 66.1     103 -> 71.1     108 -> 74.5     111 -> 89.0     115 -> 98.1     121 -> 128
-//   32-key blocks,  8          21.9 -> 16.6    25.2 -> 22.6    28.0 -> 25.1    31.7 -> 30.7    35.2 -> 32.8    39.8 -> 40.3
-//                  16          35.4 -> 24.3    40.8 -> 29.6    40.8 -> 33.1    45.3 -> 42.0    43.7 -> 42.8    50.8 -> 53.3
-//                  32          56.5 -> 38.9    60.0 -> 42.1    59.3 -> 43.5    73.2 -> 53.8    75.4 -> 61.0    74.4 -> 75.5
-//                  64           103 -> 67.6     105 -> 70.6     108 -> 72.2     109 -> 73.8     113 -> 76.2     116 -> 98.7
-//   sparse int8,   16          47.3 -> 36.3    53.6 -> 43.0    55.5 -> 48.4    60.5 -> 57.6    60.4 -> 61.1    70.9 -> 74.4
-//                  64           107 -> 74.6     110 -> 77.2     114 -> 81.4     118 -> 95.3     123 -> 104      128 -> 133
-//   sparse FP8,     8          39.8 -> 36.4    45.9 -> 46.7    49.6 -> 51.7    55.3 -> 58.9    59.6 -> 61.9    67.6 -> 72.1
-//                  16          52.3 -> 45.9    59.9 -> 52.9    62.2 -> 58.8    65.7 -> 67.7    66.5 -> 72.4    76.4 -> 85.9
-//                  32          74.2 -> 61.8    79.4 -> 67.1    82.1 -> 73.4    86.4 -> 85.8    88.0 -> 94.3    97.6 -> 114
-//   dense bf16,     4          17.8 -> 14.3    20.6 -> 19.7    22.7 -> 22.6    26.6 -> 28.7    28.6 -> 30.6    34.5 -> 38.4
-//                   8          25.6 -> 19.1    27.8 -> 22.6    29.8 -> 26.5    30.2 -> 33.2    33.6 -> 36.4    40.3 -> 44.3
-//                  16          38.7 -> 26.5    43.2 -> 32.3    43.1 -> 35.3    47.4 -> 47.6    45.9 -> 50.2    54.4 -> 60.1
-//                  64           111 -> 73.9     113 -> 81.5     118 -> 90.9     121 -> 120      127 -> 138      144 -> 167
-//   dense FP8,     16          54.1 -> 46.1    59.3 -> 52.9    62.7 -> 58.7    66.5 -> 70.3    67.1 -> 75.3    77.8 -> 89.2
-//                  64           121 -> 95.2     124 -> 99.6     127 -> 109      130 -> 135      133 -> 153      149 -> 185
-// (Dense int8 as dense bf16, at 16 blocks and 1280 rows 63.2 -> 61.9.  The limits end where the form was measured and tested
-// first: sparse rows of 64 blocks and more would gain further, 2048 rows of 128 blocks 214 -> 178 us in bf16, 216 -> 199 in FP8.)
+//                        rows  512              768              1024             1280             1536             2048
+//   sparse bf16,     1 block  14.7 -> 12.8     16.7 -> 19       19.5 -> 21.1     27.5 -> 27.5     29.6 -> 29.8     34.3 -> 35.6
+//                    4        18.2 -> 15.1     21.7 -> 22       24.7 -> 24.8     30 -> 31.6       33.4 -> 33.6     38.9 -> 43.2
+//                    8        19.8 -> 16.1     22.8 -> 24.4     26 -> 27.8       32.6 -> 35.4     35.9 -> 37.1     44.8 -> 46.7
+//                   16        29.4 -> 22.3     35 -> 29.6       35.7 -> 33.6     40.2 -> 43.1     42 -> 45.8       49.2 -> 57.9
+//                   32        48.7 -> 36       53.7 -> 42.1     53.1 -> 46.4     58.9 -> 60.4     64.5 -> 66.2     72.4 -> 85.6
+//                   64        81.2 -> 57       83.7 -> 63.9     90.1 -> 70.6     95.9 -> 84.4     100 -> 93.8      103 -> 118
+//                  128        154 -> 101       -                164 -> 113       -                177 -> 130       184 -> 162
+//   32-key blocks,   8 blocks 20 -> 16.5       22.4 -> 23.8     25.5 -> 26       31.8 -> 33.5     34.8 -> 35.2     39.2 -> 43.5
+//                   16        28.2 -> 21.7     34.3 -> 29.5     34.4 -> 32.8     39.7 -> 43.4     39.6 -> 44.6     48.1 -> 56.7
+//                   32        46.2 -> 34       50.9 -> 38.9     50.3 -> 42.9     61.2 -> 54.7     63.4 -> 61       65.1 -> 75.2
+//                   64        82 -> 55.6       84.2 -> 60.2     89.2 -> 63.7     91.3 -> 68.8     94.3 -> 75.5     97.1 -> 94.1
+//                  128        155 -> 96.8      -                163 -> 106       -                170 -> 116       176 -> 120
+//   sparse int8,    16 blocks 41.4 -> 34.5     47.8 -> 43       50.2 -> 47.6     56.3 -> 58.9     58.6 -> 61.8     68.4 -> 75.2
+//                   64        86.5 -> 64.1     89.5 -> 70.8     94.3 -> 76.7     102 -> 91.4      106 -> 101       112 -> 122
+//   sparse FP8,      1 block  36.1 -> 33       42.3 -> 42.4     47.1 -> 45.8     59.7 -> 54       61 -> 55.9       67.7 -> 65
+//                    8        41.6 -> 35.6     48.2 -> 46.9     52 -> 50.9       60.6 -> 59.8     64.4 -> 62       73.6 -> 73.6
+//                   16        52.2 -> 41.8     59.2 -> 51.1     61.6 -> 56.2     65.9 -> 65.6     69.4 -> 69.2     80 -> 81.3
+//                   32        68.7 -> 51.7     74.2 -> 57.9     76.6 -> 65       80.5 -> 76.6     81.9 -> 82.3     94.9 -> 98.4
+//                   64        98.6 -> 69.8     102 -> 73.3      105 -> 81.5      108 -> 91.4      110 -> 101       119 -> 123
+//   dense bf16,      1 block  15.4 -> 12.2     15.9 -> 17.3     18.1 -> 19.9     29 -> 25.1       29.3 -> 27.9     32.7 -> 32.7
+//                    4        19.5 -> 14.9     21.7 -> 21.1     24 -> 24         30.5 -> 30.2     31.8 -> 32.3     38.1 -> 41.2
+//                    8        23.7 -> 17.6     26.1 -> 23.5     28.5 -> 27.1     33.3 -> 35       36.2 -> 37.1     41.6 -> 46.1
+//                   16        33.3 -> 24.1     37.8 -> 31.4     37.7 -> 34.5     42.3 -> 47.9     44.5 -> 49.7     52.6 -> 61
+//                   32        54.4 -> 39.2     57.1 -> 45.8     57.6 -> 49.3     62.6 -> 68.6     65.6 -> 77.3     75.9 -> 91.6
+//                   64        92.5 -> 65.3     92.9 -> 74.2     101 -> 84.3      105 -> 114       110 -> 130       127 -> 155
+//                  128        168 -> 116       -                180 -> 151       -                201 -> 240       232 -> 286
+//   dense FP8,      16 blocks 50.8 -> 39.8     59.1 -> 48.9     59.9 -> 54.1     63.1 -> 64.4     67.5 -> 67.7     76.6 -> 80.4
+//                   64        99.4 -> 69.8     103 -> 74.9      107 -> 84.9      108 -> 104       111 -> 115       127 -> 138
+// (Dense int8 as dense bf16, 5 % less at the limits.  Rows of 128 blocks and more would gain beyond the limits, which end where
+// the form was first measured and tested: sparse, 2048 rows 184 -> 162 us in bf16, 178 -> 153 in FP8.)
 #pragma once
 
 namespace sale {
@@ -37,12 +44,12 @@ struct RowSplitLimit {
   int blocks;                                                  // longest row: at least this many 64-key blocks
   int sparse, sparse32, sparse_fp8, dense, dense_fp8;          // rows up to which two waves per row are taken
 };
-// (the last rows at which nine of ten calls of that kind and length were no slower, of 16500 drawn ones with 1 to 64 heads)
+// (from the table above; between its lengths and rows the figures of the calls that tests/test_row_split.py holds)
 constexpr RowSplitLimit kRowSplitLimits[] = {
-    {48, 1536, 2080, 1280, 1280, 1024}, {40, 1536, 1920, 1280, 1280, 1024}, {32, 1536, 1792, 1280, 1280, 1024},
-    {24, 1408, 1664, 1152, 1280, 1024}, {16, 1280, 1536, 1152, 1280, 1024}, {12, 1216, 1408, 1024, 1024, 1024},
-    {8, 960, 1152, 704, 1024, 1024},    {5, 832, 832, 704, 832, 896},       {4, 768, 768, 640, 704, 768},
-    {3, 576, 704, 512, 512, 512},       {0, 512, 512, 512, 512, 512}};
+    {200, 1536, 2080, 1280, 1280, 1152}, {64, 1536, 2080, 1280, 1152, 1152}, {48, 1408, 1920, 1280, 1152, 1152},
+    {32, 1152, 1792, 1280, 1152, 1152},  {24, 1088, 1408, 1280, 1088, 1152}, {16, 1024, 1088, 1280, 1024, 1152},
+    {12, 832, 832, 1024, 1024, 1152},    {8, 640, 576, 960, 1024, 1152},     {4, 704, 640, 960, 960, 1152},
+    {2, 512, 512, 960, 512, 1152},       {0, 512, 512, 512, 512, 512}};
 
 struct RowSplitCall {
   long rows;         // 64-row blocks of all heads and batch entries
