@@ -44,6 +44,9 @@
 //   is balanced over the XCDs by a table that moves rows of over-loaded heads to
 //   the lanes of under-loaded ones, and the short rows ride at the tail of the
 //   window launches (details at launch_sparse_rows and balance_kernel).
+#include <type_traits>
+
+#include "pass8.h"
 #include "row_split.h"
 #include "sale_common.h"
 
@@ -129,18 +132,24 @@ struct OrderJob {
 // copies nobody reads the attention call with int8 takes 1496 instead of 1512 us at 25K, with FP8 7446 instead of 7544
 // us at 64K.  (As template parameters: a run-time test kept the loads of V from being in flight with those of K, 28.0
 // instead of 27.5 us in the dense call of 1K tokens.)
+// Without the copy of K the first pass over the 8-bit operands follows in the same launch, from workgroup `tiles` on.
+struct Then8 { int tiles; Pass8 pass; };
+struct NoPass8 {};
 template <bool K, bool V>
-__global__ __launch_bounds__(256) void rearrange_kv_kernel(Geo g, OrderJob job, const uint16_t* __restrict__ k,
+__global__ __launch_bounds__(256) void rearrange_kv_kernel(Geo g, OrderJob job, std::conditional_t<K, NoPass8, Then8> then,
+                                                           const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v,
                                                            u32x4* __restrict__ kp, u32x4* __restrict__ vp,
                                                            int* __restrict__ slot_counter) {
-  __shared__ union { uint16_t sv[64 * (kHeadDim + 2)]; int bin[kOrderBins]; } lds;
+  __shared__ union { uint16_t sv[64 * (kHeadDim + 2)]; int bin[kOrderBins]; double pass[128]; } lds;
   if ((int)blockIdx.x < job.heads) {
     order_units(g, blockIdx.x, lds.bin, job.row_counts, job.order, nullptr, 0, 0, nullptr);
     return;
   }
   uint16_t* const sv = lds.sv;
   const int block = (int)blockIdx.x - job.heads, seq = g.seq;
+  if constexpr (!K)
+    if (block >= then.tiles) { then.pass.run(g, block - then.tiles, lds.pass); return; }
   const Strided &lk = g.sk, &lv = g.sv;
   const int tid = threadIdx.x;
   if (slot_counter && block == 0 && tid == 0) *slot_counter = 0;      // (for order_units_kernel, next on the stream)
@@ -1349,26 +1358,26 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const bool sort = !windows && (counts || (by_length && halves));
   const OrderJob job = {sort ? g.n_kvh : 0, mask ? row_counts : nullptr, order_at};
   int32_t* const order = sort || windows ? order_at : nullptr;
-  const dim3 kv_tiles((unsigned)(job.heads + g.n_kvh * (g.seq / 64)));
-#define SALE_REARRANGE_ARGS g, job, (const uint16_t*)k, (const uint16_t*)v, kp, vp, w.slot_counter
-  if (!qk8) rearrange_kv_kernel<true, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
-  else if (!pv8) rearrange_kv_kernel<false, true><<<kv_tiles, dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);
-  else if (w.slot_counter) rearrange_kv_kernel<false, false><<<dim3(job.heads + 1u), dim3(256), 0, st>>>(SALE_REARRANGE_ARGS);      // (the sort, and the counter's clearing)
+  Int8Operands w8 = {};
+  Fp8Operands wv = {};
+  if (qk8) w8 = carve_int8_operands(p, (void*)w.ops8);
+  if (pv8) wv = carve_fp8_operands(p, (void*)w.ops_fp8);
+  const Pass8 pass = make_pass8(p, q, k, v, qk8 ? &w8 : nullptr, pv8 ? &wv : nullptr);
+  // (with FP8 V there is nothing to copy: one workgroup, which clears the slot counter)
+  const int tiles = pv8 ? (w.slot_counter ? 1 : 0) : g.n_kvh * (g.seq / 64);
+  const dim3 first((unsigned)(job.heads + tiles + pass.blocks()));
+  const Then8 then = {tiles, pass};
+#define SALE_REARRANGE_ARGS (const uint16_t*)k, (const uint16_t*)v, kp, vp, w.slot_counter
+  if (!qk8) rearrange_kv_kernel<true, true><<<first, dim3(256), 0, st>>>(g, job, NoPass8{}, SALE_REARRANGE_ARGS);
+  else if (!pv8) rearrange_kv_kernel<false, true><<<first, dim3(256), 0, st>>>(g, job, then, SALE_REARRANGE_ARGS);
+  else rearrange_kv_kernel<false, false><<<first, dim3(256), 0, st>>>(g, job, then, SALE_REARRANGE_ARGS);
 #undef SALE_REARRANGE_ARGS
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
   Qk8 q8o = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (qk8) {
-    const Int8Operands w8i = carve_int8_operands(p, (void*)w.ops8);
-    int rc = launch_int8_operands(p, q, k, w8i, pv8 ? 32 : 16, st);
+    const int rc = launch_operands8(p, k, v, &w8, pv8 ? &wv : nullptr, pv8 ? 32 : 16, st);
     if (rc != SALE_OK) return rc;
-    q8o = {w8i.q8, (const u32x4*)w8i.k8, w8i.q_scale, w8i.k_scale, w8i.k_mean, nullptr, nullptr};
-    if (pv8) {
-      const Fp8Operands w8 = carve_fp8_operands(p, (void*)w.ops_fp8);
-      rc = launch_fp8_operands(p, v, w8, true, st);
-      if (rc != SALE_OK) return rc;
-      q8o.v8p = (const u32x4*)w8.v8;
-      q8o.v_scale = w8.v_scale;
-    }
+    q8o = {w8.q8, (const u32x4*)w8.k8, w8.q_scale, w8.k_scale, w8.k_mean, (const u32x4*)wv.v8, wv.v_scale};
   }
   const uint16_t* qq = (const uint16_t*)q;
   const bf16x8 *kpp = (const bf16x8*)kp, *vpp = (const bf16x8*)vp;

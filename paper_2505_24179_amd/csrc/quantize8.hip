@@ -3,34 +3,27 @@
 // symmetric 8-bit codes in [-127, 127] with one fp32 scale per (head, 64-row block) - the arithmetic of the
 // 4-bit quantizer with 127 in place of 7.
 //
-// All three kernels are HBM-bound and tiny next to the attention they feed (K is read twice, Q once).
-#include "sale_common.h"
+// HBM-bound and tiny next to the attention they feed (K is read twice, Q once), so at short lengths their launches are what they
+// cost.  Three launches: what needs nothing else (Pass8, beside the attention call's own first launch), the small reductions of
+// its partial results, and what needs those.  As five launches (eight with FP8 V) the whole attention call took, us, before ->
+// now: 64 tokens x 1 head int8 17.4 -> 13.7, FP8 22.5 -> 14.7; 1024 rows of 2K tokens 58 -> 53, 65 -> 52; 4160 tokens x 32 heads
+// 120 -> 114, 125 -> 113; 64K tokens the same.
+#include "pass8.h"
 
 namespace sale {
 
-// Exact column sums: bf16 values summed in fp64 lose nothing for any realistic value range, so the result
-// does not depend on the order of the additions.  One workgroup per (KV head, 64-row tile): partial[c].
-__global__ __launch_bounds__(256) void ksum_kernel(const uint16_t* __restrict__ k, Strided lk, int tiles_per_head,
-                                                   double* __restrict__ partial) {
-  __shared__ double other[128];
-  const int c = threadIdx.x & 127, phase = threadIdx.x >> 7;
-  const uint16_t* rows = k + row_off(lk, blockIdx.x / tiles_per_head, (blockIdx.x % tiles_per_head) * 64 + phase * 32) + c;
-  double s = 0.0;
-#pragma unroll 8
-  for (int r = 0; r < 32; ++r) s += (double)bf16_bits_to_float(rows[(size_t)r * lk.st]);
-  if (phase == 1) other[c] = s;
-  __syncthreads();
-  if (phase == 0) partial[(size_t)blockIdx.x * 128 + c] = s + other[c];
+__global__ __launch_bounds__(256) void pass8_kernel(Geo g, Pass8 pass) {
+  __shared__ double lds[128];
+  pass.run(g, blockIdx.x, lds);
 }
 
 // mean[kvh][c] = fp32(sum over the head's tiles / N).  One workgroup of 1024 threads per KV head: 8 threads per
 // channel take every 8th tile each, four loads in flight, and meet in LDS.  (The partial sums are fp64 sums of
 // bf16 values: exact for any data whose exponents span less than 53 - 8 - log2(N) bits, so the order is free.)
-__global__ __launch_bounds__(1024) void kmean_kernel(const double* __restrict__ partial, int tiles, int seq,
-                                                     float* __restrict__ mean) {
-  __shared__ double part[8][128];
+__device__ __forceinline__ void kmean_head(const double* __restrict__ partial, int tiles, int seq, int head,
+                                           float* __restrict__ mean, double (*part)[128]) {
   const int c = threadIdx.x & 127, ph = threadIdx.x >> 7;
-  const double* p = partial + (size_t)blockIdx.x * tiles * 128 + c;
+  const double* p = partial + (size_t)head * tiles * 128 + c;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   int t = ph;
   for (; t + 24 < tiles; t += 32) {
@@ -43,78 +36,7 @@ __global__ __launch_bounds__(1024) void kmean_kernel(const double* __restrict__ 
     double s = 0.0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += part[i][c];
-    mean[blockIdx.x * 128 + c] = (float)(s / (double)seq);
-  }
-}
-
-// One workgroup per (head, 64-row block).  Thread t holds 32 channels (32 (t % 4) ..) of row t / 4.
-// FRAG: codes go out in the operand order of the keys-as-rows product,
-//   16: of v_mfma_i32_16x16x64_i8, [head][tile][kt 0..3][ks 0..1][lane 0..63] 16 bytes: channels 64ks + 16(lane/16) .. of
-//       key row 16kt + lane%16;
-//   32: of v_mfma_i32_32x32x32_i8, [head][tile][mt 0..1][ks 0..3][lane 0..63] 16 bytes: channels 32ks + 16(lane/32) .. of
-//       key row 32mt + lane%32;
-//   0: row-major [head][row][128 bytes].
-template <int FRAG>
-__global__ __launch_bounds__(256) void quantize8_kernel(const uint16_t* __restrict__ x, Strided lx,
-                                                        const float* __restrict__ mean, int tiles_per_head,
-                                                        int8_t* __restrict__ codes, float* __restrict__ scale) {
-  __shared__ float wave_max[4];
-  const int t = threadIdx.x, r = t >> 2, cq = t & 3;
-  const size_t blk = blockIdx.x;
-  const u32x4* src = (const u32x4*)(x + row_off(lx, (int)(blk / tiles_per_head), (int)(blk % tiles_per_head) * 64 + r) + 32 * cq);
-  float v[32];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const u32x4 w = __builtin_nontemporal_load(&src[i]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[8 * i + 2 * e] = __builtin_bit_cast(float, w[e] << 16);
-      v[8 * i + 2 * e + 1] = __builtin_bit_cast(float, w[e] & 0xFFFF0000u);
-    }
-  }
-  if (mean) {
-    const float* m = mean + (blk / tiles_per_head) * 128 + 32 * cq;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) v[e] = v[e] - m[e];
-  }
-  float amax = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 32; ++e) amax = fmaxf(amax, fabsf(v[e]));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-  if ((t & 63) == 0) wave_max[t >> 6] = amax;
-  __syncthreads();
-  amax = fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]));
-  const bool zero = amax == 0.0f;
-  const float inv = zero ? 0.0f : 127.0f / amax;      // IEEE division, as in the definition
-  if (t == 0) scale[blk] = zero ? 1.0f : amax / 127.0f;
-  uint32_t packed[8];
-#pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    uint32_t word = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const float y = rintf(v[4 * w + b] * inv);
-      const int code = (int)fminf(fmaxf(y, -127.0f), 127.0f);
-      word |= (uint32_t)(code & 0xFF) << (8 * b);
-    }
-    packed[w] = word;
-  }
-  u32x4 lo, hi;
-  lo[0] = packed[0]; lo[1] = packed[1]; lo[2] = packed[2]; lo[3] = packed[3];
-  hi[0] = packed[4]; hi[1] = packed[5]; hi[2] = packed[6]; hi[3] = packed[7];
-  if (FRAG == 16) {
-    u32x4* dst = (u32x4*)codes + blk * 512 + ((r >> 4) * 2 + (cq >> 1)) * 64 + 32 * (cq & 1) + (r & 15);
-    dst[0] = lo;      // channels 32cq .. +15   -> lanes 32 (cq % 2) .. +15
-    dst[16] = hi;     // channels 32cq+16 .. +31 -> the next 16 lanes
-  } else if (FRAG == 32) {
-    u32x4* dst = (u32x4*)codes + blk * 512 + ((r >> 5) * 4 + cq) * 64 + (r & 31);
-    dst[0] = lo;      // channels 32cq .. +15   -> lanes 0..31
-    dst[32] = hi;     // channels 32cq+16 .. +31 -> lanes 32..63
-  } else {
-    u32x4* dst = (u32x4*)(codes + (blk * 64 + r) * kHeadDim + 32 * cq);
-    dst[0] = lo;
-    dst[1] = hi;
+    mean[head * 128 + c] = (float)(s / (double)seq);
   }
 }
 
@@ -123,27 +45,12 @@ __global__ __launch_bounds__(256) void quantize8_kernel(const uint16_t* __restri
 //   amax = max over the head's N tokens of |v|;  scale = amax / 448;  value = fp8(v * (448 / amax))
 // (IEEE fp32, one multiply, round to nearest even; an all-zero channel gets scale 1 and values 0).
 // ---------------------------------------------------------------------------
-// Per (KV head, 64-row tile): partial[c] = max |v| over the tile's rows.
-__global__ __launch_bounds__(256) void vamax_kernel(const uint16_t* __restrict__ v, Strided lv, int tiles_per_head,
-                                                    float* __restrict__ partial) {
-  __shared__ float other[128];
-  const int c = threadIdx.x & 127, phase = threadIdx.x >> 7;
-  const uint16_t* rows = v + row_off(lv, blockIdx.x / tiles_per_head, (blockIdx.x % tiles_per_head) * 64 + phase * 32) + c;
-  float m = 0.0f;
-#pragma unroll 8
-  for (int r = 0; r < 32; ++r) m = fmaxf(m, fabsf(bf16_bits_to_float(rows[(size_t)r * lv.st])));
-  if (phase == 1) other[c] = m;
-  __syncthreads();
-  if (phase == 0) partial[(size_t)blockIdx.x * 128 + c] = fmaxf(m, other[c]);
-}
-
 // Per KV head: scale[c] = amax / 448 and inv[c] = 448 / amax (1 and 0 for an all-zero channel).  1024 threads as
-// in kmean_kernel.
-__global__ __launch_bounds__(1024) void vscale_kernel(const float* __restrict__ partial, int tiles, float* __restrict__ scale,
-                                                      float* __restrict__ inv) {
-  __shared__ float part[8][128];
+// in kmean_head.
+__device__ __forceinline__ void vscale_head(const float* __restrict__ partial, int tiles, int head, float* __restrict__ scale,
+                                            float* __restrict__ inv, float (*part)[128]) {
   const int c = threadIdx.x & 127, ph = threadIdx.x >> 7;
-  const float* p = partial + (size_t)blockIdx.x * tiles * 128 + c;
+  const float* p = partial + (size_t)head * tiles * 128 + c;
   float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
   int t = ph;
   for (; t + 24 < tiles; t += 32) {
@@ -158,9 +65,17 @@ __global__ __launch_bounds__(1024) void vscale_kernel(const float* __restrict__ 
 #pragma unroll
     for (int i = 0; i < 8; ++i) amax = fmaxf(amax, part[i][c]);
     const bool zero = amax == 0.0f;
-    scale[blockIdx.x * 128 + c] = zero ? 1.0f : amax / 448.0f;
-    inv[blockIdx.x * 128 + c] = zero ? 0.0f : 448.0f / amax;
+    scale[head * 128 + c] = zero ? 1.0f : amax / 448.0f;
+    inv[head * 128 + c] = zero ? 0.0f : 448.0f / amax;
   }
+}
+
+// Workgroups 0 .. n_mean - 1: a KV head's mean key; the rest: its scales of V.
+__global__ __launch_bounds__(1024) void reduce8_kernel(Int8Operands w8, Fp8Operands wv, int n_mean, int tiles, int seq) {
+  __shared__ double lds[8][128];
+  const int b = blockIdx.x;
+  if (b < n_mean) kmean_head(w8.partial, tiles, seq, b, w8.k_mean, lds);
+  else vscale_head(wv.partial, tiles, b - n_mean, wv.v_scale, wv.v_inv, (float (*)[128])lds);
 }
 
 __device__ __forceinline__ uint32_t fp8x4(float a, float b, float c, float d) {
@@ -176,11 +91,11 @@ __device__ __forceinline__ uint32_t fp8x4(float a, float b, float c, float d) {
 // (the order in which the S^T accumulator registers of half-tile j hand P^T to the second product);
 // otherwise row-major [head][key][128 bytes].
 template <bool FRAG>
-__global__ __launch_bounds__(256) void quantize_v8_kernel(const uint16_t* __restrict__ v, Strided lv, int tiles_per_head,
-                                                          const float* __restrict__ inv, uint8_t* __restrict__ out) {
-  __shared__ float sv[64 * (kHeadDim + 1)];      // v * inv, rows padded by one bank
+__device__ __forceinline__ void quantize_v8_tile(const uint16_t* __restrict__ v, const Strided& lv, int tiles_per_head, int block,
+                                                 const float* __restrict__ inv, uint8_t* __restrict__ out,
+                                                 float* sv /* [64][kHeadDim + 1]: v * inv, rows padded by one bank */) {
   const int tid = threadIdx.x;
-  const size_t tile = blockIdx.x;
+  const size_t tile = block;
   const int head = (int)(tile / tiles_per_head);
   const uint16_t* vt = v + row_off(lv, head, (int)(tile % tiles_per_head) * 64);
   const float* iv = inv + (size_t)head * 128;
@@ -226,6 +141,17 @@ __global__ __launch_bounds__(256) void quantize_v8_kernel(const uint16_t* __rest
   }
 }
 
+// Workgroups 0 .. n_k - 1: codes of a 64-row tile of the smoothed K (layout KFRAG of quantize8_block); the rest: FP8 values of
+// one of V (VFRAG: in fragment order; none with the bf16 second product, layout 16).
+template <int KFRAG, bool VFRAG>
+__global__ __launch_bounds__(256) void codes8_kernel(Geo g, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                                                     Int8Operands w8, Fp8Operands wv, int n_k, int tiles) {
+  __shared__ float lds[KFRAG == 16 ? 4 : 64 * (kHeadDim + 1)];
+  const int b = blockIdx.x;
+  if (b < n_k) quantize8_block<KFRAG>(k, g.sk, w8.k_mean, tiles, b, w8.k8, w8.k_scale, lds);
+  else if constexpr (KFRAG != 16) quantize_v8_tile<VFRAG>(v, g.sv, tiles, b - n_k, wv.v_inv, wv.v8, lds);
+}
+
 size_t fp8_operand_bytes(const sale_params_t* p) {
   const size_t kvrows = (size_t)p->batch * p->n_kv_heads * p->seq_len;
   // V values | scales | inverse scales | per-tile maxima
@@ -242,20 +168,6 @@ Fp8Operands carve_fp8_operands(const sale_params_t* p, void* base) {
   w.v_inv = (float*)b;        b += heads * 128 * sizeof(float);
   w.partial = (float*)b;
   return w;
-}
-
-int launch_fp8_operands(const sale_params_t* p, const void* v, const Fp8Operands& w, bool frag, hipStream_t st) {
-  const int n_kvh = p->batch * p->n_kv_heads, tiles = p->seq_len / 64;
-  const Geo g = make_geo(p);
-  vamax_kernel<<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)v, g.sv, tiles, w.partial);
-  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  vscale_kernel<<<dim3((unsigned)n_kvh), dim3(1024), 0, st>>>(w.partial, tiles, w.v_scale, w.v_inv);
-  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  if (frag)
-    quantize_v8_kernel<true><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)v, g.sv, tiles, w.v_inv, w.v8);
-  else
-    quantize_v8_kernel<false><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)v, g.sv, tiles, w.v_inv, w.v8);
-  return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
 }
 
 size_t int8_operand_bytes(const sale_params_t* p) {
@@ -280,29 +192,49 @@ Int8Operands carve_int8_operands(const sale_params_t* p, void* base) {
   return w;
 }
 
-// Fills the operand copies: Q codes row-major, K codes in fragment order (frag_k = 16 or 32, see quantize8_kernel) or row-major (0).
-int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, int frag_k,
-                         hipStream_t st) {
+// The first pass over what is asked for (nullptr: not).
+Pass8 make_pass8(const sale_params_t* p, const void* q, const void* k, const void* v, const Int8Operands* w8, const Fp8Operands* wv) {
   const int n_kvh = p->batch * p->n_kv_heads, n_qh = p->batch * p->n_q_heads, tiles = p->seq_len / 64;
+  Pass8 s = {};
+  s.tiles = tiles;
+  if (w8) {
+    s.nq = n_qh * tiles; s.nk = n_kvh * tiles;
+    s.q = (const uint16_t*)q; s.k = (const uint16_t*)k;
+    s.q8 = w8->q8; s.q_scale = w8->q_scale; s.ksum = w8->partial;
+  }
+  if (wv) { s.nv = n_kvh * tiles; s.v = (const uint16_t*)v; s.vamax = wv->partial; }
+  return s;
+}
+
+// What follows the first pass.  kfrag: layout of the codes of K (16 or 32: in fragment order, see quantize8_block; 0: row-major);
+// V goes into fragment order with 32.
+int launch_operands8(const sale_params_t* p, const void* k, const void* v, const Int8Operands* w8, const Fp8Operands* wv, int kfrag,
+                     hipStream_t st) {
+  const int n_kvh = p->batch * p->n_kv_heads, tiles = p->seq_len / 64, mean = w8 ? n_kvh : 0, scale = wv ? n_kvh : 0;
   const Geo g = make_geo(p);
-  ksum_kernel<<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, tiles, w.partial);
+  const Int8Operands a = w8 ? *w8 : Int8Operands{};
+  const Fp8Operands b = wv ? *wv : Fp8Operands{};
+  reduce8_kernel<<<dim3((unsigned)(mean + scale)), dim3(1024), 0, st>>>(a, b, mean, tiles, p->seq_len);
   if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  kmean_kernel<<<dim3((unsigned)n_kvh), dim3(1024), 0, st>>>(w.partial, tiles, p->seq_len, w.k_mean);
-  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  quantize8_kernel<0><<<dim3((unsigned)(n_qh * tiles)), dim3(256), 0, st>>>((const uint16_t*)q, g.sq, nullptr, tiles,
-                                                                               w.q8, w.q_scale);
-  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
-  if (frag_k == 16)
-    quantize8_kernel<16><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
-                                                                               w.k8, w.k_scale);
-  else if (frag_k == 32)
-    quantize8_kernel<32><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
-                                                                               w.k8, w.k_scale);
-  else
-    quantize8_kernel<0><<<dim3((unsigned)(n_kvh * tiles)), dim3(256), 0, st>>>((const uint16_t*)k, g.sk, w.k_mean, tiles,
-                                                                                  w.k8, w.k_scale);
+  const dim3 grid((unsigned)((mean + scale) * tiles));
+#define SALE_CODES_ARGS g, (const uint16_t*)k, (const uint16_t*)v, a, b, mean * tiles, tiles
+  if (kfrag == 16) codes8_kernel<16, false><<<grid, dim3(256), 0, st>>>(SALE_CODES_ARGS);
+  else if (kfrag == 32) codes8_kernel<32, true><<<grid, dim3(256), 0, st>>>(SALE_CODES_ARGS);
+  else codes8_kernel<0, false><<<grid, dim3(256), 0, st>>>(SALE_CODES_ARGS);
+#undef SALE_CODES_ARGS
   return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
 }
+
+namespace {
+// All of it, for the parity hooks.
+int all_operands8(const sale_params_t* p, const void* q, const void* k, const void* v, const Int8Operands* w8, const Fp8Operands* wv,
+                  hipStream_t st) {
+  const Pass8 pass = make_pass8(p, q, k, v, w8, wv);
+  pass8_kernel<<<dim3((unsigned)pass.blocks()), dim3(256), 0, st>>>(make_geo(p), pass);
+  if (hipGetLastError() != hipSuccess) return SALE_ERR_HIP;
+  return launch_operands8(p, k, v, w8, wv, 0, st);
+}
+}  // namespace
 
 }  // namespace sale
 
@@ -319,7 +251,7 @@ extern "C" int sale_attn_int8_operands(const sale_params_t* p, const void* q, co
   Int8Operands w;
   w.q8 = q8; w.k8 = k8; w.q_scale = q_scale8; w.k_scale = k_scale8; w.k_mean = k_mean;
   w.partial = (double*)ws;
-  return launch_int8_operands(p, q, k, w, 0, (hipStream_t)stream);
+  return all_operands8(p, q, k, nullptr, &w, nullptr, (hipStream_t)stream);
 }
 
 extern "C" int sale_attn_fp8_operands(const sale_params_t* p, const void* v, uint8_t* v8, float* v_scale, void* ws,
@@ -333,5 +265,5 @@ extern "C" int sale_attn_fp8_operands(const sale_params_t* p, const void* v, uin
   w.v8 = v8; w.v_scale = v_scale;
   w.v_inv = (float*)ws;
   w.partial = w.v_inv + (size_t)p->batch * p->n_kv_heads * 128;
-  return launch_fp8_operands(p, v, w, false, (hipStream_t)stream);
+  return all_operands8(p, nullptr, nullptr, v, nullptr, &w, (hipStream_t)stream);
 }

@@ -206,10 +206,11 @@ struct Fp8Operands {
 };
 size_t fp8_operand_bytes(const sale_params_t* p);
 Fp8Operands carve_fp8_operands(const sale_params_t* p, void* base);
-int launch_fp8_operands(const sale_params_t* p, const void* v, const Fp8Operands& w, bool frag, hipStream_t st);
 size_t int8_operand_bytes(const sale_params_t* p);
 Int8Operands carve_int8_operands(const sale_params_t* p, void* base);
-int launch_int8_operands(const sale_params_t* p, const void* q, const void* k, const Int8Operands& w, int frag_k,
-                         hipStream_t st);
+struct Pass8;      // (pass8.h)
+Pass8 make_pass8(const sale_params_t* p, const void* q, const void* k, const void* v, const Int8Operands* w8, const Fp8Operands* wv);
+int launch_operands8(const sale_params_t* p, const void* k, const void* v, const Int8Operands* w8, const Fp8Operands* wv, int kfrag,
+                     hipStream_t st);
 
 }  // namespace sale
