@@ -38,7 +38,8 @@
 //   Sparse: row lengths are heavy-tailed (a query block with one weak row keeps
 //   everything) and differ between heads, so every unit is its own 64-thread
 //   workgroup.  Short sequences: one sweep per row, rows issued by decreasing
-//   kept-block count (a counting sort of row_counts).  Longer ones: the long
+//   kept-block count (a counting sort of row_counts), the shorter half from
+//   queues where that pays (next_in_queue).  Longer ones: the long
 //   rows are swept window by window (a window of K', V' fits an XCD's L2) with
 //   their accumulators parked in the workspace in between, every window launch
 //   is balanced over the XCDs by a table that moves rows of over-loaded heads to
@@ -106,8 +107,10 @@ __global__ __launch_bounds__(1024) void order_units_kernel(Geo g, const int32_t*
 // The same sort as the first workgroups (one per KV head) of the launch of rearrange_kv_kernel, for calls without window
 // launches, whose sort needs no slot counter: one launch less
 // (attention call: one head of 2K tokens 21.2 -> 18.9 us, 4K x 32 heads 136.3 -> 134.0, 16K 820 -> 815).
+constexpr int kQueueStride = 32;      // ints from one queue's counter to the next (see next_in_queue)
 struct OrderJob {
   int heads;                      // 0: nothing to sort
+  int* taken;                     // cleared: the heads' queues (see next_in_queue)
   const int32_t* row_counts;      // nullptr: rows by their length
   int32_t* order;
 };
@@ -143,6 +146,7 @@ __global__ __launch_bounds__(256) void rearrange_kv_kernel(Geo g, OrderJob job, 
                                                            int* __restrict__ slot_counter) {
   __shared__ union { uint16_t sv[64 * (kHeadDim + 2)]; int bin[kOrderBins]; double pass[128]; } lds;
   if ((int)blockIdx.x < job.heads) {
+    if (job.taken && threadIdx.x == 0) job.taken[kQueueStride * blockIdx.x] = 0;
     order_units(g, blockIdx.x, lds.bin, job.row_counts, job.order, nullptr, 0, 0, nullptr);
     return;
   }
@@ -206,6 +210,8 @@ struct RowFilter {
   int win_word;    // first mask word of the window, or < 0
   int win_words;   // words per window
   int tail_from, tail_stride, tail_phase;
+  int* taken;           // issue by queue (below): rows taken from each KV head's queue; nullptr: rows as they come
+  int queue_from;       // first rank in the queues
 };
 
 // order: optional [kv head][rank] -> unit id within the KV head (block * group + head-in-group).
@@ -255,6 +261,40 @@ constexpr int fp8_upto(int i, int nq, int np, int nt, int ops) {
   return done <= 0 ? 0 : done >= total ? ops : (ops * done + total - 1) / total;
 }
 
+// Issue by queue (calls without window launches; see issue_by_queue for which).  Workgroups go to the XCDs round-robin, so with
+// lane = KV head every XCD has the rows of its own heads, and these keep different numbers of blocks: at 16K tokens x 32 heads
+// the XCDs had finished after 690 .. 887 us.  The longer half of a head's sorted rows is issued as before; the rows of rank
+// queue_from .. are a queue, from which a workgroup takes the next row of its own head (whose K', V' its XCD's L2 holds) or,
+// when there is none left, of the head with the most rows left.  The grid has more workgroups than rows, so that an XCD that
+// is done early has some left; those that find nothing only read the counters.  A counter has 128 bytes of its own: next to
+// each other the additions of all XCDs went one by one, and the call took 20 % longer.
+// Attention call, before -> after: 16K x 32 heads bf16 750 -> 689 us, int8 666 -> 624, FP8 630 -> 570; 12K 522 -> 461, 470 -> 435,
+// 447 -> 390.
+__device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, int units, int lane, bool own, int& kvh) {
+  const int n = units - flt.queue_from;
+  for (;; own = true) {      // (a queue found empty stays empty: at most once per head)
+    if (own) {
+      int r = 0;
+      if (lane == 0) r = atomicAdd(&flt.taken[kQueueStride * kvh], 1);
+      r = __builtin_amdgcn_readfirstlane(r);
+      if (r < n) return flt.queue_from + r;
+    }
+    int least = n, at = 0;
+    for (int h = lane; h < n_kvh; h += 64) {
+      const int t = __hip_atomic_load(&flt.taken[kQueueStride * h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t < least) { least = t; at = h; }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const int l = __shfl_xor(least, off, 64), a = __shfl_xor(at, off, 64);
+      if (l < least || (l == least && a < at)) { least = l; at = a; }
+    }
+    least = __builtin_amdgcn_readfirstlane(least);
+    if (least >= n) return units;
+    kvh = __builtin_amdgcn_readfirstlane(at);
+  }
+}
+
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
 // and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 276 - 348
@@ -285,7 +325,11 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   {
     const int b = tail ? (int)blockIdx.x - flt.tail_from : (int)blockIdx.x;
     u.kvh = b % g.n_kvh;
-    const int rank = tail ? (b / g.n_kvh) * flt.tail_stride + flt.tail_phase : (b / g.n_kvh) * WAVES + wave;
+    int rank = tail ? (b / g.n_kvh) * flt.tail_stride + flt.tail_phase : (b / g.n_kvh) * WAVES + wave;
+    if (WAVES == 1 && NT == 2 && flt.taken && rank >= flt.queue_from) {
+      rank = __builtin_amdgcn_readfirstlane(next_in_queue(flt, g.n_kvh, units, lane, rank < units, u.kvh));
+      u.kvh = __builtin_amdgcn_readfirstlane(u.kvh);
+    }
     u.valid = rank < units;
     int id = !u.valid ? 0 : (order ? order[(size_t)u.kvh * units + rank] : units - 1 - rank);
     if (assign && !tail) {
@@ -1009,6 +1053,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 constexpr int kMaxLanes = 256;
 struct LaneLoad { unsigned long long work; int n_in; int pad; };      // per (window, KV head)
 constexpr size_t kLaneLoadBytes = (size_t)(kMaskWordsMax / 2) * kMaxLanes * sizeof(LaneLoad);      // 128 KB
+static_assert(kLaneLoadBytes >= kMaxQueues * kQueueStride * sizeof(int), "without window launches the loads' place holds the queues' counters");
 
 // Shared by the two kernels below: the units of ONE head in ONE window, 1024 threads, thread t looks at the
 // ranks t * per .. of the head's sorted list.
@@ -1204,7 +1249,7 @@ template <bool BK32, bool QK8, bool PV8 = false>
 int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const bf16x8* vp, Qk8 q8o, const uint64_t* mask,
                        const int32_t* row_counts, int32_t* order /* nullptr: as they come */, int32_t* assign, LaneLoad* load, int32_t* slot_of,
                        int* slot_counter, int n_slots, uint16_t* o, float* o32, float* lse, f32x4* st_o, float* st_ml,
-                       bool windows, bool halves, hipStream_t st) {
+                       bool windows, bool halves, bool queues, hipStream_t st) {
   const int units = g.n_qb * g.group;
   const int f = BK32 ? 2 : 1;          // mask bits per 64 keys
   const dim3 grid((unsigned)(units * g.n_kvh));
@@ -1220,10 +1265,15 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
     return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
   if (!windows) {
-    // (one sweep per row: every row reads K', V' of the whole sequence, and moving rows to another XCD costs
-    // more L2 misses than the balance gains: 3.1 against 2.7 ms at 32K)
-    attn_rows_kernel<1, BK32, QK8, PV8><<<grid, dim3(64), 0, st>>>(g, q, kp, vp, q8o, mask, order, nullptr,
-                                                             o, o32, lse, all, nullptr, nullptr);
+    RowFilter flt = all;
+    dim3 issue = grid;
+    if (queues) {      // (what an XCD may take beyond its own heads' rows: an eighth of them)
+      flt.taken = (int*)load;
+      flt.queue_from = units / 2;
+      issue.x += (unsigned)(units / 8 * g.n_kvh);
+    }
+    attn_rows_kernel<1, BK32, QK8, PV8><<<issue, dim3(64), 0, st>>>(g, q, kp, vp, q8o, mask, order, nullptr,
+                                                             o, o32, lse, flt, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? SALE_OK : SALE_ERR_HIP;
   }
 
@@ -1356,7 +1406,9 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const bool by_length = halves && !counts && shape.long_rows_wait;
   if (by_length && !order_at) halves = false;      // (a dense workspace without the order's bytes)
   const bool sort = !windows && (counts || (by_length && halves));
-  const OrderJob job = {sort ? g.n_kvh : 0, mask ? row_counts : nullptr, order_at};
+  const bool queues = counts && !windows && !halves && issue_by_queue({(long)n_units, shape.even_rows, shape.longest, g.n_kvh,
+                                                                                g.group, false, g.bk == 32, qk8, pv8, false});
+  const OrderJob job = {sort ? g.n_kvh : 0, queues ? (int*)w.load : nullptr, mask ? row_counts : nullptr, order_at};
   int32_t* const order = sort || windows ? order_at : nullptr;
   Int8Operands w8 = {};
   Fp8Operands wv = {};
@@ -1383,7 +1435,7 @@ int launch_attn_rows(const sale_params_t* p, const void* q, const void* k, const
   const bf16x8 *kpp = (const bf16x8*)kp, *vpp = (const bf16x8*)vp;
   if (mask) {
 #define SALE_SPARSE_ARGS g, qq, kpp, vpp, q8o, mask, row_counts, order, w.assign, w.load, w.slot_of, w.slot_counter, n_slots, \
-                         (uint16_t*)o, o32, lse, st_o, st_ml, windows, halves, st
+                         (uint16_t*)o, o32, lse, st_o, st_ml, windows, halves, queues, st
     if (g.bk == 32) return qk8 ? launch_sparse_rows<true, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<true, false>(SALE_SPARSE_ARGS);
     if (pv8) return launch_sparse_rows<false, true, true>(SALE_SPARSE_ARGS);
     return qk8 ? launch_sparse_rows<false, true>(SALE_SPARSE_ARGS) : launch_sparse_rows<false, false>(SALE_SPARSE_ARGS);

@@ -1,4 +1,5 @@
-// Which attention calls run with two waves per row (NT = 1 of attn_rows_kernel).  Host only, plain C++.
+// Which attention calls run with two waves per row (NT = 1 of attn_rows_kernel), and which sparse ones of the others take their
+// shorter rows from queues.  Host only, plain C++.
 //
 // A SIMD holds one wave of either form, so 1024 waves run at a time.  Up to 512 rows every half row has a place from the
 // start, and the longest row, which is the call, takes about two thirds of the time.  With more rows the rest waits for
@@ -94,6 +95,23 @@ inline bool two_waves_per_row(const RowSplitCall& c) {
     if (crowded < limit) limit = crowded;
   }
   return c.even_rows <= limit;
+}
+
+// Issue by queue (next_in_queue) of sparse calls with row counts, one wave per row and no window launches.  It evens out the XCDs
+// but lets one read the K', V' of another's heads, and a row from a queue starts later by an atomic addition's round trip.
+// Attention call, us, rows issued by position in the sorted list -> by queue:
+//   bf16            4160 x 32 heads 111 -> 112, 8K 264 -> 265, 10K 356 -> 347, 12K 522 -> 461, 16K 750 -> 689; 12K x 8, batch 3
+//                   433 -> 414; 14K x 40 heads over 2 KV heads 710 -> 698; 16K x 8 (2048 rows) 342.8 -> 344.2
+//   32-key blocks   8K 201 -> 213, 10K 262 -> 271, 12K 379 -> 343, 12K x 8, batch 3 342 -> 354; 16K 538 -> 519, 16 over 2, batch 2
+//                   467 -> 465
+//   int8            8K 266 -> 260, 10K 346 -> 336, 12K 470 -> 435, 16K 666 -> 624
+//   FP8             4160 127 -> 114, 6K x 24 heads 153 -> 141, 8K 260 -> 248, 12K 447 -> 390, 16K 630 -> 570
+// The 16-bit pass is the one whose operands no longer fit its own XCD's L2 above 8K tokens, where there is little left to lose;
+// the FP8 pass asks for half of them.
+constexpr int kMaxQueues = 256;      // (room for the counters)
+inline bool issue_by_queue(const RowSplitCall& c) {
+  if (c.kv_heads < 2 || c.kv_heads > kMaxQueues) return false;
+  return c.fp8 || (c.rows >= 4096 && c.longest >= (c.bk32 ? 256 : 160));
 }
 
 }  // namespace sale
