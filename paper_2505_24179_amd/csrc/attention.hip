@@ -219,7 +219,7 @@ struct RowFilter {
 // pairs of 32-key half-tiles; with b_k = 64 a pair is the two halves of one block, with b_k = 32 it is any
 // two kept half-tiles of the row (the operand copies K', V' are addressable by half-tile).
 // QK8: the first product runs on the 8-bit operands of the quantized Computation-Pass (Sec. 3.4 "Integration
-// with SageAttention") with v_mfma_i32_32x32x32_i8: half the K bytes and half the MFMA time of that product.
+// with SageAttention") with v_mfma_i32_16x16x64_i8 (PV8: 32x32x32): half the K bytes and half the MFMA time of that product.
 struct Qk8 {
   const int8_t* q8;       // [q head][N][128]
   const u32x4* k8p;       // fragment order, 8 KB per 64 keys
@@ -231,7 +231,7 @@ struct Qk8 {
 };
 // PV8 (with QK8, 64-key blocks): the second product in FP8 with v_mfma_f32_32x32x64_f8f6f4 - a quarter of the V
 // bytes and half the MFMA time of that product; see the PV8 section of the kernel.
-constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_half)
+constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_mfma)
 
 // The matrix stream of one phase of the pipeline (see the kernel): nq MFMAs of the first product (kind 0) and np of the
 // second (kind 1), taken in turn by groups of four that share an operand, then the row sums (kind 2), which give the last
@@ -297,9 +297,10 @@ __device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, in
 
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
-// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 276 - 348
-// registers (bf16 316, int8 277, FP8 348) against 374 - 466, where two waves would need 256 or less.  So a row gains because its work is on two SIMDs, not because one wave covers the other's latency.  A
-// query's arithmetic is the same in both, bit for bit.
+// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 270 - 316
+// registers (bf16 316, int8 277, FP8 270) against 410 - 466, where two waves would need 256 or less.  So a row gains because
+// its work is on two SIMDs, not because one wave covers the other's latency.  A query's arithmetic is the same in both, bit
+// for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
 __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g, const uint16_t* __restrict__ q,
                                                                const bf16x8* __restrict__ kp,
@@ -696,17 +697,13 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   f32x4 S[QK8 ? 1 : 2][2][NQ];      // [slot][16-key tile][query tile]: keys 4 g16 .. of query n16
   i32x4 A[QK8 ? 2 : 1][2][NQ];      // QK8: the integer accumulators (see qk_mfma)
   bf16x8 P[2][NQ];                  // keys 4 g16 .. of both 16-key tiles: the B operand of the second product as it is
-  f32x4 lacc;                       // row sums: every register of lane (n16, g16) holds the sum over all keys of query n16 of tile g16
+  f32x4 lacc[NQ];                   // row sums: every register of lane (n16, g16) holds the sum over all keys of query n16
   bf16x8 kf[QK8 ? 1 : 2][QK8 ? 1 : 8], vf[2][8];      // operands of slot mt: K chunk 4 kt + s, V chunk dt
   i32x4 kf8[QK8 ? 2 : 1][QK8 ? 4 : 1];                // K chunk 2 kt + s
-  bf16x8 rows_of[NQ];               // A operand of the row sums of tile qt: ones in rows 4 qt .. 4 qt + 3
+  bf16x8 ones;                      // A operand of the row sums
 #pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) rows_of[qt][e] = (__bf16)(n16 >> 2 == qt ? 1.0f : 0.0f);
-  }
-#pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) asm("" : "+a"(rows_of[qt]));      // (operands that stay go to accumulation registers: the
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  asm("" : "+a"(ones));      // (operands that stay go to accumulation registers: the
   // results of both products and what the vector unit makes take nearly all of the 256 ordinary ones, and a spill in front
   // of the sweep makes its waits for the operand loads those of the reload)
   if constexpr (!QK8) {
@@ -716,13 +713,9 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       for (int ks = 0; ks < 4; ++ks) asm("" : "+a"(qf[qt][ks]));
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) lacc[r] = 0.0f;
-  if (resume) {
+  for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) lacc[r] = g16 == qt ? l_run[qt] : lacc[r];
-  }
+    for (int r = 0; r < 4; ++r) lacc[qt][r] = l_run[qt];
   const i32x4 magic = {0x4B400000, 0x4B400000, 0x4B400000, 0x4B400000};
   constexpr int kSteps = QK8 ? 2 : 4;                                                   // contraction steps of the first product
   constexpr int kQk = 2 * kSteps * NQ, kPv = 8 * NQ, kElems = 8 * NQ;                   // MFMAs of the two products and scores per lane of a phase
@@ -746,9 +739,10 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     o16[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[y][dt], P[y][qt], o16[dt][qt], 0, 0, 0);
   };
   // Row sums of the ROUNDED probabilities, on the matrix unit (v_dot2c_f32_bf16, one per two probabilities, held up the MFMAs
-  // next to it by 18 cycles each).  The query tiles share one accumulator, four rows each.
+  // next to it by 18 cycles each).  (One accumulator for all query tiles, four rows of it each, is 12 registers less, but 0 x NaN
+  // would carry a query's NaN to the others.)
   auto sum_mfma = [&](int y, int qt) __attribute__((always_inline)) {
-    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows_of[qt], P[y][qt], lacc, 0, 0, 0);
+    lacc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[y][qt], lacc[qt], 0, 0, 0);
   };
   auto load_k1 = [&](int t, int y, int n) __attribute__((always_inline)) {      // chunk n of a half-tile's K operands
     if constexpr (QK8) kf8[y][n] = load_chunk<i32x4>(k8t, lane16, t * 4096, n);
@@ -895,26 +889,34 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
     for (int n = 0; n < NQ; ++n) sum_mfma(1, n);
     if (park || again) break;
-    // Did the row stay within reach of its reference?  (O can only have overflowed where the sums are large, or V is beyond
-    // what the sums of probabilities below 1 could stand.)
-    if (__builtin_amdgcn_ballot_w64(!(lacc[0] <= 65536.0f)) == 0ull) break;
-    float odd = !(lacc[0] <= 0x1p100f) ? 1.0f : 0.0f;
+    // Did the row stay within reach of its reference?  (Neither its sum nor O, whatever V is.)
+    float far[NQ], most = 0.0f, top_of[NQ];
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt)
+    for (int qt = 0; qt < NQ; ++qt) {
+      far[qt] = lacc[qt][0] * 0x1p27f;
 #pragma unroll
-      for (int qt = 0; qt < NQ; ++qt)
+      for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) odd = !(__builtin_fabsf(o16[dt][qt][r]) <= 3.0e38f) ? 1.0f : odd;
-    if (__builtin_amdgcn_ballot_w64(odd != 0.0f) == 0ull) break;
+        for (int r = 0; r < 4; ++r) far[qt] = __builtin_elementwise_maximum(far[qt], __builtin_fabsf(o16[dt][qt][r]));
+      most = __builtin_elementwise_maximum(most, far[qt]);
+    }
+    if (__builtin_amdgcn_ballot_w64(!(most <= 0x1.8p127f)) == 0ull) break;
+    // (a query that did keeps its reference, and with it its bits, whichever queries share the wave)
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      far[qt] = !(far[qt] <= 0x1.8p127f) ? 1.0f : 0.0f;
+      far[qt] = fmaxf(far[qt], __shfl_xor(far[qt], 16, 64));
+      far[qt] = fmaxf(far[qt], __shfl_xor(far[qt], 32, 64));
+    }
     // It did not: the row's true maximum, over all its windows, and the sweep again from there.
     if constexpr (kListed) build_list(0, last_word);
     asm("" : "+v"(n_pairs));
     resume = false;
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      m_run[qt] = -INFINITY;
+      top_of[qt] = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) lacc[r] = 0.0f;
+      for (int r = 0; r < 4; ++r) lacc[qt][r] = 0.0f;
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
@@ -932,12 +934,14 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
         float mx[NQ];
         max_of(y, factor(y ? p.kb : p.ka), mx);
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) m_run[qt] = fmaxf(m_run[qt], mx[qt]);
+        for (int qt = 0; qt < NQ; ++qt) top_of[qt] = fmaxf(top_of[qt], mx[qt]);
       }
     }
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) m_run[qt] = far[qt] != 0.0f ? top_of[qt] : m_run[qt];
   }
 #pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) l_run[qt] = __shfl(lacc[0], 16 * qt + n16, 64);
+  for (int qt = 0; qt < NQ; ++qt) l_run[qt] = lacc[qt][0];
   }
 
   if constexpr (NT == 2) if (park) {

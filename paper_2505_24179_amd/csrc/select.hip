@@ -653,9 +653,9 @@ namespace {
 // other), and up to 32K the last rows leave places empty.  The rows are cut so that at most
 // 16384 (row, cut) waves are launched, more than half as many where the limits below do not stop it (about half of them lie
 // above the diagonal and end at once), in powers of two from 8 blocks on (below, the re-encoding of Q~ costs more than the blocks:
-// 4K took 62 us with 4).  Select call, before -> after (the faster re-encoding of Q~ is part of it; without the cut it
-// gave 79.7, 321 and 13100): 4K tokens 85.7 -> 54.8 us, 16K 338 -> 301, 32K 1020 -> 990, 128K (not cut) 13400 -> 13090.
-// With twice as many waves 16K took 314 us, with four times 360; with half as many 304.
+// 4K took 62 us with 4).  Select call, before -> after with the 32x32x64 products it had then (the faster re-encoding of Q~
+// is part of it; without the cut it gave 79.7 and 321): 4K tokens 85.7 -> 54.8 us, 16K 338 -> 301, 32K 1020 -> 990; with the
+// present products 49.8, 287 and 974.  With twice as many waves 16K took 314 us, with four times 360; with half as many 304.
 int select_chunk(const Geo& g, int hpw) {
   const long waves = (long)g.n_qb * (g.group / hpw) * g.n_kvh, blocks = (long)g.words * 64;
   long chunk = 8;

@@ -119,3 +119,29 @@ def test_rows_that_rise_with_the_8_bit_first_product(sale, rise):
         got = lse[0, h].cpu().double() - shift
         ref = torch.logsumexp(s, -1)
         assert ((got - ref).abs() <= 4e-3 + off + 2.0 ** -18 * (ref.abs() + shift.abs())).all()
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n,heads", [(640, 2), (1088, 96)])      # two waves per row; one
+def test_nan_and_infinity_stay_with_their_queries(sale, value, n, heads):
+    """Rows of other queries are the bits they are without the value."""
+    q, k, v = _inputs(n, heads, 0.0, 7)
+    p = sale.Params(1, heads, heads, n)
+    want, want_lse = sale.dense_attn(p, q.cuda(), k.cuda(), v.cuda(), want_lse=True)
+    q[0, 0, 70, 5] = value
+    k[0, 1, 300, 9] = value
+    o, lse = sale.dense_attn(p, q.cuda(), k.cuda(), v.cuda(), want_lse=True)
+    other = torch.ones(1, heads, n, dtype=torch.bool)
+    other[0, 0, 70] = False
+    other[0, 1, 300:] = False
+    assert torch.equal(o.cpu()[other], want.cpu()[other]) and torch.equal(lse.cpu()[other], want_lse.cpu()[other])
+
+
+def test_values_near_the_largest(sale):
+    """A sum of probabilities above 1 times V near the largest float is not within reach: the mean of V, not infinity."""
+    n, heads = 640, 2
+    q, k, v = _inputs(n, heads, 0.0, 8)
+    v[0, :, 70] = 3.0e38
+    p = sale.Params(1, heads, heads, n)
+    o, _ = sale.dense_attn(p, q.cuda(), k.cuda(), v.cuda())
+    assert torch.isfinite(o).all()
