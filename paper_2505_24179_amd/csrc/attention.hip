@@ -298,7 +298,7 @@ __device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, in
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
 // and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 270 - 316
-// registers (bf16 316, int8 277, FP8 270) against 410 - 466, where two waves would need 256 or less.  So a row gains because
+// registers (bf16 316, int8 272, FP8 270) against 410 - 488, where two waves would need 256 or less.  So a row gains because
 // its work is on two SIMDs, not because one wave covers the other's latency.  A query's arithmetic is the same in both, bit
 // for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
