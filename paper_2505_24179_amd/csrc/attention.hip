@@ -19,16 +19,16 @@
 //   register, the B operand of the second product O^T = V^T P^T (up to a
 //   permutation of the contraction index that the V copy applies as well), so P
 //   never leaves registers.
-// * The 16x16x32 shape, because the long calls run at the card's power limit (a
-//   step of 64 keys x 64 queries in 2570 cycles, but at 1.5 GHz): contracting 32
-//   instead of 16 deep it reads and writes its accumulators half as often per
-//   FLOP.  Random operands, matrix stream with the softmax's instructions beside
+// * The 16x16x32 shape, because the long calls run at the card's power limit:
+//   contracting 32 instead of 16 deep it reads and writes its accumulators half
+//   as often per FLOP.  Random operands, matrix stream with exponentials beside
 //   it, per SIMD: 48.2 MFLOP x 32768 / us with 32x32x16, 52.9 with 16x16x32; the
-//   8-bit product alone 54.8 and 64.7.  Dense, 32K x 32 heads: 6.82 -> 6.26 ms.
-// * Softmax in fp32 with exp2 and the scale folded in, against a reference that
-//   a row takes from its first half-tile and keeps (max_of); O accumulates in
-//   fp32.  The finished bf16 tile is transposed through LDS (each wave its own
-//   17 KB, no barrier) so that it leaves as whole 256-byte rows.
+//   8-bit product alone 54.8 and 64.7.  (Dense, 32K x 32 heads, in a kernel that
+//   took no running maximum: 6.82 -> 6.26 ms.)
+// * Softmax in fp32 with exp2 and the scale folded in, against the running
+//   maximum of the row; O accumulates in fp32.  The finished bf16 tile is
+//   transposed through LDS (each wave its own 17 KB, no barrier) so that it
+//   leaves as whole 256-byte rows.
 // * Scheduling.  Few rows, dense and sparse: a workgroup is one unit, its two
 //   waves take 32 queries each.  Otherwise, dense: a workgroup is 4 successive
 //   units of one KV head (with 4 query heads per KV head the same query block:
@@ -233,18 +233,11 @@ struct Qk8 {
 // bytes and half the MFMA time of that product; see the PV8 section of the kernel.
 constexpr float kIntOffset = 12582912.0f;            // 1.5 * 2^23, bit pattern 0x4B400000 (see qk_mfma)
 
-// The matrix stream of one phase of the pipeline (see the kernel): nq MFMAs of the first product (kind 0) and np of the
-// second (kind 1), taken in turn by groups of four that share an operand, then the row sums (kind 2), which give the last
-// scores time to arrive.
+// The matrix stream of one phase of the pipeline (see the kernel): nq MFMAs of the first product (kind 0), whose scores the
+// second half of the phase then looks at, np of the second (kind 1), and the row sums (kind 2).
 struct PhaseStep { int kind, n; };
-constexpr PhaseStep phase_step(int i, int nq, int np, int group) {
-  if (i >= nq + np) return {2, i - nq - np};
-  int iq = 0, ip = 0;
-  for (int k = 0;; ++k) {
-    const bool first = iq < nq && ip % group == 0 && (iq % group != 0 || iq * np <= ip * nq);
-    if (k == i) return {first ? 0 : 1, first ? iq : ip};
-    if (first) ++iq; else ++ip;
-  }
+constexpr PhaseStep phase_step(int i, int nq, int np) {
+  return i < nq ? PhaseStep{0, i} : i < nq + np ? PhaseStep{1, i - nq} : PhaseStep{2, i - nq - np};
 }
 // The same for a step of the FP8 pass: np MFMAs of the second product (kind 1), 64 cycles each, nt of the row sums (kind 2)
 // and nq of the first product (kind 0), 32 cycles each.  fp8_upto: how many of `ops` vector instructions are issued by the end
@@ -297,8 +290,8 @@ __device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, in
 
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
-// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 270 - 316
-// registers (bf16 316, int8 272, FP8 270) against 410 - 488, where two waves would need 256 or less.  So a row gains because
+// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 270 - 312
+// registers (bf16 312, int8 276, FP8 270) against 395 - 453, where two waves would need 256 or less.  So a row gains because
 // its work is on two SIMDs, not because one wave covers the other's latency.  A query's arithmetic is the same in both, bit
 // for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
@@ -423,7 +416,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   f32x4 o16[PV8 ? 1 : 8][PV8 ? 1 : NQ];        // otherwise: O^T in 16x16 tiles, channels 16 dt + 4 g16 .. of query n16 of tile qt
   float m_run[NQ], l_run[NQ];      // m_run in log2 units (PV8: [nt])
 #pragma unroll
-  for (int qt = 0; qt < NQ; ++qt) { m_run[qt] = -INFINITY; l_run[qt] = 0.0f; }
+  for (int qt = 0; qt < NQ; ++qt) { m_run[qt] = PV8 ? -INFINITY : -1e30f; l_run[qt] = 0.0f; }
   if constexpr (PV8) {
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -685,17 +678,22 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   // A software pipeline over half-tiles (32 keys x all queries of the wave), two of them (a pair) per iteration.  Phase t
   //   S(t + 1) = K(t + 1) Q^T       MFMA
   //   O += V(t - 1)^T P(t - 1)^T    MFMA, and the row sums of P(t - 1)
-  //   P(t) = exp2(S(t) - reference) VALU
+  //   P(t) = exp2(S(t) - maximum)   VALU, and the largest of the scores S(t + 1)
   //   loads of K(t + 3), V(t + 1) into the registers that the two products have just read
   // has no branch and no dependency between its three streams, so that they are laid side by side by hand: micro-group i is
   // one MFMA, its share of the VALU stream and of the loads, closed by a scheduling barrier.  (A wave alone on its SIMD
-  // issues one vector instruction inside the 16 cycles of an MFMA for free, two for 4 cycles more; a phase asks for 1.2.)
-  // Before, a step found every block's row maxima, rescaled O where one had grown and walked its mask bits in vector
-  // registers: 290 vector instructions besides the MFMAs instead of 160, and branches that cut the schedule in pieces.
-  // Attention call, before -> after: dense 32K 7.52 -> 6.26 ms, sparse 16K 904 -> 772 us, 32K 2.51 -> 2.19 ms, 128K 33.0 ->
-  // 29.2, 64K with 32-key blocks 6.52 -> 5.88; int8 at 25K 1.52 -> 1.28 ms.
-  f32x4 S[QK8 ? 1 : 2][2][NQ];      // [slot][16-key tile][query tile]: keys 4 g16 .. of query n16
-  i32x4 A[QK8 ? 2 : 1][2][NQ];      // QK8: the integer accumulators (see qk_mfma)
+  // issues one vector instruction inside the 16 cycles of an MFMA for free, two for 4 cycles more; a phase asks for 1.5.)
+  // Between two phases one test: has some row of S(t + 1) grown beyond its maximum?  Then the maximum is raised before
+  // P(t + 1) is made, and O and the row sums, which P(t) has yet to enter at the old one, are scaled after the next phase.
+  // (Before, a step found the maxima across lanes in every block, in front of its exponentials, summed with dot products and
+  // walked its mask bits in vector registers: 290 vector instructions besides the MFMAs instead of 207, and branches that cut
+  // the schedule in pieces.  Without a running maximum it is 168, but then the largest probability of a row is rounded like
+  // the others instead of being 1, and the errors against 64 bits grow by 1 % in O, by 30 % in lse.)
+  // Attention call, before -> after, and without the maximum: dense 32K 7.60 -> 6.77 ms (6.27), sparse 4K 133 -> 124 us (113),
+  // 16K 823 -> 720 (679), 32K 2.45 -> 2.27 ms (2.15), 128K 38.3 -> 35.4 (33.9), 64K with 32-key blocks 7.73 -> 7.11 (6.91);
+  // int8 at 25K 1.49 -> 1.27 (1.18); dense 1K 27.5 -> 28.1 us (24.8).
+  f32x4 S[2][2][NQ];                // [slot][16-key tile][query tile]: keys 4 g16 .. of query n16
+  i32x4 A[2][NQ];                   // QK8: the integer accumulators of the first product (see qk_mfma)
   bf16x8 P[2][NQ];                  // keys 4 g16 .. of both 16-key tiles: the B operand of the second product as it is
   f32x4 lacc[NQ];                   // row sums: every register of lane (n16, g16) holds the sum over all keys of query n16
   bf16x8 kf[QK8 ? 1 : 2][QK8 ? 1 : 8], vf[2][8];      // operands of slot mt: K chunk 4 kt + s, V chunk dt
@@ -706,12 +704,12 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   asm("" : "+a"(ones));      // (operands that stay go to accumulation registers: the
   // results of both products and what the vector unit makes take nearly all of the 256 ordinary ones, and a spill in front
   // of the sweep makes its waits for the operand loads those of the reload)
-  if constexpr (!QK8) {
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt)
+  for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) asm("" : "+a"(qf[qt][ks]));
-  }
+    for (int ks = 0; ks < (QK8 ? 2 : 4); ++ks) {
+      if constexpr (QK8) asm("" : "+a"(qf8[qt][ks])); else asm("" : "+a"(qf[qt][ks]));
+    }
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
@@ -727,7 +725,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       // The integer accumulators start at the bit pattern of kIntOffset = 1.5 * 2^23: an integer x with |x| < 2^22
       // added to it (the sums are below 127 * 127 * 128 < 2^21) gives the bit pattern of the FLOAT kIntOffset + x,
       // so the sums are read as floats without a conversion each; the offset leaves with the scaling FMAs.
-      A[y][kt][qt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf8[y][kSteps * kt + ks], qf8[qt][ks], ks == 0 ? magic : A[y][kt][qt], 0, 0, 0);
+      A[kt][qt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf8[y][kSteps * kt + ks], qf8[qt][ks], ks == 0 ? magic : A[kt][qt], 0, 0, 0);
     } else {
       const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
       S[y][kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[y][kSteps * kt + ks], qf[qt][ks], ks == 0 ? z : S[y][kt][qt], 0, 0, 0);
@@ -759,9 +757,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
     for (int n = 0; n < 8; ++n) load_v1(t, y, n);
   };
-  auto scores = [&](int x, int kt, int qt) __attribute__((always_inline)) -> f32x4 {
-    if constexpr (QK8) return int_bits_as_floats(A[x][kt][qt]); else return S[x][kt][qt];
-  };
+  auto finish = [&](int y, int kt, int qt) __attribute__((always_inline)) { if constexpr (QK8) S[y][kt][qt] = int_bits_as_floats(A[kt][qt]); };      // (no instruction)
   // keys after the query: koff = first key of the half-tile minus first query row of the block (a huge koff empties it)
   auto hide = [&](int x, int koff) __attribute__((always_inline)) {
 #pragma unroll
@@ -771,55 +767,78 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (16 * kt + r > seen) {
-            if constexpr (QK8) A[x][kt][qt][r] = (int)0xFF800000; else S[x][kt][qt][r] = -INFINITY;
-          }
+          if (16 * kt + r > seen) S[x][kt][qt][r] = -INFINITY;
     }
   };
-  // Reference of the exponents, m_run: the row maximum over the first half-tile, and no running maximum after it.  A softmax
-  // is exact for any reference that lets neither the probabilities overflow nor the largest of them vanish: bf16 and fp32 share
-  // their exponent range, so a row may rise 2^100 above its first half-tile.  One that rises further is swept a second time
-  // from its true maximum (below).
-  auto max_of = [&](int x, float ch, float (&mx)[NQ]) __attribute__((always_inline)) {
+  // Reference of the exponents, m_run: the running maximum of each query, half-tile by half-tile (a query that has seen no key
+  // yet: a number below all logits).
+  auto factor = [&](float k_scale) __attribute__((always_inline)) { return QK8 ? k_scale * sq_cs : cs; };      // score -> logit in log2 units
+  auto logit = [&](float v, float ch) __attribute__((always_inline)) { return QK8 ? __builtin_fmaf(v, ch, -kIntOffset * ch) : v * ch; };
+  float seen[NQ];      // (not QK8) m_run as a score
+  float alpha[NQ];     // what the last rise takes O and the row sums by, if they are still ...
+  bool due = false;    // ... to be scaled
+  // (v_maximum3_f32: for v_max3_f32 the compiler first quiets every product that enters.  A NaN makes its query's results NaN anyway.)
+  auto max3 = [](float a, float b, float w) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), w); };
+  // top[qt]: the largest score that a lane holds of query tile qt
+  auto tops_of = [&](int x, float (&top)[NQ]) __attribute__((always_inline)) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      const f32x4 e = scores(x, 0, qt), f = scores(x, 1, qt);
-      float v = fmaxf(fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])), fmaxf(fmaxf(f[0], f[1]), fmaxf(f[2], f[3])));
-      v = fmaxf(v, __shfl_xor(v, 16, 64));
-      v = fmaxf(v, __shfl_xor(v, 32, 64));
-      if constexpr (QK8) mx[qt] = __builtin_fmaf(v, ch, -kIntOffset * ch);
-      else mx[qt] = v * ch;
+      const f32x4 e = S[x][0][qt], f = S[x][1][qt];
+      top[qt] = __builtin_elementwise_maximum(max3(max3(max3(e[0], e[1], e[2]), e[3], f[0]), f[1], f[2]), f[3]);
+    }
+  };
+  auto raise = [&](float (&top)[NQ], float ch) __attribute__((always_inline)) {
+    max_over_rows(top);
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      const float m_new = __builtin_elementwise_maximum(m_run[qt], logit(top[qt], ch));
+      if constexpr (!QK8) seen[qt] = __builtin_elementwise_maximum(seen[qt], top[qt]);
+      alpha[qt] = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
+      m_run[qt] = m_new;
+    }
+  };
+  auto rescale = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      if (__builtin_amdgcn_ballot_w64(alpha[qt] != 1.0f) == 0ull) continue;
+      lacc[qt] *= alpha[qt];
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) o16[dt][qt] *= alpha[qt];
     }
   };
 
   struct Pair { int a, b; float ka, kb; };      // half-tiles of the two slots; QK8: the K scales of their blocks
-  auto factor = [&](float k_scale) __attribute__((always_inline)) { return QK8 ? k_scale * sq_cs : cs; };      // score -> logit in log2 units
-  // One phase.  x: slot whose probabilities are made; y = 1 - x: slot of the two products and of the loads.
-  auto phase = [&](auto xc, float k_scale, int k_next, int v_next) __attribute__((always_inline)) {
+  // One phase.  x: slot whose probabilities are made; y = 1 - x: slot of the two products and of the loads.  more: the scores
+  // made here are complete (no key of theirs is to be hidden), so that their maximum counts.
+  auto phase = [&](auto xc, float k_scale, int k_next, int v_next, float k_scale_next, bool more) __attribute__((always_inline)) {
     constexpr int x = decltype(xc)::value, y = 1 - x;
-    constexpr int groups = kQk + kPv + NQ, slots = (kElems / 2 + 1) * 5;
-    const float ch = factor(k_scale);
-    float mb[NQ], E[kElems];
-    f32x4 F[kElems / 4];
+    constexpr int groups = kQk + kPv + NQ, exps = (kElems / 2 + 1) * 5, slots = exps + 4 * NQ;
+    const float ch = factor(k_scale), ch_next = factor(k_scale_next);
+    float mb[NQ], E[kElems], top[NQ];
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-      mb[qt] = (BK32 && m_run[qt] == -INFINITY) ? 0.0f : m_run[qt];
-      if constexpr (QK8) mb[qt] = __builtin_fmaf(kIntOffset, ch, mb[qt]);      // the accumulators' offset
-    }
+    for (int qt = 0; qt < NQ; ++qt) mb[qt] = QK8 ? __builtin_fmaf(kIntOffset, ch, m_run[qt]) : m_run[qt];      // (QK8: the accumulators' offset)
     // The VALU stream, five instructions per two scores (score e: query tile e / 8, 16-key tile e / 4 % 2, register e % 4):
-    // scale e, exp2 e - 1, scale e + 1, exp2 e, pack e - 2 and e - 1
+    // scale e, exp2 e - 1, scale e + 1, exp2 e, pack e - 2 and e - 1; then four per query tile for the maxima of the next scores
     auto valu = [&](int n) __attribute__((always_inline)) {
-      const int e0 = 2 * (n / 5), o = n % 5;
-      const int e = o == 0 ? e0 : o == 1 ? e0 - 1 : o == 2 ? e0 + 1 : o == 3 ? e0 : e0 - 2;
-      if (e < 0 || e >= kElems) return;
-      if (o == 0 && e % 4 == 0) F[e / 4] = scores(x, e / 4 % 2, e / 8);
-      if (o == 0 || o == 2) E[e] = __builtin_fmaf(F[e / 4][e % 4], ch, -mb[e / 8]);
-      else if (o == 1 || o == 3) E[e] = __builtin_amdgcn_exp2f(E[e]);
-      else { P[x][e / 8][e % 8] = (__bf16)E[e]; P[x][e / 8][e % 8 + 1] = (__bf16)E[e + 1]; }
+      if (n < exps) {
+        const int e0 = 2 * (n / 5), o = n % 5;
+        const int e = o == 0 ? e0 : o == 1 ? e0 - 1 : o == 2 ? e0 + 1 : o == 3 ? e0 : e0 - 2;
+        if (e < 0 || e >= kElems) return;
+        if (o == 0 || o == 2) E[e] = __builtin_fmaf(S[x][e / 4 % 2][e / 8][e % 4], ch, -mb[e / 8]);
+        else if (o == 1 || o == 3) E[e] = __builtin_amdgcn_exp2f(E[e]);
+        else { P[x][e / 8][e % 8] = (__bf16)E[e]; P[x][e / 8][e % 8 + 1] = (__bf16)E[e + 1]; }
+      } else {
+        const int qt = (n - exps) % NQ, o = (n - exps) / NQ;
+        const f32x4 &e = S[y][0][qt], &f = S[y][1][qt];
+        if (o == 0) { finish(y, 0, qt); top[qt] = max3(e[0], e[1], e[2]); }
+        else if (o == 1) { finish(y, 1, qt); top[qt] = max3(top[qt], e[3], f[0]); }
+        else if (o == 2) top[qt] = max3(top[qt], f[1], f[2]);
+        else top[qt] = __builtin_elementwise_maximum(top[qt], f[3]);
+      }
     };
     static_for<groups>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
-      constexpr PhaseStep st = phase_step(i, kQk, kPv, NQ);
+      constexpr PhaseStep st = phase_step(i, kQk, kPv);
       if constexpr (st.kind == 0) {
         qk_mfma(y, st.n);
         if constexpr (st.n % NQ == NQ - 1) load_k1(k_next, y, st.n / NQ);
@@ -833,6 +852,17 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       static_for<to - from>([&](auto vc) __attribute__((always_inline)) { valu(from + decltype(vc)::value); });
       __builtin_amdgcn_sched_barrier(0);
     });
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) asm volatile("" ::"v"(P[x][qt]));      // (the compiler would move their making past the branch, away from the MFMAs)
+    uint64_t rose = 0;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) rose |= QK8 ? __builtin_amdgcn_ballot_w64(logit(top[qt], ch_next) > m_run[qt]) : __builtin_amdgcn_ballot_w64(top[qt] > seen[qt]);
+    const bool grew = more && rose != 0ull;
+    if (__builtin_expect_with_probability(due || grew, 0, 0.99)) {
+      if (due) rescale();
+      due = grew;
+      if (grew) raise(top, ch_next);
+    }
   };
   const auto slot0 = std::integral_constant<int, 0>{};
   const auto slot1 = std::integral_constant<int, 1>{};
@@ -849,7 +879,9 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 
   if constexpr (kListed) build_list(word_lo, word_hi); else n_pairs = tiles;
   asm("" : "+v"(n_pairs));      // (a vector register on purpose: with scalar loop conditions the register allocator copies O^T between the loop's exits and spills)
-  for (bool again = false; n_pairs > 0; again = true) {
+  if (n_pairs > 0) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) seen[qt] = (m_run[qt] - 0x1p-20f * __builtin_fabsf(m_run[qt])) * (1.0f / cs);      // (of a resumed row: not above it)
     Pair c0 = pair_of(entry(0)), c1 = pair_of(entry(1));
     uint32_t ahead = entry(2);
     load_k(c0.a, 0);
@@ -858,9 +890,14 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
     for (int n = 0; n < kQk; ++n) qk_mfma(0, n);
     load_k(c1.a, 0);
-    if (!resume && !again) {
-      if (n_pairs == 1) hide(0, (c0.a - 2 * il) * 32);
-      max_of(0, factor(c0.ka), m_run);
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) { finish(0, 0, qt); finish(0, 1, qt); }
+    if (n_pairs == 1) hide(0, (c0.a - 2 * il) * 32);
+    {
+      float top[NQ];
+      tops_of(0, top);
+      raise(top, factor(c0.ka));
+      due = resume;
     }
     if (BK32 && lone) hide(0, 1 << 24);
     // (nothing to multiply by yet: the first phase adds zeros)
@@ -875,70 +912,28 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     for (int n = 1; n < n_pairs; ++n) {
       const Pair c2 = pair_of(ahead);
       ahead = entry(n + 2);
-      phase(slot0, c0.ka, c1.b, c0.b);
-      phase(slot1, c0.kb, c2.a, c1.a);
+      phase(slot0, c0.ka, c1.b, c0.b, c0.kb, true);
+      phase(slot1, c0.kb, c2.a, c1.a, c1.ka, n + 1 < n_pairs);
       c0 = c1; c1 = c2;
     }
     // the last pair: the diagonal block, if it is kept (its phases make scores that nobody reads)
-    hide(0, lone && n_pairs == 1 ? 1 << 24 : (c0.a - 2 * il) * 32);
-    phase(slot0, c0.ka, c0.b, c0.b);
+    float top[NQ];
+    if (n_pairs > 1) {
+      hide(0, (c0.a - 2 * il) * 32);
+      tops_of(0, top);
+      raise(top, factor(c0.ka));
+      due = true;
+    }
+    phase(slot0, c0.ka, c0.b, c0.b, c0.kb, false);
     hide(1, (c0.b - 2 * il) * 32);
-    phase(slot1, c0.kb, c0.b, c0.b);
+    tops_of(1, top);
+    raise(top, factor(c0.kb));
+    due = true;
+    phase(slot1, c0.kb, c0.b, c0.b, c0.ka, false);
 #pragma unroll
     for (int n = 0; n < kPv; ++n) pv_mfma(1, n);
 #pragma unroll
     for (int n = 0; n < NQ; ++n) sum_mfma(1, n);
-    if (park || again) break;
-    // Did the row stay within reach of its reference?  (Neither its sum nor O, whatever V is.)
-    float far[NQ], most = 0.0f, top_of[NQ];
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-      far[qt] = lacc[qt][0] * 0x1p27f;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) far[qt] = __builtin_elementwise_maximum(far[qt], __builtin_fabsf(o16[dt][qt][r]));
-      most = __builtin_elementwise_maximum(most, far[qt]);
-    }
-    if (__builtin_amdgcn_ballot_w64(!(most <= 0x1.8p127f)) == 0ull) break;
-    // (a query that did keeps its reference, and with it its bits, whichever queries share the wave)
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-      far[qt] = !(far[qt] <= 0x1.8p127f) ? 1.0f : 0.0f;
-      far[qt] = fmaxf(far[qt], __shfl_xor(far[qt], 16, 64));
-      far[qt] = fmaxf(far[qt], __shfl_xor(far[qt], 32, 64));
-    }
-    // It did not: the row's true maximum, over all its windows, and the sweep again from there.
-    if constexpr (kListed) build_list(0, last_word);
-    asm("" : "+v"(n_pairs));
-    resume = false;
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) {
-      top_of[qt] = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) lacc[qt][r] = 0.0f;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o16[dt][qt][r] = 0.0f;
-    }
-    for (int n = 0; n < n_pairs; ++n) {
-      const Pair p = pair_of(entry(n));
-      load_k(p.a, 0);
-      load_k(p.b, 1);
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-#pragma unroll
-        for (int e = 0; e < kQk; ++e) qk_mfma(y, e);
-        hide(y, ((y ? p.b : p.a) - 2 * il) * 32);
-        float mx[NQ];
-        max_of(y, factor(y ? p.kb : p.ka), mx);
-#pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) top_of[qt] = fmaxf(top_of[qt], mx[qt]);
-      }
-    }
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) m_run[qt] = far[qt] != 0.0f ? top_of[qt] : m_run[qt];
   }
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) l_run[qt] = lacc[qt][0];

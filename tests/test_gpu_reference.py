@@ -1,8 +1,6 @@
-"""Rows whose scores rise far above those of their first kept half-tile.
-
-The attention kernels (bf16 and 8-bit first product) take the reference of a row's exponents from its first 32 kept keys
-and sweep a row a second time, from its true maximum, if the sums leave the range of fp32 (by more than 2^100, or by what
-makes O overflow).  Compared with 64-bit attention over the same operands.
+"""The reference of a row's exponents in the attention kernels (bf16 and 8-bit first product): the running maximum of its
+kept keys.  Rows whose scores rise far above those of their first kept half-tile, against 64-bit attention over the same
+operands; rows that take no part in their last window; and the largest probability, which is 1 and is not rounded.
 
 Tolerance: the probabilities and the output are rounded to bf16 (2^-9 of the largest |v| each), the logits carry the rounding
 of fp32 sums and of the scaling FMA, up to 2^-20 of 1000 in the exponent; together below 2^-7 of the largest |v|.
@@ -53,7 +51,7 @@ def _check(o, lse, ref, ref_lse, v):
     assert ((lse.double() - ref_lse).abs()[seen] <= lim).all()
 
 
-@pytest.mark.parametrize("rise", [60.0, 160.0, 2000.0])      # within reach, just out of it, far out
+@pytest.mark.parametrize("rise", [60.0, 160.0, 2000.0])      # beyond fp32 from about 88 on, if nothing were rescaled
 @pytest.mark.parametrize("block_k", [64, 32])
 @pytest.mark.parametrize("n,heads", [(640, 2), (64, 2), (1088, 96)])      # two waves per row; one block; one wave per row
 def test_rows_that_rise_above_their_first_keys(sale, rise, block_k, n, heads):
@@ -79,7 +77,7 @@ def test_rows_that_rise_above_their_first_keys(sale, rise, block_k, n, heads):
 
 
 def test_rows_that_rise_in_the_window_launches(sale):
-    """A row that leaves the range is swept again over all of its windows: the bits of the one-sweep call."""
+    """A row that is parked between windows keeps its maximum: the bits of the one-sweep call."""
     n, heads = 20480, 2
     q, k, v = _inputs(n, heads, 400.0, 6)
     p = sale.Params(1, heads, heads, n)
@@ -95,6 +93,59 @@ def test_rows_that_rise_in_the_window_launches(sale):
         s = (q[0, h, rows].double() @ k[0, h].double().T) / math.sqrt(D)
         s.masked_fill_(torch.arange(n)[None, :] > torch.arange(n)[rows][:, None], -math.inf)
         _check(o[0, h, rows].cpu(), lse[0, h, rows].cpu(), torch.softmax(s, -1) @ v[0, h].double(), torch.logsumexp(s, -1), v[0, h])
+
+
+@pytest.mark.parametrize("block_k,int8", [(64, False), (32, False), (64, True), (32, True)])
+def test_rows_that_keep_nothing_in_their_last_window(sale, block_k, int8):
+    """A row that rises in its parked windows and has no key in the last one: what was parked goes out as it is."""
+    n, heads, clear_from = 20480, 2, 16384
+    q, k, v = _inputs(n, heads, 400.0, 6)
+    p = sale.Params(1, heads, heads, n, block_k=block_k, flags=sale.FLAG_ATTN_INT8_QK if int8 else 0)
+    mask = torch.full((1, heads, p.n_q, p.words), -1, dtype=torch.int64, device="cuda")
+    mask[..., clear_from // block_k // 64:] = 0
+    counts = (torch.arange(1, p.n_q + 1, device="cuda").clamp(max=clear_from // 64) * (64 // block_k)).int()
+    counts = counts.expand(1, heads, -1).contiguous()
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    o, lse = sale.sparse_attn(p, qd, kd, vd, mask, counts, want_lse=True)      # rows above 192 blocks in windows
+    o1, lse1 = sale.sparse_attn(p, qd, kd, vd, mask, None, want_lse=True)      # one sweep per row
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all() and torch.isfinite(lse).all()
+    assert torch.equal(o, o1) and torch.equal(lse, lse1)
+    if not int8:      # (8-bit logits of this size are not those of the bf16 operands)
+        rows = slice(n - 64, n)
+        for h in range(heads):
+            s = (q[0, h, rows].double() @ k[0, h, :clear_from].double().T) / math.sqrt(D)
+            _check(o[0, h, rows].cpu(), lse[0, h, rows].cpu(), torch.softmax(s, -1) @ v[0, h, :clear_from].double(),
+                   torch.logsumexp(s, -1), v[0, h])
+
+
+@pytest.mark.parametrize("block_k", [64, 32])
+@pytest.mark.parametrize("n,heads", [(640, 2), (1088, 96), (20480, 2)])      # two waves per row; one; windows
+def test_the_largest_probability_is_exact(sale, block_k, n, heads):
+    """Rows dominated by one late key: the log-sum-exp is its logit, to the rounding of fp32 (2^-20 of a logit of up to 32).
+    A largest probability that is rounded to bf16 is off by up to 2^-8."""
+    g = torch.Generator().manual_seed(11)
+    q, k, v = (torch.randn(1, heads, n, D, generator=g) for _ in range(3))
+    at = n - n // 8
+    q[..., 0] = 16.0
+    k[..., 0] = 0.0
+    k[:, :, at, 0] = 20.0
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    p = sale.Params(1, heads, heads, n, block_k=block_k)
+    mask = torch.full((1, heads, p.n_q, p.words), -1, dtype=torch.int64, device="cuda")
+    counts = ((torch.arange(p.n_q, device="cuda") + 1) * (64 // block_k)).int().expand(1, heads, -1).contiguous()
+    o, lse = sale.sparse_attn(p, q.cuda(), k.cuda(), v.cuda(), mask, counts, want_lse=True)
+    od, lsed = sale.dense_attn(p, q.cuda(), k.cuda(), v.cuda(), want_lse=True)
+    for h in (0, heads - 1):
+        s = q[0, h, at:].double() @ k[0, h].double().T / math.sqrt(D)
+        s.masked_fill_(torch.arange(n)[None, :] > torch.arange(at, n)[:, None], -math.inf)
+        want = torch.logsumexp(s, -1)
+        assert (s[:, at] - want).min() > -1e-5 and want.max() < 32
+        for got in (lse, lsed):
+            assert (got[0, h, at:].cpu().double() - want).abs().max() <= 2.0 ** -15
+        for got in (o, od):
+            err = (got[0, h, at:].cpu().double() - torch.softmax(s, -1) @ v[0, h].double()).abs()
+            assert err.max() <= 2.0 ** -8 * v[0, h].abs().max()
 
 
 @pytest.mark.parametrize("rise", [60.0, 400.0])
