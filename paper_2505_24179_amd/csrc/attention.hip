@@ -504,7 +504,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     // vector instructions.)
     static_assert(QK8 && !BK32, "the FP8 second product comes with the 8-bit first product on 64-key blocks");
     const float kLog2Top = 8.807354922057604f;      // log2(448)
-    constexpr int kQ8 = 8 * NT, kP8 = 4 * NT, kOps = 103 * NT;
+    constexpr int kQ8 = 8 * NT, kP8 = 4 * NT, kTileOps = 106, kOps = kTileOps * NT;
     i32x4 k8[2][4];
     u32x4 v8[4][2];
     i32x16 S[2][NT];         // [half-tile][query tile]: the integer accumulators, as in the QK8 pass below
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma clang fp contract(off)      // (every copy of the step rounds alike)
       const float cj = k_scale * sq_cs;              // raw integer product -> logit in log2 units
       const float off = kIntOffset * cj;             // what the accumulators' offset amounts to in logit units
-      float mx[NT], mb[NT], E[NT][32];
+      float most[NT], mx[NT], mb[NT], over[NT], up[NT], E[NT][32];
       f32x16 F[NT][2];
       int top[NT][2];
       i32x8 P_new[NT];
@@ -569,9 +569,12 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
         for (int nt = 0; nt < NT; ++nt) now[mt][nt] = S[mt][nt];
       // The VALU stream, per query tile: 16 maxima in two chains (of integers: with the offset all scores are positive floats
       // of one exponent, hidden ones negative), the row maximum, then five instructions per two scores as in `phase`.
+      // The base mb has the size of the accumulators' offset, so it is rounded in steps of about cj: with large scales
+      // (outliers in K) the largest probability would come out above 464, which is NaN in FP8, and a query's NaN would reach
+      // the sums of the queries that share its column there (0 x NaN).  A base that lets it is moved up to where it does not.
       auto valu = [&](int n) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
-        const int nt = n / 103, o = n % 103;
+        const int nt = n / kTileOps, o = n % kTileOps;
         if (o < 16) {
           auto max3 = [](int a, int b, int w) { return max(max(a, b), w); };
           const int mt = o % 2, i = o / 2;
@@ -580,12 +583,19 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
           else if (mt == 0) top[nt][0] = max3(top[nt][0], now[0][nt][15], now[1][nt][15]);
           else top[nt][0] = max(top[nt][0], top[nt][1]);
         } else if (o == 16) {
-          mx[nt] = __builtin_fmaf(max_with_other_half(int_bits_as_float(top[nt][0])), cj, -off);
+          most[nt] = max_with_other_half(int_bits_as_float(top[nt][0]));
+          mx[nt] = __builtin_fmaf(most[nt], cj, -off);
         } else if (o == 17) {
           m_new[nt] = fmaxf(m_run[nt], mx[nt]);
           mb[nt] = m_new[nt] - kLog2Top + off;       // exp2(x - m) * 448, x = (S - offset) * cj
+        } else if (o == 18) {
+          over[nt] = __builtin_fmaf(most[nt], cj, -mb[nt]);
+        } else if (o == 19) {
+          up[nt] = __builtin_fmaf(mb[nt], 1.0f + 0x1p-23f, over[nt] - kLog2Top);      // (at least mb + (over - log2 448), however it is rounded)
+        } else if (o == 20) {
+          mb[nt] = over[nt] > 8.85f ? up[nt] : mb[nt];      // (2^8.85 = 461)
         } else {
-          const int q = o - 18, e0 = 2 * (q / 5), k = q % 5;
+          const int q = o - 21, e0 = 2 * (q / 5), k = q % 5;
           const int e = k == 0 ? e0 : k == 1 ? e0 - 1 : k == 2 ? e0 + 1 : k == 3 ? e0 : e0 - 2;
           if (e < 0 || e >= 32) return;
           if (k == 0 && e % 16 == 0) F[nt][e / 16] = int_bits_as_floats(now[e / 16][nt]);

@@ -146,3 +146,21 @@ def test_fp8_flag_needs_the_8bit_first_product_and_64_key_blocks(sale):
         with pytest.raises(sale.SaleError) as e:
             sale.dense_attn(p, x, x, x, ws=ws)
         assert e.value.status == -3
+
+
+@pytest.mark.parametrize("outlier", [5e3, 1e5, 1e8])
+@pytest.mark.parametrize("n,heads", [(640, 2), (1088, 96)])      # two waves per row; one
+def test_outliers_in_k_leave_every_query_finite(sale, outlier, n, heads):
+    """The exponents carry the rounding of the accumulators' offset, which grows with the scales of the 8-bit operands (at
+    5e3 here the largest probability of a row comes out up to 9 % above 1, beyond the largest FP8 value).  O stays an average of
+    V whatever the weights: with V rounded to FP8 (2^-4) at most 17/16 of the largest |v|, and the bf16 rounding of O.  (At 1e8
+    the offset is rounded in steps of thousands of logits and rows may lose all their weights: O is 0, but no NaN.)"""
+    g = torch.Generator().manual_seed(13)
+    q, k, v = (torch.randn(1, heads, n, 128, generator=g).bfloat16() for _ in range(3))
+    k[:, :, 17::97, 3] = outlier
+    p = sale.Params(1, heads, heads, n, flags=sale.FLAG_ATTN_INT8_QK | sale.FLAG_ATTN_FP8_PV)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    mask = torch.full((1, heads, p.n_q, p.words), -1, dtype=torch.int64, device="cuda")
+    for o, lse in (sale.dense_attn(p, qd, kd, vd, want_lse=True), sale.sparse_attn(p, qd, kd, vd, mask, want_lse=True)):
+        assert torch.isfinite(o).all() and not torch.isnan(lse).any() and (outlier > 1e5 or torch.isfinite(lse).all())
+        assert o.abs().max() <= 17 / 16 * (1 + 2.0 ** -8) * v.abs().max()
