@@ -483,10 +483,11 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     if (lone && lane == 0) list[0] = (uint16_t)first;
     if (lane < 8) list[n + lane] = (uint16_t)last;      // (the loads run up to two pairs ahead, the list is read three ahead)
     n_pairs = BK32 ? n >> 1 : n;
+    wave_exchange();
   };
   auto entry = [&](int n) __attribute__((always_inline)) -> uint32_t {      // of pair n
     if constexpr (!kListed) return (uint32_t)min(n, tiles - 1);
-    else if constexpr (BK32) return *(const uint32_t*)(list + 2 * n);
+    else if constexpr (BK32) return (uint32_t)list[2 * n] | (uint32_t)list[2 * n + 1] << 16;      // (one load)
     else return list[n];
   };
   if constexpr (PV8) {
@@ -1039,6 +1040,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   }
   if (!o32) {
     // (each wave reads back only its own tile: no barrier, LDS operations of a wave complete in order)
+    wave_exchange();
     uint16_t* const out = o + row_off(g.so, u.qh, u.i * 64 + q0);
 #pragma unroll
     for (int it = 0; it < 8 * NT; ++it) {

@@ -111,6 +111,13 @@ __device__ __forceinline__ f32x16 int_bits_as_floats(i32x16 x) {
   return y;
 }
 
+// Between what the lanes of a wave write to LDS and what other lanes of it read: holds the compiler to that order (the hardware
+// keeps it).  No instruction.
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Some value, for an operand that does not matter: no instruction.
 __device__ __forceinline__ int any_int() {
   int x;
