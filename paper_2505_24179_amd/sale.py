@@ -74,12 +74,17 @@ class Params:
             cp._offsets = offsets      # (the host array lives as long as the struct)
         return cp
 
-    # What follows from the fields alone is made once: a call of a small layer is as long as its host side.
+    # What follows from the fields alone is made once: a call of a small layer is as long as its host side.  (Offsets that
+    # are not a tuple may be changed between calls: they are read by every call.)
     @cached_property
+    def _kept(self):
+        return ctypes.byref(self.c())
+
+    @property
     def _contiguous(self):
         """The C struct of contiguous tensors, as an argument.  (The library reads it during the call and never writes it, so
         calls and threads may share it.)"""
-        return ctypes.byref(self.c())
+        return self._kept if isinstance(self.cu_seqlens, tuple) else ctypes.byref(self.c())
 
     @cached_property
     def _ws_bytes(self) -> dict:
@@ -234,7 +239,9 @@ def raw():
 def workspace_bytes(p: Params, which: int) -> int:
     n = p._ws_bytes.get(which)
     if n is None:
-        n = p._ws_bytes[which] = int(_lib.sale_workspace_bytes(p._contiguous, which))
+        n = int(_lib.sale_workspace_bytes(p._contiguous, which))
+        if isinstance(p.cu_seqlens, tuple):
+            p._ws_bytes[which] = n
     return n
 
 

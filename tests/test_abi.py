@@ -188,3 +188,31 @@ def test_strides_are_validated(sale):
     assert call(q_stride=[-8, 256 * 128, 128]) == -2
     # the struct grew at the end: a caller that fills only the leading fields gets contiguous tensors
     assert ctypes.sizeof(good.c()) == 40 + 4 * 3 * 8 + 16      # (+ n_seqs and the offsets pointer)
+
+
+def test_offsets_that_change_are_read_by_every_call(sale):
+    """A list may be refilled between calls; a tuple is read once."""
+    import copy
+    import pickle
+    offsets = [0, 4096, 8192]
+    p = sale.Params(1, 8, 2, 8192, cu_seqlens=offsets)
+    kinds = (sale.WS_SELECT, sale.WS_SPARSE_ATTN, sale.WS_DENSE_ATTN)
+
+    def check(of):
+        fresh = sale.Params(1, 8, 2, 8192, cu_seqlens=tuple(of))
+        assert p.words == fresh.words
+        assert [sale.workspace_bytes(p, w) for w in kinds] == [sale.workspace_bytes(fresh, w) for w in kinds]
+        c = p._contiguous._obj
+        assert [c.cu_seqlens[i] for i in range(c.n_seqs + 1)] == list(of)
+
+    check(offsets)
+    offsets[1] = 640
+    check(offsets)
+    offsets[1:] = [64, 128, 5000 - 5000 % 64, 8192]
+    check(offsets)
+    offsets[:] = [0, 128]                                                # (no longer those of the token axis: refused)
+    assert [sale.workspace_bytes(p, w) for w in kinds] == [0, 0, 0]
+    kept = sale.Params(1, 8, 2, 8192, cu_seqlens=(0, 64, 8192))
+    assert kept._contiguous is kept._contiguous
+    for other in (copy.copy(kept), copy.deepcopy(kept), pickle.loads(pickle.dumps(kept))):
+        assert other == kept and other.cu_seqlens == (0, 64, 8192) and other._contiguous is not kept._contiguous
