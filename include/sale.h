@@ -279,8 +279,9 @@ int sale_dense_attn(const sale_params_t* p, const void* q, const void* k, const 
  * Parity hook: the exact integer products of the Selection-Pass,
  *   out[r][c] = sum_t Q~[q_block*b_q + r][t] * K~[k_block_begin*b_k + c][t]
  * for one (batch*head) index `q_head` (flattened batch*n_q_heads), computed
- * with the same matrix instructions and operand handling the Selection-Pass
- * uses.  out: int32 [b_q][(k_block_end - k_block_begin) * b_k].
+ * with the re-encoding of the codes and the product that the Selection-Pass
+ * uses.  (The Selection-Pass reads K~ from re-encoded copies in its workspace
+ * and keeps only what the products' maxima decide: its masks.)  out: int32 [b_q][(k_block_end - k_block_begin) * b_k].
  */
 int sale_qk_int4_products(const sale_params_t* p, const uint8_t* q4, const uint8_t* k4,
                           int32_t q_head, int32_t q_block,

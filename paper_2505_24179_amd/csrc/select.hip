@@ -371,18 +371,11 @@ __device__ __forceinline__ i32x8 fragment_of_nibbles(const uint8_t* rows16, int 
   return f;
 }
 
-// acc[kt][qt] = (16 K~ rows kt) (16 Q~ rows qt)^T, keys x queries, exact integers held in fp32: register r of a lane is key
-// 4 (lane / 16) + r of query lane % 16.  Neighbouring products share an operand.
-template <int MT>
-__device__ __forceinline__ void qk_tile_fp6(const i32x8 kf[2 * MT], const i32x8 qf[4], f32x4 acc[2 * MT][4]) {
-#pragma unroll
-  for (int kt = 0; kt < 2 * MT; ++kt)
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      const int qt = kt & 1 ? 3 - n : n;
-      const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-      acc[kt][qt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf[kt], qf[qt], z, 2, 2, 0, 0, 0, 0);
-    }
+// (16 K~ rows) (16 Q~ rows)^T, keys x queries, exact integers held in fp32: register r of a lane is key 4 (lane / 16) + r of
+// query lane % 16.
+__device__ __forceinline__ f32x4 qk_fp6(const i32x8& k, const i32x8& q) {
+  const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(k, q, z, 2, 2, 0, 0, 0, 0);
 }
 
 // Maximum over the keys of a block of what one lane holds for query tile nt (16-bit estimate).
@@ -518,10 +511,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       constexpr int u = decltype(uc)::value, v = u - 1;
       static_for<kTiles>([&](auto kc) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value, kt = u % 2 ? kTiles - 1 - k : k;
-        if constexpr (u < kUnits) {
-          const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-          acc[u % 2][kt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(kf[kt], qf[u / 4][u % 4], z, 2, 2, 0, 0, 0, 0);
-        }
+        if constexpr (u < kUnits) acc[u % 2][kt] = qk_fp6(kf[kt], qf[u / 4][u % 4]);
         if constexpr (v >= 0)
           static_for<(k + 1) * kOps / kTiles - k * kOps / kTiles>([&](auto oc) __attribute__((always_inline)) {
             constexpr int o = k * kOps / kTiles + decltype(oc)::value, a = v / 4, half = o / 2;
@@ -616,8 +606,8 @@ __global__ __launch_bounds__(256) void select16_kernel(Geo g, const uint16_t* __
   if (lane == 0) row_counts[(size_t)u.qh * g.n_qb + u.i] = count;
 }
 
-// Parity hook: the integer products themselves, one wave per key block, through the same
-// re-encoding and the same MFMA as the Selection-Pass.
+// Parity hook: the integer products themselves, one wave per key block, through the re-encoding (pack_fp6) and the product
+// (qk_fp6) of select_kernel.  (Which takes K~ from the copies of the pre-pass, and looks at the products' maxima alone.)
 template <int MT>
 __global__ __launch_bounds__(64) void products_kernel(const uint8_t* __restrict__ q4_head, const uint8_t* __restrict__ k4_head,
                                                       int q_block, int k_begin, int n_kblocks, int32_t* __restrict__ out) {
@@ -628,18 +618,18 @@ __global__ __launch_bounds__(64) void products_kernel(const uint8_t* __restrict_
   for (int qt = 0; qt < 4; ++qt) qf[qt] = fragment_of_nibbles(q4_head + ((size_t)q_block * 4 + qt) * 1024, lane);
 #pragma unroll
   for (int kt = 0; kt < 2 * MT; ++kt) kf[kt] = fragment_of_nibbles(k4_head + ((size_t)(k_begin + jb) * 2 * MT + kt) * 1024, lane);
-  f32x4 acc[2 * MT][4];
-  qk_tile_fp6<MT>(kf, qf, acc);
   const size_t ld = (size_t)n_kblocks * (32 * MT);
 #pragma unroll
   for (int kt = 0; kt < 2 * MT; ++kt)
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt)
+    for (int qt = 0; qt < 4; ++qt) {
+      const f32x4 acc = qk_fp6(kf[kt], qf[qt]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int key = 16 * kt + 4 * (lane >> 4) + r, qr = 16 * qt + c;
-        out[(size_t)qr * ld + jb * (32 * MT) + key] = (int32_t)acc[kt][qt][r];
+        out[(size_t)qr * ld + jb * (32 * MT) + key] = (int32_t)acc[r];
       }
+    }
 }
 
 }  // namespace sale
