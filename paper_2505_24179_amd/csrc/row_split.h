@@ -1,5 +1,5 @@
-// Which attention calls run with two waves per row (NT = 1 of attn_rows_kernel), and which sparse ones of the others take their
-// shorter rows from queues.  Host only, plain C++.
+// Which attention calls run with two waves per row (NT = 1 of attn_rows_kernel), which sparse ones of the others take their
+// shorter rows from queues, and how many heads a wave of the Selection-Pass takes.  Host only, plain C++.
 //
 // A SIMD holds one wave of either form, so 1024 waves run at a time.  Up to 512 rows every half row has a place from the
 // start, and the longest row, which is the call, takes about two thirds of the time.  With more rows the rest waits for
@@ -112,6 +112,22 @@ constexpr int kMaxQueues = 256;      // (room for the counters)
 inline bool issue_by_queue(const RowSplitCall& c) {
   if (c.kv_heads < 2 || c.kv_heads > kMaxQueues) return false;
   return c.fp8 || (c.rows >= 4096 && c.longest >= (c.bk32 ? 256 : 160));
+}
+
+// Query heads per wave of select_kernel: four, so that a K~ fragment feeds twice as many products, where rows are long and work
+// is plenty (rows times mask words of the longest); with two there are twice as many waves.  Select call, us, two heads -> four
+// (query / KV heads x tokens):
+//   rows of fewer than 8 mask words  32/8x12K 179 -> 182, x16K 280 -> 287, x20K 402 -> 413, x24.4K 586 -> 601, x28K 751 -> 746;
+//                                    64/8x16K 533 -> 539, x24K 1062 -> 1060
+//   little work                      4/1x32K 145 -> 165, 8/1x30K 239 -> 243, 8/2x32K 266 -> 271
+//   otherwise                        12/1x32K 396 -> 385, 16/2x32K 490 -> 487, 32/8x30K 866 -> 829, x32K 948 -> 942, x48K 1984 ->
+//                                    1941, 4/1x64K 486 -> 478, 8/2x48K 562 -> 555, x64K 915 -> 888, 32/8x64K 3437 -> 3287,
+//                                    4/1x128K 1822 -> 1745, 32/8x128K 13300 -> 12530; two sequences of 32K 1882 -> 1850
+// (A packed call whose longest sequence is not most of it may lose a little: 32K, 12K 1106 -> 1130.)  With 32-key blocks, which
+// have half the maxima per product, two are as fast at 64K (3.66, 3.70 ms) and use fewer registers.
+inline int select_heads_per_wave(bool bk32, int group, long rows, int words) {
+  if (!bk32 && group % 4 == 0 && words >= 8 && rows * words >= 40960) return 4;
+  return group % 2 == 0 ? 2 : 1;
 }
 
 }  // namespace sale

@@ -13,6 +13,7 @@
 // (see below).
 #include <mutex>
 
+#include "row_split.h"
 #include "sale_common.h"
 
 namespace sale {
@@ -658,10 +659,7 @@ int launch_select(const Geo& g, bool est16, const void* q, const void* k, const 
                   const float* q_scale, const float* k_scale, const float* tau, int tau_len, const float* thr_c,
                   float* thr, uint64_t* block_mask, int32_t* row_counts, float* m_out, float* l_out, hipStream_t st) {
   const int tiles = (g.n_qb * g.group + 3) / 4;
-  // Heads per wave of select_kernel: four, so that a K~ fragment feeds twice as many products, where there are waves enough
-  // (select call, four / two heads: 128K x 32 heads 12.7 / 13.3 ms, 32K 974 / 984 us; 16K 302 / 287, 4K 56.6 / 49.8).  With
-  // 32-key blocks, which have half the maxima per product, two are as fast at 64K (3.66 / 3.70 ms) and use fewer registers.
-  const int hpw = MT == 2 && g.group % 4 == 0 && (long)g.n_qb * g.n_qh >= 16384 ? 4 : g.group % 2 == 0 ? 2 : 1;
+  const int hpw = select_heads_per_wave(MT == 1, g.group, (long)g.n_qb * g.n_qh, g.words);
   const int chunk = est16 ? 0 : select_chunk(g, hpw);
   const ClearRows clear = {chunk ? row_counts : nullptr, chunk && chunk < 64 ? block_mask : nullptr};
   const long kgroups = est16 ? 0 : (long)g.n_kvh * (g.seq / 32);

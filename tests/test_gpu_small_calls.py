@@ -23,16 +23,17 @@ def _qkv(tokens, q_heads, kv_heads):
 def _blocks_per_wave(p):
     """Key blocks of a row that one wave scores (0: the whole row): the cut of the library."""
     group = p.n_q_heads // p.n_kv_heads
-    heads = 4 if p.block_k == 64 and group % 4 == 0 else 2 if group % 2 == 0 else 1
+    long = p.words >= 8 and p.batch * p.n_q_heads * p.n_q * p.words >= 40960
+    heads = 4 if p.block_k == 64 and group % 4 == 0 and long else 2 if group % 2 == 0 else 1
     waves, blocks, chunk = p.n_q * (p.n_q_heads // heads) * p.batch, p.words * 64, 8
     while chunk * 16384 < blocks * waves:
         chunk *= 2
     return chunk if chunk < blocks else 0
 
 
-# Every batch takes another cut than the single call (asserted).  In 64-key blocks: 65 blocks, 32 / 8 heads: 8, 16, 32, 64, whole
-# rows; 198 blocks: 32, 64, 128, whole rows.  6 / 2 heads: one head per wave; 4 / 2: two.
-@pytest.mark.parametrize("tokens,q_heads,kv_heads,batches", [(4160, 32, 8, (2, 4, 8, 16)), (12672, 32, 8, (2, 4, 8)),
+# Every batch takes another cut than the single call (asserted).  In 64-key blocks: 65 blocks, 16 / 4 heads: 8, 16, 32, 64, whole
+# rows, 32 / 8 heads: from 16 on; 198 blocks: 64, 128, whole rows.  6 / 2 heads: one head per wave; otherwise two.
+@pytest.mark.parametrize("tokens,q_heads,kv_heads,batches", [(4160, 32, 8, (2, 4, 8, 16)), (4160, 16, 4, (2, 4, 8, 16)), (12672, 32, 8, (2, 4, 8)),
                                                              (4160, 6, 2, (4, 11, 22)), (4160, 4, 2, (33, 64)), (64, 4, 1, (2400,))])
 @pytest.mark.parametrize("block_k,segments", [(64, False), (32, True)])
 def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv_heads, batches, block_k, segments):
@@ -54,6 +55,29 @@ def test_selection_does_not_depend_on_how_rows_are_cut(sale, tokens, q_heads, kv
         mask_n, counts_n, cut = choose(n)
         assert cut != alone, (n, cut)
         assert torch.equal(mask_n, mask.expand_as(mask_n)) and torch.equal(counts_n, counts.expand_as(counts_n)), n
+
+
+# Four heads per wave: the masks of the same heads one by one (one per wave).  833 blocks, 14 words, rows whole and cut; packed: a
+# sequence of 577 blocks among short ones.
+@pytest.mark.parametrize("tokens,q_heads,kv_heads,offsets", [(53312, 4, 1, ()), (36928, 16, 2, ()),
+                                                             (65536, 4, 1, (0, 64, 36992, 36992 + 1024, 65536))])
+def test_selection_does_not_depend_on_heads_per_wave(sale, tokens, q_heads, kv_heads, offsets):
+    gen = torch.Generator(device="cuda").manual_seed(tokens)
+    q, k = (torch.randn(1, h, tokens, 128, generator=gen, device="cuda") for h in (q_heads, kv_heads))
+    q += 0.5 * k.repeat_interleave(q_heads // kv_heads, 1)      # (a query's own key is its largest: few other blocks are kept)
+    q, k, tau = q.bfloat16(), k.bfloat16(), torch.tensor([0.1], device="cuda")
+
+    def choose(qs, ks):
+        p = sale.Params(1, qs.shape[1], ks.shape[1], tokens, cu_seqlens=offsets)
+        return p, *sale.select(p, qs, ks, *sale.quantize_qk(p, qs, ks), tau)[:2]
+
+    p, mask, counts = choose(q, k)
+    assert p.words >= 8 and q_heads * p.n_q * p.words >= 40960      # (four heads)
+    assert 0.05 < counts.float().mean() / (p.n_q / 2) < 0.95      # (some of the blocks that they see)
+    for h in range(q_heads):
+        kv = h * kv_heads // q_heads
+        _, alone, alone_counts = choose(q[:, h:h + 1].contiguous(), k[:, kv:kv + 1].contiguous())
+        assert torch.equal(mask[:, h:h + 1], alone) and torch.equal(counts[:, h:h + 1], alone_counts)
 
 
 # 1024 tokens, 8 / 2 heads: 128 rows alone (two waves per row), 2176 rows seventeen times (one).  704 tokens: an odd

@@ -18,11 +18,15 @@ def rule(tmp_path_factory):
                    'extern "C" int rule(long rows, long even_rows, int longest, int kv_heads, int group, int dense, int bk32, int int8,\n'
                    '                    int fp8, int by_position) {\n'
                    '  return sale::two_waves_per_row({rows, even_rows, longest, kv_heads, group, dense != 0, bk32 != 0, int8 != 0,\n'
-                   '                                  fp8 != 0, by_position != 0});\n}\n')
+                   '                                  fp8 != 0, by_position != 0});\n}\n'
+                   'extern "C" int heads(int bk32, int group, long rows, int words) {\n'
+                   '  return sale::select_heads_per_wave(bk32 != 0, group, rows, words);\n}\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2505_24179_amd", "csrc"), str(src),
                     "-o", str(lib)], check=True)
     fn = ctypes.CDLL(str(lib)).rule
     fn.argtypes = [ctypes.c_long] * 2 + [ctypes.c_int] * 8
+    fn.heads = ctypes.CDLL(str(lib)).heads
+    fn.heads.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     return fn
 
 
@@ -63,3 +67,22 @@ def test_few_rows_always_and_many_never(rule):
                 on = [rule(rows, rows, longest, kv_heads, group, dense, bk32, int8, fp8, False) for rows in range(1, 2200)]
                 limit = sum(on)
                 assert 512 <= limit <= most and all(on[:limit])
+
+
+# Selection-Pass: (query heads, KV heads, tokens): us with two heads per wave, with four
+SELECT = [
+    (32, 8, 12288, 178.8, 182.2), (32, 8, 16384, 280.4, 287.2), (32, 8, 20480, 402.7, 412.8), (32, 8, 25024, 586.2, 601.0),
+    (64, 8, 16384, 532.8, 539.3), (4, 1, 32768, 145.0, 165.5), (8, 1, 30720, 239.5, 242.9), (8, 2, 32768, 266.5, 270.9),
+    (12, 1, 32768, 396.1, 384.7), (32, 8, 30720, 866.9, 829.3), (32, 8, 40960, 1415.4, 1387.8), (32, 8, 49152, 1982.5, 1941.5),
+    (4, 1, 65536, 486.3, 478.2), (8, 2, 49152, 562.3, 554.6), (16, 2, 65536, 1765.9, 1726.5), (8, 2, 65536, 914.8, 887.7),
+    (32, 8, 65536, 3438.3, 3288.1), (4, 1, 131072, 1822.5, 1744.7), (8, 2, 131072, 3468.2, 3429.3), (32, 8, 131072, 13309.0, 12531.1),
+]
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,tokens,two,four", SELECT)
+def test_selection_takes_the_faster_number_of_heads(rule, q_heads, kv_heads, tokens, two, four):
+    assert abs(two - four) >= 0.01 * min(two, four)
+    rows, words = tokens // 64 * q_heads, -(-tokens // 4096)
+    assert rule.heads(0, q_heads // kv_heads, rows, words) == (4 if four < two else 2)
+    assert rule.heads(1, q_heads // kv_heads, rows, words) == 2
+    assert rule.heads(0, 3, rows, words) == 1 and rule.heads(0, 6, rows, words) == 2
