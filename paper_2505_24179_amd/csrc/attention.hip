@@ -290,8 +290,8 @@ __device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, in
 
 // NT: 32-query tiles per wave.  NT = 2: one wave per row (or WAVES rows per workgroup).  NT = 1 (WAVES = 1, no window
 // launches): the two waves of a workgroup take 32 queries each of ONE row: half the MFMAs and half the softmax per wave
-// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 270 - 312
-// registers (bf16 312, int8 276, FP8 270) against 395 - 453, where two waves would need 256 or less.  So a row gains because
+// and key block, the same operand loads (the second wave of a row hits in L1).  Both forms run one wave per SIMD: 268 - 304
+// registers (bf16 304, int8 268, FP8 270) against 393 - 449, where two waves would need 256 or less.  So a row gains because
 // its work is on two SIMDs, not because one wave covers the other's latency.  A query's arithmetic is the same in both, bit
 // for bit.
 template <int WAVES, bool BK32, bool QK8, bool PV8 = false, int NT = 2>
@@ -695,14 +695,18 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   // one MFMA, its share of the VALU stream and of the loads, closed by a scheduling barrier.  (A wave alone on its SIMD
   // issues one vector instruction inside the 16 cycles of an MFMA for free, two for 4 cycles more; a phase asks for 1.5.)
   // Between two phases one test: has some row of S(t + 1) grown beyond its maximum?  Then the maximum is raised before
-  // P(t + 1) is made, and O and the row sums, which P(t) has yet to enter at the old one, are scaled after the next phase.
+  // P(t + 1) is made, and O and the row sums, which P(t) has yet to enter at the old one, are scaled after the next phase, both
+  // for the 16-query tiles with such a row alone.  (A rise costs about 600 cycles, half of it the branches, which a wave alone
+  // on its SIMD waits for.  The sinks and local keys of attention make them rare after the first blocks; on random operands
+  // without either, 8K x 32 / 8 heads, dense, they are a fifth of the call: 529 us, 541 with all tiles treated at once, 414
+  // if none were seen; 556 with the kernel before.)
   // (Before, a step found the maxima across lanes in every block, in front of its exponentials, summed with dot products and
   // walked its mask bits in vector registers: 290 vector instructions besides the MFMAs instead of 207, and branches that cut
   // the schedule in pieces.  Without a running maximum it is 168, but then the largest probability of a row is rounded like
   // the others instead of being 1, and the errors against 64 bits grow by 1 % in O, by 30 % in lse.)
   // Attention call, before -> after, and without the maximum: dense 32K 7.60 -> 6.77 ms (6.27), sparse 4K 133 -> 124 us (113),
   // 16K 823 -> 720 (679), 32K 2.45 -> 2.27 ms (2.15), 128K 38.3 -> 35.4 (33.9), 64K with 32-key blocks 7.73 -> 7.11 (6.91);
-  // int8 at 25K 1.49 -> 1.27 (1.18); dense 1K 27.5 -> 28.1 us (24.8).
+  // int8 at 25K 1.49 -> 1.27 (1.18); dense 1K 27.4 -> 27.7 us (24.8).
   f32x4 S[2][2][NQ];                // [slot][16-key tile][query tile]: keys 4 g16 .. of query n16
   i32x4 A[2][NQ];                   // QK8: the integer accumulators of the first product (see qk_mfma)
   bf16x8 P[2][NQ];                  // keys 4 g16 .. of both 16-key tiles: the B operand of the second product as it is
@@ -786,8 +790,8 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   auto factor = [&](float k_scale) __attribute__((always_inline)) { return QK8 ? k_scale * sq_cs : cs; };      // score -> logit in log2 units
   auto logit = [&](float v, float ch) __attribute__((always_inline)) { return QK8 ? __builtin_fmaf(v, ch, -kIntOffset * ch) : v * ch; };
   float seen[NQ];      // (not QK8) m_run as a score
-  float alpha[NQ];     // what the last rise takes O and the row sums by, if they are still ...
-  bool due = false;    // ... to be scaled
+  float alpha[NQ];     // what the last rise takes O and the row sums of a query tile by, ...
+  uint32_t due = 0;    // ... and the tiles (one bit each) where that is still to be done
   // (v_maximum3_f32: for v_max3_f32 the compiler first quiets every product that enters.  A NaN makes its query's results NaN anyway.)
   auto max3 = [](float a, float b, float w) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), w); };
   // top[qt]: the largest score that a lane holds of query tile qt
@@ -798,24 +802,38 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       top[qt] = __builtin_elementwise_maximum(max3(max3(max3(e[0], e[1], e[2]), e[3], f[0]), f[1], f[2]), f[3]);
     }
   };
-  auto raise = [&](float (&top)[NQ], float ch) __attribute__((always_inline)) {
-    max_over_rows(top);
+  // The tiles with a query that rises above its maximum.  (Ballots: scalars, and so are the branches on them.)
+  struct Rose { uint64_t in[NQ], any; };
+  auto look = [&](const float (&top)[NQ], float ch) __attribute__((always_inline)) -> Rose {
+    Rose r;
+    r.any = 0;
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      const float m_new = __builtin_elementwise_maximum(m_run[qt], logit(top[qt], ch));
-      if constexpr (!QK8) seen[qt] = __builtin_elementwise_maximum(seen[qt], top[qt]);
+      r.in[qt] = QK8 ? __builtin_amdgcn_ballot_w64(logit(top[qt], ch) > m_run[qt]) : __builtin_amdgcn_ballot_w64(top[qt] > seen[qt]);
+      r.any |= r.in[qt];
+    }
+    return r;
+  };
+  auto raise = [&](const Rose& rose, const float (&top)[NQ], float ch) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      if (rose.in[qt] == 0) continue;
+      const float v = max_over_rows(top[qt]), m_new = __builtin_elementwise_maximum(m_run[qt], logit(v, ch));
+      if constexpr (!QK8) seen[qt] = __builtin_elementwise_maximum(seen[qt], v);
       alpha[qt] = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
       m_run[qt] = m_new;
+      due |= 1u << qt;
     }
   };
   auto rescale = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      if (__builtin_amdgcn_ballot_w64(alpha[qt] != 1.0f) == 0ull) continue;
+      if ((due >> qt & 1) == 0) continue;
       lacc[qt] *= alpha[qt];
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) o16[dt][qt] *= alpha[qt];
     }
+    due = 0;
   };
 
   struct Pair { int a, b; float ka, kb; };      // half-tiles of the two slots; QK8: the K scales of their blocks
@@ -865,14 +883,10 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     });
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) asm volatile("" ::"v"(P[x][qt]));      // (the compiler would move their making past the branch, away from the MFMAs)
-    uint64_t rose = 0;
-#pragma unroll
-    for (int qt = 0; qt < NQ; ++qt) rose |= QK8 ? __builtin_amdgcn_ballot_w64(logit(top[qt], ch_next) > m_run[qt]) : __builtin_amdgcn_ballot_w64(top[qt] > seen[qt]);
-    const bool grew = more && rose != 0ull;
-    if (__builtin_expect_with_probability(due || grew, 0, 0.99)) {
-      if (due) rescale();
-      due = grew;
-      if (grew) raise(top, ch_next);
+    Rose rose = look(top, ch_next);
+    if (__builtin_expect_with_probability(due != 0 || (more && rose.any != 0), 0, 0.99)) {
+      rescale();
+      if (more) raise(rose, top, ch_next);
     }
   };
   const auto slot0 = std::integral_constant<int, 0>{};
@@ -889,6 +903,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   };
 
   if constexpr (kListed) build_list(word_lo, word_hi); else n_pairs = tiles;
+  const int pairs = n_pairs;
   asm("" : "+v"(n_pairs));      // (a vector register on purpose: with scalar loop conditions the register allocator copies O^T between the loop's exits and spills)
   if (n_pairs > 0) {
 #pragma unroll
@@ -904,12 +919,10 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) { finish(0, 0, qt); finish(0, 1, qt); }
     if (n_pairs == 1) hide(0, (c0.a - 2 * il) * 32);
-    {
-      float top[NQ];
-      tops_of(0, top);
-      raise(top, factor(c0.ka));
-      due = resume;
-    }
+    float top[NQ];
+    auto look_at = [&](int x, float ch) __attribute__((always_inline)) { tops_of(x, top); raise(look(top, ch), top, ch); };
+    look_at(0, factor(c0.ka));
+    if (!resume) due = 0;      // (O is zero)
     if (BK32 && lone) hide(0, 1 << 24);
     // (nothing to multiply by yet: the first phase adds zeros)
 #pragma unroll
@@ -924,22 +937,19 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
       const Pair c2 = pair_of(ahead);
       ahead = entry(n + 2);
       phase(slot0, c0.ka, c1.b, c0.b, c0.kb, true);
-      phase(slot1, c0.kb, c2.a, c1.a, c1.ka, n + 1 < n_pairs);
+      phase(slot1, c0.kb, c2.a, c1.a, c1.ka, n + 1 < pairs);
       c0 = c1; c1 = c2;
     }
-    // the last pair: the diagonal block, if it is kept (its phases make scores that nobody reads)
-    float top[NQ];
+    // the last pair: the diagonal block, if it is kept
+    c0.a = __builtin_amdgcn_readfirstlane(c0.a);      // (scalars to the compiler again, so that the loads stay single instructions)
+    c0.b = __builtin_amdgcn_readfirstlane(c0.b);
     if (n_pairs > 1) {
       hide(0, (c0.a - 2 * il) * 32);
-      tops_of(0, top);
-      raise(top, factor(c0.ka));
-      due = true;
+      look_at(0, factor(c0.ka));
     }
     phase(slot0, c0.ka, c0.b, c0.b, c0.kb, false);
     hide(1, (c0.b - 2 * il) * 32);
-    tops_of(1, top);
-    raise(top, factor(c0.kb));
-    due = true;
+    look_at(1, factor(c0.kb));
     phase(slot1, c0.kb, c0.b, c0.b, c0.ka, false);
 #pragma unroll
     for (int n = 0; n < kPv; ++n) pv_mfma(1, n);

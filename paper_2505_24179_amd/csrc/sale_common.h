@@ -137,26 +137,14 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(lo, hi);
 }
 
-// v[i] = its maximum over the four lanes that are equal modulo 16 (v_permlane16_swap exchanges odd rows of 16 lanes with even
-// ones; two values at a time share the wait states).  A NaN stays.
-template <int N>
-__device__ __forceinline__ void max_over_rows(float (&v)[N]) {
-  static_assert(N % 2 == 0, "two at a time");
-  float w[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) w[i] = v[i];
-#pragma unroll
-  for (int i = 0; i < N; i += 2)
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3"
-                 : "+v"(v[i]), "+v"(w[i]), "+v"(v[i + 1]), "+v"(w[i + 1]));
-#pragma unroll
-  for (int i = 0; i < N; ++i) w[i] = v[i] = __builtin_elementwise_maximum(v[i], w[i]);
-#pragma unroll
-  for (int i = 0; i < N; i += 2)
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3"
-                 : "+v"(v[i]), "+v"(w[i]), "+v"(v[i + 1]), "+v"(w[i + 1]));
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = __builtin_elementwise_maximum(v[i], w[i]);
+// The maximum over the four lanes that are equal modulo 16 (v_permlane16_swap exchanges odd rows of 16 lanes with even ones).
+// A NaN stays.
+__device__ __forceinline__ float max_over_rows(float v) {
+  float w = v;
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(v), "+v"(w));
+  w = v = __builtin_elementwise_maximum(v, w);
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(v), "+v"(w));
+  return __builtin_elementwise_maximum(v, w);
 }
 
 // Operand copies in fragment order are read through buffer descriptors: an address is descriptor base + scalar tile
