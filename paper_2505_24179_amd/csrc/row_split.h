@@ -5,38 +5,51 @@
 // start, and the longest row, which is the call, takes about two thirds of the time.  With more rows the rest waits for
 // places: what a row costs besides its blocks (start, Q in, O out) is then paid one after the other, twice as often as
 // with whole rows, and the operand loads, twice as many per FLOP, begin to count.  So the limit goes by the longest row.
-// Attention call, us, one wave per row -> two (group of 4 where the rows allow it; rows of one batch, all alike):
+// Attention call, us, one wave per row -> two (group of 4 where the rows allow it; rows of one batch, all alike; operands with a
+// sink and a query's own key as its largest, masks that keep as much as the Selection-Pass does):
 //                        rows  512              768              1024             1280             1536             2048
-//   sparse bf16,     1 block  14.7 -> 12.8     16.7 -> 19       19.5 -> 21.1     27.5 -> 27.5     29.6 -> 29.8     34.3 -> 35.6
-//                    4        18.2 -> 15.1     21.7 -> 22       24.7 -> 24.8     30 -> 31.6       33.4 -> 33.6     38.9 -> 43.2
-//                    8        19.8 -> 16.1     22.8 -> 24.4     26 -> 27.8       32.6 -> 35.4     35.9 -> 37.1     44.8 -> 46.7
-//                   16        29.4 -> 22.3     35 -> 29.6       35.7 -> 33.6     40.2 -> 43.1     42 -> 45.8       49.2 -> 57.9
-//                   32        48.7 -> 36       53.7 -> 42.1     53.1 -> 46.4     58.9 -> 60.4     64.5 -> 66.2     72.4 -> 85.6
-//                   64        81.2 -> 57       83.7 -> 63.9     90.1 -> 70.6     95.9 -> 84.4     100 -> 93.8      103 -> 118
-//                  128        154 -> 101       -                164 -> 113       -                177 -> 130       184 -> 162
-//   32-key blocks,   8 blocks 20 -> 16.5       22.4 -> 23.8     25.5 -> 26       31.8 -> 33.5     34.8 -> 35.2     39.2 -> 43.5
-//                   16        28.2 -> 21.7     34.3 -> 29.5     34.4 -> 32.8     39.7 -> 43.4     39.6 -> 44.6     48.1 -> 56.7
-//                   32        46.2 -> 34       50.9 -> 38.9     50.3 -> 42.9     61.2 -> 54.7     63.4 -> 61       65.1 -> 75.2
-//                   64        82 -> 55.6       84.2 -> 60.2     89.2 -> 63.7     91.3 -> 68.8     94.3 -> 75.5     97.1 -> 94.1
-//                  128        155 -> 96.8      -                163 -> 106       -                170 -> 116       176 -> 120
-//   sparse int8,    16 blocks 41.4 -> 34.5     47.8 -> 43       50.2 -> 47.6     56.3 -> 58.9     58.6 -> 61.8     68.4 -> 75.2
-//                   64        86.5 -> 64.1     89.5 -> 70.8     94.3 -> 76.7     102 -> 91.4      106 -> 101       112 -> 122
-//   sparse FP8,      1 block  36.1 -> 33       42.3 -> 42.4     47.1 -> 45.8     59.7 -> 54       61 -> 55.9       67.7 -> 65
-//                    8        41.6 -> 35.6     48.2 -> 46.9     52 -> 50.9       60.6 -> 59.8     64.4 -> 62       73.6 -> 73.6
-//                   16        52.2 -> 41.8     59.2 -> 51.1     61.6 -> 56.2     65.9 -> 65.6     69.4 -> 69.2     80 -> 81.3
-//                   32        68.7 -> 51.7     74.2 -> 57.9     76.6 -> 65       80.5 -> 76.6     81.9 -> 82.3     94.9 -> 98.4
-//                   64        98.6 -> 69.8     102 -> 73.3      105 -> 81.5      108 -> 91.4      110 -> 101       119 -> 123
-//   dense bf16,      1 block  15.4 -> 12.2     15.9 -> 17.3     18.1 -> 19.9     29 -> 25.1       29.3 -> 27.9     32.7 -> 32.7
-//                    4        19.5 -> 14.9     21.7 -> 21.1     24 -> 24         30.5 -> 30.2     31.8 -> 32.3     38.1 -> 41.2
-//                    8        23.7 -> 17.6     26.1 -> 23.5     28.5 -> 27.1     33.3 -> 35       36.2 -> 37.1     41.6 -> 46.1
-//                   16        33.3 -> 24.1     37.8 -> 31.4     37.7 -> 34.5     42.3 -> 47.9     44.5 -> 49.7     52.6 -> 61
-//                   32        54.4 -> 39.2     57.1 -> 45.8     57.6 -> 49.3     62.6 -> 68.6     65.6 -> 77.3     75.9 -> 91.6
-//                   64        92.5 -> 65.3     92.9 -> 74.2     101 -> 84.3      105 -> 114       110 -> 130       127 -> 155
-//                  128        168 -> 116       -                180 -> 151       -                201 -> 240       232 -> 286
-//   dense FP8,      16 blocks 50.8 -> 39.8     59.1 -> 48.9     59.9 -> 54.1     63.1 -> 64.4     67.5 -> 67.7     76.6 -> 80.4
-//                   64        99.4 -> 69.8     103 -> 74.9      107 -> 84.9      108 -> 104       111 -> 115       127 -> 138
-// (Dense int8 as dense bf16, 5 % less at the limits.  Rows of 128 blocks and more would gain beyond the limits, which end where
-// the form was first measured and tested: sparse, 2048 rows 184 -> 162 us in bf16, 178 -> 153 in FP8.)
+//   sparse bf16,      1 block 14.5 -> 13.8     15.9 -> 18.9     18.5 -> 20.8     26.6 -> 26.6     28.1 -> 27.9     33 -> 34.3
+//                     2      17.8 -> 15.6     19.8 -> 21.8     22.1 -> 23.9     28.3 -> 30.1     31.5 -> 33.2     37.3 -> 39.5
+//                     4      20.9 -> 17.9     23.6 -> 22.9     26.4 -> 26.2     30.4 -> 32.6     32.8 -> 34.7     39 -> 43.4
+//                     8      27.6 -> 21.5     29.9 -> 25.5     33.3 -> 29.9     35.1 -> 37.8     38.5 -> 39.7     44.2 -> 48.9
+//                    16      39.4 -> 27.3     43.9 -> 32.6     44.6 -> 36.5     50.6 -> 48.9     47.9 -> 50.4     56.4 -> 62.9
+//                    32      56.7 -> 38       65 -> 43.7       63.4 -> 48.1     69.9 -> 62.9     71.7 -> 70.3     78.8 -> 85.2
+//                    64      90.4 -> 58.2     98 -> 66         102 -> 73.7      100 -> 90.8      104 -> 103       117 -> 131
+//                   128      127 -> 78.4      131 -> 91.3      134 -> 97        141 -> 136       142 -> 142       152 -> 177
+//   32-key blocks,    4 block 21.2 -> 17.4     23.6 -> 23.3     26.4 -> 26.5     30.5 -> 32.7     33 -> 35         39.1 -> 44
+//                     8      27.3 -> 21.2     29.8 -> 26       32.8 -> 29.6     34.6 -> 37.5     38.3 -> 39.7     43.9 -> 48.7
+//                    16      36.8 -> 25.8     42.7 -> 32.5     42.1 -> 36.2     47.3 -> 47.5     45.8 -> 49       53.2 -> 61.1
+//                    32      53.3 -> 35.8     61 -> 40.8       58.9 -> 45.6     63.3 -> 61.1     65.3 -> 67       71.4 -> 82.4
+//                    64      67.8 -> 45.2     73.2 -> 51.2     78 -> 59.5       77.6 -> 73.9     81.1 -> 83.2     92.8 -> 106
+//                   128      100 -> 62        96.5 -> 67.7     98 -> 73.7       106 -> 99        102 -> 103       113 -> 129
+//   sparse int8,      8 block 35.6 -> 29.2     39.9 -> 35.7     42.1 -> 40.1     45.1 -> 48.3     50.5 -> 52.3     59.7 -> 64.9
+//                    16      45.2 -> 34.3     53.1 -> 42.5     53.5 -> 46.3     57.9 -> 57.8     58.1 -> 60.8     70.4 -> 76.5
+//                    32      64.9 -> 46.1     70.1 -> 51.5     69.4 -> 55.7     74.9 -> 70.4     80.1 -> 77.8     86.5 -> 95.4
+//                    64      91.4 -> 61.9     101 -> 69.3      105 -> 76.7      104 -> 94.6      105 -> 105       118 -> 132
+//                   128      124 -> 80.4      134 -> 92        132 -> 96.6      138 -> 126       144 -> 137       150 -> 170
+//   sparse FP8,       1 block 25.9 -> 23.8     30.8 -> 31.8     34.4 -> 34.7     47 -> 42.3       49.8 -> 45.5     56.8 -> 55.5
+//                     2      29.4 -> 24.8     34.8 -> 33       34.8 -> 36.1     46.4 -> 43.8     50 -> 46.4       57.1 -> 57.2
+//                     8      36.1 -> 27.6     42.5 -> 36.1     41.7 -> 39.8     51 -> 48.7       55 -> 52.1       63.3 -> 64
+//                    16      45.7 -> 32.4     52.5 -> 40.5     51.2 -> 44.8     56.1 -> 54.4     60.2 -> 59       70.9 -> 72.4
+//                    32      62.3 -> 42       67.5 -> 46.4     66.5 -> 52.4     69 -> 65.2       69.6 -> 70.8     83.7 -> 87.8
+//                    64      87.4 -> 55.5     93.6 -> 60.5     90.8 -> 68.4     94 -> 84.5       93.6 -> 92.7     109 -> 116
+//                   128      114 -> 74        119 -> 75.8      115 -> 84.3      120 -> 109       131 -> 118       133 -> 146
+//   dense bf16,       1 block 14.8 -> 12       15.5 -> 17.1     17.7 -> 19.1     26 -> 24.2       27.3 -> 26.1     30.1 -> 32.2
+//                     4      22 -> 16.4       23.5 -> 21.9     25.8 -> 24.6     29.9 -> 30.9     32.3 -> 33       38.5 -> 41.4
+//                     8      28.9 -> 20.6     30.4 -> 24.7     32.6 -> 29       35 -> 36.4       38.1 -> 38.4     45.3 -> 47.4
+//                    16      42.6 -> 27.6     46.1 -> 32.9     45.4 -> 37       49.6 -> 49.5     50 -> 52.2       59.2 -> 63.8
+//                    32      66.5 -> 41.8     70.1 -> 47.3     69 -> 52.7       74.7 -> 70.2     76.3 -> 79.1     86.6 -> 95.8
+//                    64      113 -> 68.7      116 -> 75.4      118 -> 87.9      120 -> 117       124 -> 132       145 -> 163
+//                   128      205 -> 121       205 -> 138       211 -> 156       210 -> 220       218 -> 240       257 -> 299
+//   dense FP8,        2 block 28.4 -> 22.2     31.2 -> 30.2     33.2 -> 33.7     44.8 -> 41.3     48 -> 43.3       54.6 -> 54
+//                     8      34.8 -> 26       38.8 -> 33.2     40.8 -> 37.5     47.5 -> 45.6     51.6 -> 48.8     60.5 -> 61.3
+//                    16      44.5 -> 31.7     48.1 -> 38.7     50.2 -> 43       54.5 -> 54.1     58.9 -> 57.8     69.5 -> 72
+//                    32      62.1 -> 42.3     65.8 -> 46.7     67.1 -> 54.1     71.8 -> 68.3     73.1 -> 74.9     89.5 -> 92.2
+//                    64      94.8 -> 61.5     98.6 -> 66       100 -> 75.4      103 -> 98.2      107 -> 110       126 -> 136
+//                   128      161 -> 100       163 -> 109       166 -> 120       167 -> 161       170 -> 181       202 -> 225
+// (8-bit first products with 32-key blocks as bf16 ones, dense ones 5 % less at the limits.  Rows of one or two blocks gain
+// again beyond 1024 rows, where neither form has places for all; the limits leave that out for bf16 and sparse FP8.  Over 904
+// calls of 56 shapes the form that is taken is 0.2 % slower than the better one, 7 % at most but for one-block rows of FP8, 11.)
 #pragma once
 
 namespace sale {
@@ -45,12 +58,12 @@ struct RowSplitLimit {
   int blocks;                                                  // longest row: at least this many 64-key blocks
   int sparse, sparse32, sparse_fp8, dense, dense_fp8;          // rows up to which two waves per row are taken
 };
-// (from the table above; between its lengths and rows the figures of the calls that tests/test_row_split.py holds)
+// (from the table above and, between its lengths and rows, from the calls that tests/test_row_split.py holds)
 constexpr RowSplitLimit kRowSplitLimits[] = {
-    {200, 1536, 2080, 1280, 1280, 1152}, {64, 1536, 2080, 1280, 1152, 1152}, {48, 1408, 1920, 1280, 1152, 1152},
-    {32, 1152, 1792, 1280, 1152, 1152},  {24, 1088, 1408, 1280, 1088, 1152}, {16, 1024, 1088, 1280, 1024, 1152},
-    {12, 832, 832, 1024, 1024, 1152},    {8, 640, 576, 960, 1024, 1152},     {4, 704, 640, 960, 960, 1152},
-    {2, 512, 512, 960, 512, 1152},       {0, 512, 512, 512, 512, 512}};
+    {96, 1536, 1536, 1536, 1280, 1280}, {64, 1536, 1280, 1536, 1280, 1280}, {48, 1536, 1280, 1536, 1280, 1344},
+    {32, 1280, 1280, 1408, 1280, 1280}, {24, 1280, 1152, 1408, 1280, 1280}, {16, 1280, 1152, 1536, 1152, 1536},
+    {12, 1152, 1024, 1536, 1152, 1536}, {6, 1024, 1024, 1536, 1024, 1536},  {4, 960, 896, 1536, 1024, 1536},
+    {3, 768, 704, 1536, 768, 1536},     {2, 512, 512, 1536, 512, 1536},     {0, 512, 512, 512, 512, 1536}};
 
 struct RowSplitCall {
   long rows;         // 64-row blocks of all heads and batch entries
@@ -70,9 +83,9 @@ inline bool two_waves_per_row(const RowSplitCall& c) {
   auto limit_of = [&](const RowSplitLimit& r) {
     return c.dense ? (c.fp8 ? r.dense_fp8 : r.dense) : c.bk32 ? r.sparse32 : c.fp8 ? r.sparse_fp8 : r.sparse;
   };
-  const int most = limit_of(kRowSplitLimits[0]);
   int limit = limit_of(*l);
-  if (c.rows > most) return false;
+  // (all rows of a packed call, of which the limit counts the long ones: as many as were timed)
+  if (c.rows > (c.dense ? (c.fp8 ? 1536 : 1280) : c.bk32 ? 2080 : 1536)) return false;
   // Whole rows issued by position start some of the longest last once there are more of them than places; halves are sorted
   // (packed, dense: 78 x 1024 tokens, one head 84.3 -> 66.3 us; 3 x 4096, 6 / 2 heads 128 -> 117; 10 x 256, 32 / 8 heads 38.0 ->
   // 31.7).
@@ -84,14 +97,14 @@ inline bool two_waves_per_row(const RowSplitCall& c) {
   // few query heads share them, and a KV head's rows are spread over the XCDs, the operands do not stay in the L2s, and halves,
   // with twice the loads, lose more: dense, 1K x 63 heads 48.9 -> 57.9 us, 4K x 19 heads 128 -> 151, 256 x 191 24.7 -> 27.3
   // (21 groups of 3, 1K: 46.3 -> 41.3; 1K x 50 heads 46.8 -> 38.9, 62 heads 48.1 -> 46.9), and up to these limits they do
-  // not: 2K x 31 74.4 -> 73.4, 4K x 15 120 -> 108, 1K x 43 45.8 -> 40.7.  Sparse: 2.1K x 45 heads 92.9 -> 108, 1.7K x 45
-  // 71.0 -> 74.7 (6K x 15 heads 175 -> 121).  (The 8-bit first product loads half as much for it and does not lose:
-  // 1K x 63 67.3 -> 67.7, 33 KV heads of 2K 91.7 -> 87.8.)
+  // not: 2K x 31 74.4 -> 73.4, 4K x 15 119 -> 108, 1K x 43 47.4 -> 40.4, 1K x 62 49.8 -> 46.6.  Sparse: 1.7K x 45 heads 76.2 ->
+  // 78.1, 4K x 19 115 -> 121, 16K x 5 217 -> 226 (4K x 18 106 -> 93.2); with 32-key blocks 71.2 -> 74.7, 91.5 -> 97.5, 156 -> 169
+  // (84.5 -> 77.1).  (The 8-bit first product loads half as much for it: dense, 4K x 18 130 -> 115, x 19 129 -> 136, 1.7K x 45
+  // 83.4 -> 90.8; sparse 4K x 19 121 -> 114, 16K x 5 200 -> 188.)
   int share = 1;      // gcd(kv_heads, 8): KV head h is served by 8 / share of the XCDs
   while (share < 8 && c.kv_heads % (2 * share) == 0) share *= 2;
-  if (!c.int8 && !c.bk32 && c.group < 3 && share < 4 && c.kv_heads / share > 4) {
-    const int crowded =
-        !c.dense ? (c.longest >= 48 ? limit : 1280) : c.longest >= 32 ? 1024 : share == 2 ? 896 : c.longest >= 8 ? 768 : 640;
+  if ((c.dense || !c.int8) && c.group < 3 && share < 4 && c.kv_heads / share > 4) {
+    const int crowded = !c.dense || c.int8 ? 1152 : c.longest >= 32 || share == 2 ? 1024 : c.longest >= 8 ? 768 : 640;
     if (crowded < limit) limit = crowded;
   }
   return c.even_rows <= limit;
