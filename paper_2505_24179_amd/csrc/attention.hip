@@ -115,22 +115,12 @@ struct OrderJob {
   int32_t* order;
 };
 
-// ---------------------------------------------------------------------------
-// Computation-Pass proper: every wave walks its OWN mask row.
-//
-// The masks of the query heads that share a KV head differ block by block, so
-// staging a tile once for several heads only pays when their bits coincide.
-// Here each wave streams the operands of exactly the blocks its row keeps,
-// straight from global memory into MFMA operand registers: no LDS, no
-// barriers, a skipped block costs nothing.  To make those loads full 1 KB
-// coalesced transactions (and to get V transposed for free) a pre-pass copies
-// K and V once into "fragment order":
+// Fragment order: what one load instruction of the attention kernel reads is 1 KB in a row.
 //   K' [kv head][block j][kt 0..3][s 0..3][lane 0..63]   : 8 channels 32s + 8(lane/16).. of key row 16kt + lane%16
 //   V' [kv head][block j][half 0..1][dt 0..7][lane 0..63] : channel 16dt + lane%16 of the 8 keys
 //                                                           32half + 16(e/4) + 4(lane/16) + e%4,  e = 0..7
 // (the key order inside V' is the order in which the S^T accumulator registers
 // hand P^T to the second product).
-// ---------------------------------------------------------------------------
 // K, V: which copies are made.  The 8-bit first product does not read K' and the FP8 second product not V': without the
 // copies nobody reads the attention call with int8 takes 1496 instead of 1512 us at 25K, with FP8 7446 instead of 7544
 // us at 64K.  (As template parameters: a run-time test kept the loads of V from being in flight with those of K, 28.0
@@ -261,8 +251,8 @@ constexpr int fp8_upto(int i, int nq, int np, int nt, int ops) {
 // when there is none left, of the head with the most rows left.  The grid has more workgroups than rows, so that an XCD that
 // is done early has some left; those that find nothing only read the counters.  A counter has 128 bytes of its own: next to
 // each other the additions of all XCDs went one by one, and the call took 20 % longer.
-// Attention call, before -> after: 16K x 32 heads bf16 750 -> 689 us, int8 666 -> 624, FP8 630 -> 570; 12K 522 -> 461, 470 -> 435,
-// 447 -> 390.
+// Attention call, without -> with: 16K x 32 heads bf16 757 -> 740 us, int8 692 -> 665, FP8 590 -> 568; 12K 518 -> 476, 478 -> 443,
+// 416 -> 379.
 __device__ __forceinline__ int next_in_queue(const RowFilter& flt, int n_kvh, int units, int lane, bool own, int& kvh) {
   const int n = units - flt.queue_from;
   for (;; own = true) {      // (a queue found empty stays empty: at most once per head)
@@ -515,7 +505,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
     i32x8 P8[NT], rows_of[NT];
     f32x4 lacc;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) lacc[r] = 2.0f * (h == 0 ? l_run[0] : l_run[NT - 1]);      // (parked as half the sum: see below)
+    for (int r = 0; r < 4; ++r) lacc[r] = h == 0 ? l_run[0] : l_run[NT - 1];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
@@ -681,9 +671,8 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) sum8(nt);
     }
-    // the common tail adds the two lane halves' partial sums; here every lane already holds the whole sum
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) l_run[nt] = 0.5f * __shfl(lacc[0], c + 32 * nt, 64);
+    for (int nt = 0; nt < NT; ++nt) l_run[nt] = __shfl(lacc[0], c + 32 * nt, 64);      // (the sum of query c of tile nt, in both halves)
   } else {
   // ---- one sweep over the row's kept half-tiles ----------------------------------------------------------
   // A software pipeline over half-tiles (32 keys x all queries of the wave), two of them (a pair) per iteration.  Phase t
@@ -1023,8 +1012,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
   if constexpr (PV8) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const float l_tot = l_run[nt] + swap_half(l_run[nt]);
-      const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+      const float inv = l_run[nt] > 0.0f ? 1.0f / l_run[nt] : 0.0f;
       // O = v_scale[channel] * (sum P8 V8) / (sum P8)
       const float* vs = q8o.v_scale + (size_t)u.kvh * kHeadDim + 4 * h;
 #pragma unroll
@@ -1037,7 +1025,7 @@ __global__ __launch_bounds__(WAVES * (2 / NT) * 64) void attn_rows_kernel(Geo g,
           for (int e = 0; e < 4; ++e) w[e] = oacc[dt][nt][4 * q4 + e] * sc[e] * inv;
           put4(32 * nt + c, 4 * h + 32 * dt + 8 * q4, w);
         }
-      if (lse && h == 0) put_lse(32 * nt + c, m_run[nt], l_tot);
+      if (lse && h == 0) put_lse(32 * nt + c, m_run[nt], l_run[nt]);
     }
   } else {
 #pragma unroll
@@ -1239,9 +1227,9 @@ __global__ __launch_bounds__(1024) void balance_kernel(Geo g, const uint64_t* __
 constexpr int kLongRow = 192;        // rows keeping more than this (12K tokens) are swept window by window
 // Window width in mask words of 64 x 64 keys.  bf16: 8K tokens, 4 MB of K', V' per KV head.  The 8-bit passes read three
 // quarters or half as much per block and shorter steps pay more for every further window: 16K tokens.  Attention call, 8K / 12K /
-// 16K / 32K tokens: FP8 64K 5.39 / 5.26 / 5.19 / 5.36 ms, 128K 20.5 / 19.7 / 19.4 / 20.3; int8 25K 1.33 / 1.28 / 1.26 / 1.25, 64K
-// 6.29 / 6.26 / 6.30 / 6.57, 128K 24.1 / 23.8 / 23.8 / 26.0, 64K with 32-key blocks 5.12 / 5.05 / 4.97 / 5.22; bf16 128K 29.3 /
-// 29.5 / 30.2 / 39.0, 64K with 32-key blocks 5.87 / 5.87 / 6.02 / 6.90.
+// 16K / 32K tokens: FP8 64K 6.28 / 6.15 / 5.99 / 6.36 ms, 128K 23.8 / 23.2 / 23.3 / 24.9; int8 25K 1.35 / 1.31 / 1.27 / 1.30, 64K
+// 7.78 / 7.75 / 7.78 / 8.23, 128K 29.9 / 30.0 / 31.1 / 32.5, 64K with 32-key blocks 6.19 / 6.13 / 6.14 / 6.46; bf16 32K 2.31 /
+// 2.30 / 2.28 / 2.43, 64K 9.21 / 9.26 / 9.32 / 10.6, 128K 35.8 / 37.0 / 37.6 / 44.5, 64K with 32-key blocks 7.20 / 7.25 / 7.29 / 7.96.
 constexpr int kWindowWords = 2, kWindowWords8 = 4;
 constexpr int kWindowMinWords = 4;   // sequences of up to 16K tokens use one sweep per row
 
@@ -1299,8 +1287,8 @@ int launch_sparse_rows(const Geo& g, const uint16_t* q, const bf16x8* kp, const 
   }
 
   // Long rows carry most of the work and keep scattered blocks over the whole sequence: swept
-  // independently they miss L2 on most loads.  They are processed one window of 8K tokens (4 MB of K', V'
-  // per KV head: the size of an XCD's L2) at a time, all rows together, so that the window is served by
+  // independently they miss L2 on most loads.  They are processed one window (kWindowWords: in bf16 4 MB of K', V'
+  // per KV head, the size of an XCD's L2) at a time, all rows together, so that the window is served by
   // the L2 of the XCD that owns the KV head; their accumulators wait in the workspace in between.
   // Measured at 128K tokens (L2 fills / time of the call): one sweep per row 218 GB / 50.7 ms; windows of
   // 16K tokens 121 GB / 37.5 ms; 8K tokens 57 GB / 37.4 ms; 4K tokens 50 GB / 39.1 ms (the parked state

@@ -112,13 +112,13 @@ inline bool two_waves_per_row(const RowSplitCall& c) {
 
 // Issue by queue (next_in_queue) of sparse calls with row counts, one wave per row and no window launches.  It evens out the XCDs
 // but lets one read the K', V' of another's heads, and a row from a queue starts later by an atomic addition's round trip.
-// Attention call, us, rows issued by position in the sorted list -> by queue:
-//   bf16            4160 x 32 heads 111 -> 112, 8K 264 -> 265, 10K 356 -> 347, 12K 522 -> 461, 16K 750 -> 689; 12K x 8, batch 3
-//                   433 -> 414; 14K x 40 heads over 2 KV heads 710 -> 698; 16K x 8 (2048 rows) 342.8 -> 344.2
-//   32-key blocks   8K 201 -> 213, 10K 262 -> 271, 12K 379 -> 343, 12K x 8, batch 3 342 -> 354; 16K 538 -> 519, 16 over 2, batch 2
-//                   467 -> 465
-//   int8            8K 266 -> 260, 10K 346 -> 336, 12K 470 -> 435, 16K 666 -> 624
-//   FP8             4160 127 -> 114, 6K x 24 heads 153 -> 141, 8K 260 -> 248, 12K 447 -> 390, 16K 630 -> 570
+// Attention call of 32 / 8 heads, us, rows issued by position in the sorted list -> by queue:
+//   bf16            4160 tokens 134 -> 134, 8K 294 -> 292, 10K 377 -> 365, 12K 518 -> 476, 16K 757 -> 740
+//   32-key blocks   8K 216 -> 226, 10K 273 -> 280, 12K 370 -> 342, 16K 537 -> 526
+//   int8            8K 275 -> 271, 10K 356 -> 351, 12K 478 -> 443, 16K 692 -> 665; 32-key blocks 8K 225 -> 230, 12K 368 -> 339
+//   FP8             4160 112 -> 112, 6K 163 -> 163, 8K 247 -> 240, 12K 416 -> 379, 16K 590 -> 568
+// (With an earlier step, fewer rows or heads: 14K x 40 heads over 2 710 -> 698, 12K x 8, batch 3 433 -> 414, 16K x 8 (2048 rows)
+// 342.8 -> 344.2; 32-key 12K x 8, batch 3 342 -> 354, 16K, 16 over 2, batch 2 467 -> 465; FP8 6K x 24 153 -> 141.)
 // The 16-bit pass is the one whose operands no longer fit its own XCD's L2 above 8K tokens, where there is little left to lose;
 // the FP8 pass asks for half of them.
 constexpr int kMaxQueues = 256;      // (room for the counters)
